@@ -135,6 +135,8 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   }
   dfree(ctx->sigma_scratch);
   dfree(ctx->pack_stats);
+  dfree(ctx->rec);
+  dfree(ctx->rec_head);
   if (ctx->sigma_host) (void)hipHostFree(ctx->sigma_host);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
   delete ctx;
@@ -572,6 +574,17 @@ static double e_max_of(const ctd_spectrum *sp) {
   return m;
 }
 
+// Energy node nearest to the spectrum's mean energy.
+static int mean_energy_node(const ctd_egrid &eg, const ctd_spectrum *sp) {
+  double wsum = 0.0, emean = 0.0;
+  for (size_t i = 0; i < sp->lo.size(); ++i) {
+    wsum += sp->w[i];
+    emean += sp->w[i] * (sp->lo[i] + 0.5 * sp->width);
+  }
+  emean /= wsum;
+  return std::min(std::max((int)std::lround((emean - eg.e0) / eg.de), 0), eg.ne - 1);
+}
+
 // CTD_TRACK_AUTO: macro-cell majorants pay where one material's attenuation
 // sets the global majorant well above that of the material filling most of
 // the phantom (bone in tissue): at the spectrum's mean energy, the largest
@@ -580,14 +593,8 @@ static double e_max_of(const ctd_spectrum *sp) {
 // the inputs only, so a case's histories do not depend on the machine.
 int ctd::auto_tracking(const ctd_phantom *ph, const ctd_matset *ms, const ctd_spectrum *sp,
                        bool rayleigh) {
-  double wsum = 0.0, emean = 0.0;
-  for (size_t i = 0; i < sp->lo.size(); ++i) {
-    wsum += sp->w[i];
-    emean += sp->w[i] * (sp->lo[i] + 0.5 * sp->width);
-  }
-  emean /= wsum;
   const ctd_egrid &eg = ms->eg;
-  const int j = std::min(std::max((int)std::lround((emean - eg.e0) / eg.de), 0), eg.ne - 1);
+  const int j = mean_energy_node(eg, sp);
   double top = 0.0, bulk = 0.0;
   uint32_t bulk_n = 0;
   for (int m = 0; m < ms->M; ++m) {
@@ -601,6 +608,21 @@ int ctd::auto_tracking(const ctd_phantom *ph, const ctd_matset *ms, const ctd_sp
     }
   }
   return bulk > 0.0 && top > 1.5 * bulk ? CTD_TRACK_MACRO : CTD_TRACK_GLOBAL;
+}
+
+// Share of the global majorant that photoelectric and Compton interactions
+// take up, on average over the voxels, at the spectrum's mean energy: an
+// estimate of the deposits per Woodcock step.  From the inputs alone.
+static double deposit_share(const ctd_phantom *ph, const ctd_matset *ms, const ctd_spectrum *sp,
+                            const std::vector<float> &mu_max) {
+  const int j = mean_energy_node(ms->eg, sp);
+  double sum = 0.0;
+  for (int m = 0; m < ms->M; ++m) {
+    if (!ph->present[m]) continue;
+    const float *r = ms->mu_rho.data() + ((size_t)m * ms->eg.ne + j) * 3;
+    sum += (double)ph->count[m] * 0.5 * (ph->rho_min[m] + ph->rho_max[m]) * ((double)r[0] + r[1]);
+  }
+  return mu_max[(size_t)j] > 0.0f ? sum / ((double)ph->V * mu_max[(size_t)j]) : 0.0;
 }
 
 int ctd::upload_desc(ctd_ctx *ctx, ctd_case *cs) {
@@ -697,6 +719,7 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
     delete cs;
     return set_err(ctx, CTD_EINVAL, "majorant is zero: empty phantom");
   }
+  cs->deposit_share = deposit_share(ph, ms, sp, cs->mu_max);
   const int64_t V = ph->V;
   auto cleanup = [&](int code) {
     free_case_buffers(cs);
@@ -1024,6 +1047,12 @@ extern "C" int32_t ctd_get_tuning(ctd_ctx *ctx, const ctd_case *cs, ctd_tuning *
 
 // ------------------------------------------------------------- launching
 
+// LDS is allocated to workgroups in granules: a workgroup within its share of
+// the CU's LDS but past the last whole granule of it costs the CU a workgroup
+// (32.5 KB with five per CU: 51.8 ms per 2e8 histories of a six-material case
+// against 41.6 ms at 31.0 KB).
+constexpr size_t kLdsGranule = 1280;
+
 // Grid of the persistent transport kernel: waves_per_simd resident waves on
 // each of the 4 SIMDs of every CU.
 static LaunchCfg launch_cfg(const ctd_ctx *ctx, const ctd_tuning &t) {
@@ -1040,7 +1069,114 @@ static LaunchCfg launch_cfg(const ctd_ctx *ctx, const ctd_tuning &t) {
   // LDS per workgroup that keeps 4 x waves_per_simd waves resident per CU
   const int wgs_per_cu = std::max(1, 4 * t.waves_per_simd / (t.block / 64));
   cfg.lds_budget = (size_t)std::min(ctx->lds_per_block, ctx->lds_per_cu / wgs_per_cu);
+  cfg.lds_budget -= cfg.lds_budget % kLdsGranule;
   return cfg;
+}
+
+// Deposit records of a launch (DepositLog).  Fills the cases' buckets and dl
+// and returns true where the launch takes them.  They pay where the tally's
+// atomics, which the memory side performs at 2.4e10/s at best and far slower on
+// few addresses, bound the launch, and cost a little where it is bound by its
+// steps:
+//  - plain steps: the water phantom ran at 94 % of the atomic rate (36.2 ms
+//    per 3e8 histories, 24.9 with records), the 32^3 pencil-beam cube at 3 %
+//    of it on contended words (122 and 8.0 ms per 1e8).  Deferred and
+//    macro-cell steps are bound by instruction issue (head: 22.3 and 26.7 ms,
+//    14.2 and 19.2 ms per 1e8);
+//  - a deposit share (ctd_case::deposit_share) of kRecordShare or more: water
+//    0.65, the water box and cube 0.95, while bodies in air (0.3 and below,
+//    0.15-0.2 deposits per step) ran 3-20 % slower with records;
+//  - kRecordMin histories and kRecordPerVoxel per voxel or more in the launch:
+//    below, the chains' set-up and the tally's flush outweigh the atomics
+//    (water, 1.6e6 voxels: 3e6 histories 472 and 493 us, 1e7 1318 and 1038 us;
+//    cube: 1e5 203 and 265 us, 3e5 432 and 280 us);
+//  - tally mode 0 (modes 1 and 2 name another place for the deposits) without
+//    the event log, in a context that keeps the workspace;
+//  - at most kRecordBuckets buckets per case, so its cursors fit beside the
+//    tables.
+// A bucket holds as few voxels as give at most 64 buckets (32-64 measured
+// best, 128 and more cost the cube 8 % and more: a bucket's open line stays in
+// L2 while a workgroup fills it), at most the 2^14 whose sums fill 128 KB of
+// LDS.
+constexpr uint64_t kRecordMin = 200000, kRecordPerVoxel = 3;
+constexpr double kRecordShare = 0.45;
+constexpr int kRecordBuckets = 1024, kRecordMaxBits = 14;
+constexpr double kRecordsPerHistory = 3.5;   // room; deposits beyond it go to the tally
+constexpr size_t kRecordMaxBytes = (size_t)4 << 30;
+
+static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, RoundCase *rc,
+                         const LaunchCfg &cfg, int kind, bool with_log, DepositLog &dl,
+                         int &tile_voxels) {
+  std::memset(&dl, 0, sizeof dl);
+  if (with_log || cfg.tally_mode != 0 || !ctx->keep_records || kind != kStepPlain) return false;
+  int max_bits = kRecordMaxBits;
+  while (max_bits > 0 && ((size_t)8 << max_bits) > (size_t)ctx->lds_per_block) --max_bits;
+  uint64_t n = 0, voxels = 0;
+  uint32_t total = 0, most = 0;
+  tile_voxels = 0;
+  for (size_t i = 0; i < items.size(); ++i) {
+    if (items[i].deposit_share < kRecordShare) return false;
+    int bits = 0;
+    while (bits < max_bits && ((items[i].V - 1) >> bits) >= 64) ++bits;
+    const uint64_t nb = (uint64_t)((items[i].V - 1) >> bits) + 1;
+    if (nb > kRecordBuckets) return false;
+    rc[i].bucket0 = total;
+    rc[i].buckets = (uint32_t)nb;
+    rc[i].bucket_bits = (uint32_t)bits;
+    total += (uint32_t)nb;
+    most = std::max(most, (uint32_t)nb);
+    tile_voxels = std::max(tile_voxels, (int)std::min<int64_t>((int64_t)1 << bits, items[i].V));
+    n += items[i].n;
+    voxels += (uint64_t)items[i].V;
+  }
+  if (n < kRecordMin || n < kRecordPerVoxel * voxels) return false;
+  dl.buckets = total;
+  dl.cursors = (int32_t)((most + 1) & ~1u);
+  if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors) > cfg.lds_budget) return false;
+  const size_t seg_bytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
+  double want = kRecordsPerHistory * (double)n / ((double)cfg.grid * kLogSeg);
+  want += (double)std::min(total, 2 * most);   // a part-filled segment per bucket
+  size_t per_wg = (size_t)std::ceil(std::min(want, 1e9));
+  const size_t heads = (size_t)cfg.grid * total;
+  const size_t segs_of = ctx->rec_segs;
+  if (ctx->rec_heads < heads || segs_of < per_wg * cfg.grid + 1) {
+    // grown to what the launch wants, within kRecordMaxBytes and an eighth of
+    // the memory that is free (with what is given back first)
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+    const size_t have = segs_of * seg_bytes + ctx->rec_heads * 8;
+    const size_t lim = std::min(kRecordMaxBytes, (free_b + have) / 8);
+    const size_t hb = std::max(ctx->rec_heads, heads) * 8;
+    if (hb >= lim) return false;
+    const size_t segs = std::min((lim - hb) / seg_bytes, std::max(segs_of, per_wg * cfg.grid + 1));
+    if (segs > segs_of || ctx->rec_heads < heads) {
+      if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+      dfree(ctx->rec);
+      dfree(ctx->rec_head);
+      ctx->rec = nullptr;
+      ctx->rec_head = nullptr;
+      ctx->rec_segs = ctx->rec_heads = 0;
+      if (hipMalloc(&ctx->rec, segs * seg_bytes) != hipSuccess ||
+          hipMalloc(&ctx->rec_head, hb) != hipSuccess) {
+        (void)hipGetLastError();
+        dfree(ctx->rec);
+        ctx->rec = nullptr;
+        return false;
+      }
+      ctx->rec_segs = segs;
+      ctx->rec_heads = hb / 8;
+    }
+  }
+  per_wg = std::min(per_wg, (ctx->rec_segs - 1) / (size_t)cfg.grid);
+  if (per_wg == 0) return false;
+  dl.rec = (uint2 *)ctx->rec;
+  dl.prev = (uint32_t *)((char *)ctx->rec + ctx->rec_segs * kLogSeg * sizeof(uint2));
+  dl.head = (unsigned long long *)ctx->rec_head;
+  dl.seg_per_wg = (uint32_t)per_wg;
+  return true;
 }
 
 // Stage one round (RoundCase table, bin prefixes, chunk counter) through a
@@ -1079,6 +1215,9 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
   char *d = (char *)s.dev;
   RoundCase *rc = (RoundCase *)h;
   LaunchCfg cfg = launch_cfg(ctx, t);
+  DepositLog dl;
+  int tile_voxels = 0;
+  const bool records = plan_records(ctx, items, rc, cfg, kind, with_log, dl, tile_voxels);
   uint64_t chunks = 0;
   for (int i = 0; i < nrc; ++i) {
     rc[i].cd = items[i].cd;
@@ -1087,6 +1226,9 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
     rc[i].n = items[i].n;
     rc[i].chunk_begin = chunks;
     rc[i].beamlets = items[i].beamlets;
+    rc[i].tally = items[i].tally;
+    if (!records) rc[i].bucket0 = rc[i].buckets = rc[i].bucket_bits = 0;
+    rc[i].reserved = 0;
     chunks += (items[i].n + (uint64_t)t.chunk - 1) / (uint64_t)t.chunk;
     std::memcpy(h + poff[i], items[i].prefix.data(), 8 * items[i].prefix.size());
   }
@@ -1099,10 +1241,20 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
     cfg.tab_n = std::max(cfg.tab_n, it.tab_n);
     cfg.tab_ne = std::max(cfg.tab_ne, it.tab_ne);
   }
+  const int out = records ? kOutRecords : with_log ? kOutEvents : kOutTally;
+  if (records && launch_zero(dl.head, (size_t)cfg.grid * dl.buckets * 8, ctx->stream) != 0)
+    return hip_err(ctx, hipGetLastError(), "record heads clear");
   if (chunks > 0 &&
       launch_transport((const RoundCase *)d, nrc, chunks, (unsigned long long *)(d + ctr_off),
-                       cfg, with_log, kind, ctx->stream) != 0)
+                       cfg, out, dl, kind, ctx->stream) != 0)
     return hip_err(ctx, hipGetLastError(), "transport launch");
+  if (records) {
+    // two workgroups per CU walk the chains; more slices add more atomics
+    const int slices = std::max(1, (int)(2u * (uint32_t)ctx->n_cu / dl.buckets));
+    if (launch_collect((const RoundCase *)d, nrc, dl, cfg.grid, tile_voxels, slices,
+                       ctx->stream) != 0)
+      return hip_err(ctx, hipGetLastError(), "record collection launch");
+  }
   HIPCHK(ctx, hipEventRecord(s.ev, ctx->stream));
   return CTD_OK;
 }
@@ -1177,6 +1329,9 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
     it.cd = cases[i]->d_desc;
     it.h_begin = cases[i]->h_next;
     it.n = n[i];
+    it.V = cases[i]->ph->V;
+    it.deposit_share = cases[i]->deposit_share;
+    it.tally = cases[i]->d_tally;
     it.step_kind = step_kind(cases[i], t);
     it.tab_n = cases[i]->ms->M * cases[i]->ms->eg.ne;
     it.tab_ne = cases[i]->ms->eg.ne;
@@ -1420,6 +1575,7 @@ extern "C" int32_t ctd_run_batches_static(ctd_ctx *ctx, ctd_case *cs, uint64_t b
   std::memset(&a, 0, sizeof a);
   a.cd = cs->d_desc;
   a.beamlets = cs->d_mh_state ? cs->d_mh_beam : nullptr;
+  a.tally = cs->d_tally;
   a.nbins = nb;
   uint64_t cnt[kStaticMaxBins];
   if (alloc_bins(batch_histories, nb, cs->sp->w.data(), cnt) != CTD_OK)
@@ -1454,8 +1610,9 @@ extern "C" int32_t ctd_run_batches_static(ctd_ctx *ctx, ctd_case *cs, uint64_t b
       return hip_err(ctx, hipGetLastError(), "Metropolis-Hastings fill launch");
     if (launch_static_round_setup(table, a, ctx->stream) != 0 ||
         launch_transport((const RoundCase *)table, 1, chunks,
-                         (unsigned long long *)(table + kStaticCounterOff), cfg, with_log,
-                         step_kind(cs, t), ctx->stream) != 0 ||
+                         (unsigned long long *)(table + kStaticCounterOff), cfg,
+                         with_log ? kOutEvents : kOutTally, DepositLog{}, step_kind(cs, t),
+                         ctx->stream) != 0 ||
         launch_fold(cs->d_tally, t.tally_mode ? kTallyCopies : 1, cs->d_s1, cs->d_s2,
                     cs->ph->V, cs->d_acc, ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "static round launch");

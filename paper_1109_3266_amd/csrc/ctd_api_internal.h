@@ -18,6 +18,9 @@ constexpr int kSigmaBlocks = 1024;
 struct RoundItem {
   const CaseDev *cd;
   uint64_t h_begin, n;
+  int64_t V = 0;                       // voxels of the case
+  double deposit_share = 0.0;          // ctd_case::deposit_share
+  unsigned long long *tally = nullptr; // the batch tally the deposits go to
   std::vector<unsigned long long> prefix;
   const int32_t *beamlets = nullptr;   // Alg. A1 beamlets of the round, or null
   int step_kind = 0;                   // kStepPlain, kStepDeferred or kStepMacro
@@ -43,6 +46,13 @@ struct ctd_ctx {
   double *sigma_scratch = nullptr;
   double *sigma_host = nullptr;
   unsigned int *pack_stats = nullptr;  // [kPackStats] phantom statistics of k_pack
+  // workspace of the deposit records (plan_records): the segments with their
+  // links behind them, and the chain heads; grown on demand, at most
+  // kRecordMaxBytes, freed with the context.  Not kept by a server's contexts,
+  // whose device memory is a budget of its own.
+  bool keep_records = true;
+  void *rec = nullptr, *rec_head = nullptr;
+  size_t rec_segs = 0, rec_heads = 0;
   bool xcd_tally_ok = false;  // every XCC id < kTallyCopies
   unsigned int max_xcc = 0;
   int lds_per_cu = 160 * 1024, lds_per_block = 64 * 1024;  // device LDS limits
@@ -114,6 +124,7 @@ struct ctd_case {
   double e_max = 0.0;
   ctd_tuning tune{};
   std::vector<float> mu_max;
+  double deposit_share = 0.0;   // estimated deposits per Woodcock step
   ctd::CaseDev desc{};
   ctd::CaseDev *d_desc = nullptr;
   float *d_mu_max = nullptr;

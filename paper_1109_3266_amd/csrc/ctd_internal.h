@@ -133,10 +133,34 @@ struct RoundCase {
   const unsigned long long *prefix;
   uint64_t h_begin, n, chunk_begin;
   const int32_t *beamlets;     // [n] Alg. A1 beamlet per history, or null
+  unsigned long long *tally;   // the batch tally ([kTallyCopies][V] in modes 1, 2)
+  // deposit records: the case's buckets [bucket0, bucket0 + buckets) of the
+  // launch, each of 2^bucket_bits consecutive voxels
+  uint32_t bucket0, buckets, bucket_bits, reserved;
   // the case's home workgroups [wg_lo, next case's wg_lo) of the launch's
   // grid (home_round_cases); home_waves = their waves, which take the case's
   // first chunks by rank
   uint32_t wg_lo, home_waves;
+};
+
+// Where a transport launch leaves its deposits: added to the batch tallies
+// as they happen (also with the event log on), or appended to DepositLog for
+// k_collect.
+constexpr int kOutTally = 0, kOutEvents = 1, kOutRecords = 2;
+
+// Deposit records of a launch.  Every workgroup owns seg_per_wg segments of
+// kLogSeg records (numbered from 1: 0 is none) and appends a deposit to the
+// segment its LDS cursor of the voxel's bucket points to; prev links a
+// bucket's segments of one workgroup, head[workgroup][bucket] = (last
+// segment, records in it) once the workgroup has left the bucket's case.
+constexpr uint32_t kLogSeg = 256;
+struct DepositLog {
+  uint2 *rec;                // [segments][kLogSeg] (voxel within the bucket, q)
+  uint32_t *prev;            // [segments]
+  unsigned long long *head;  // [workgroups][buckets], zero before the launch
+  uint32_t seg_per_wg;
+  uint32_t buckets;          // of the whole launch
+  int32_t cursors;           // largest bucket count of one case, padded to even
 };
 
 // Fill wg_lo and home_waves of a round's cases (chunk_begin already set) for
@@ -169,6 +193,7 @@ struct StaticRoundArgs {
   const CaseDev *cd;
   uint64_t h_begin, n;
   const int32_t *beamlets;
+  unsigned long long *tally;
   int32_t nbins;
   uint32_t home_waves;   // every wave of the grid: the one case is everyone's home
   unsigned long long prefix[kStaticMaxBins + 1];
@@ -196,16 +221,23 @@ constexpr int kStepPlain = 0, kStepDeferred = 1, kStepMacro = 2;
 
 // Kernel launchers (ctd_kernels.hip).  All enqueue on `stream`.
 int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,
-                     unsigned long long *chunk_ctr, const LaunchCfg &cfg, bool with_log,
-                     int step_kind, void *stream);
+                     unsigned long long *chunk_ctr, const LaunchCfg &cfg, int out,
+                     const DepositLog &dl, int step_kind, void *stream);
+// Add the records that a kOutRecords launch of `wgs` workgroups left to the
+// batch tallies: `slices` workgroups per bucket, LDS for tile_voxels sums (the
+// largest bucket).
+int launch_collect(const RoundCase *rc_dev, int nrc, const DepositLog &dl, int wgs,
+                   int tile_voxels, int slices, void *stream);
 // Whether a transport workgroup of `block` threads in tally_mode fits the
 // device's LDS limit (mode 2 adds a sub-tally per wave).
 bool transport_lds_fits(int block, int tally_mode, int device);
 // Dynamic LDS of a transport workgroup: its header, case descriptor and
 // class table, per-wave counters, the tally-mode-2 sub-tallies, and room for
 // tab_n mu/rho rows, tab_ne majorant nodes and tab_n bound-test sums (0:
-// none), and a source stash of stash_cap records per wave.
-size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap);
+// none), a source stash of stash_cap records per wave, and `cursors` words of
+// deposit-record cursors.
+size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap,
+                           int cursors);
 // Fold ncopies batch tallies [ncopies][V]: S1 += sum, S2 += sum^2, zero them;
 // fold the batch counters of acc into its 128-bit totals and record the
 // per-voxel maxima of S1 and of S2's high word.

@@ -154,6 +154,13 @@ struct StepCase {
   // bound-test sums per material and energy cell (CaseDev::bnd)
   const GLOBAL float *bnd;
   GLOBAL unsigned long long *tally;
+  // deposit records (kOutRecords): the workgroup's cursors of the case's
+  // voxel buckets and its segment counter in LDS, the record array
+  LOCAL unsigned long long *cur;
+  LOCAL uint32_t *seg_next;
+  GLOBAL uint2 *rec;
+  GLOBAL uint32_t *rec_prev;
+  uint32_t bbits;
   float fnx, fny, fnz, inv_dx, inv_dy, inv_dz, e0, inv_de;
   int32_t nx, ny, ne, rayleigh, npal;
   // tally mode 2: the wave's LDS sub-tally (slot keys = voxel or -1, values);
@@ -187,13 +194,18 @@ __device__ __forceinline__ int32_t uniform_i(int32_t x) {
   return __builtin_amdgcn_readfirstlane(x);
 }
 
-// tally_mode 0: the case's tally; 1, 2: this XCD's copy of it; cache: the
-// wave's LDS sub-tally (mode 2) or null; bound_shift: the bound grid used
-// (-1: none).
-__device__ __forceinline__ StepCase make_step_case(const CaseDev &c, int tally_mode,
-                                                   int bound_shift,
+// tally: the batch tally of the round's case; tally_mode 0: as it is; 1, 2:
+// this XCD's copy of it; cache: the wave's LDS sub-tally (mode 2) or null;
+// bound_shift: the bound grid used (-1: none).
+__device__ __forceinline__ StepCase make_step_case(const CaseDev &c, unsigned long long *tally,
+                                                   int tally_mode, int bound_shift,
                                                    LOCAL unsigned char *cache) {
   StepCase s;
+  s.cur = nullptr;
+  s.seg_next = nullptr;
+  s.rec = nullptr;
+  s.rec_prev = nullptr;
+  s.bbits = 0;
   s.bgrid = nullptr;
   s.bshift = 0;
   if (bound_shift >= 0 && c.bclass) {
@@ -209,7 +221,7 @@ __device__ __forceinline__ StepCase make_step_case(const CaseDev &c, int tally_m
   s.tabbnd = nullptr;
   s.bnd = uniform_ptr(c.bnd);
   s.mu_max = uniform_ptr(c.mu_max);
-  s.tally = uniform_ptr(c.tally);
+  s.tally = uniform_ptr(tally);
   if (tally_mode) s.tally += (size_t)xcc_id() * (size_t)uniform_i((int32_t)c.V);
   s.cvals = (LOCAL unsigned long long *)cache;
   s.ckeys = cache ? (LOCAL int32_t *)(cache + kCacheSlots * 8) : nullptr;
@@ -260,6 +272,45 @@ __device__ void flush(Counters &c, unsigned long long *acc, int lane, uint32_t r
 // same atomic instruction, performed at the memory side).
 __device__ __forceinline__ void tally_add(const StepCase &S, int32_t vox, unsigned long long q) {
   __hip_atomic_fetch_add(S.tally + vox, q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Deposit records (kOutRecords): append (voxel within its bucket, q) to the
+// bucket's segment of this workgroup.  A cursor word holds the segment and
+// the records appended to it; the lane whose append finds the segment full
+// (exactly one per segment) takes the workgroup's next segment, links it to
+// the full one and installs it, while later lanes add again a bounded number
+// of times.  A lane without a slot after that, or in a workgroup without
+// segments left, adds straight to the tally.  The loop's condition is the
+// wave's (a ballot), so the installing lane always runs inside it.
+__device__ __forceinline__ void record_deposit(const StepCase &S, int32_t vox, uint32_t q) {
+  LOCAL unsigned long long *cur = S.cur + ((uint32_t)vox >> S.bbits);
+  bool todo = true;
+  for (int t = 0; __ballot(todo) != 0ull; ++t) {
+    if (!todo) continue;
+    const unsigned long long w =
+        __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    uint32_t seg = (uint32_t)(w >> 32), pos = (uint32_t)w;
+    if (pos >= kLogSeg) {
+      const bool mine = pos == kLogSeg;
+      const uint32_t next = __hip_atomic_fetch_add(S.seg_next, mine ? 1u : 0u, __ATOMIC_RELAXED,
+                                                   __HIP_MEMORY_SCOPE_WORKGROUP);
+      if (next >= S.seg_next[1] || (!mine && t >= 16)) {
+        tally_add(S, vox, q);
+        todo = false;
+      } else if (mine) {
+        S.rec_prev[next] = seg;
+        seg = next;
+        pos = 0;
+        __hip_atomic_store(cur, ((unsigned long long)next << 32) | 1ull, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_WORKGROUP);
+      }
+    }
+    if (todo && pos < kLogSeg) {
+      S.rec[(size_t)seg * kLogSeg + pos] =
+          make_uint2((uint32_t)vox & ((1u << S.bbits) - 1u), q);
+      todo = false;
+    }
+  }
 }
 
 // Tally mode 2: add the wave's LDS sub-tally to the case's tally and empty it
@@ -379,10 +430,10 @@ __device__ __forceinline__ void rotate(Photon &p, float mu, float t) {
   p.uz = nw * n;
 }
 
-template <bool LOG>
+template <int OUT>
 __device__ __forceinline__ void log_event(const CaseDev &G, Photon &p, int type, int64_t vox,
                                           float e, float Eafter) {
-  if (!LOG) return;
+  if constexpr (OUT != kOutEvents) return;
   const uint64_t h = ((uint64_t)p.hhi << 32) | p.hlo;
   if (h < G.log_h0 || h >= G.log_h1) return;
   const unsigned long long idx = atomicAdd(G.log_n, 1ull);
@@ -403,14 +454,17 @@ __device__ __forceinline__ void log_event(const CaseDev &G, Photon &p, int type,
 
 // Exact tally update: e is a multiple of 2^-24 keV, so q = e * 2^24 is an
 // integer (< 2^32 for e < 256 keV) and the int64 sum is exact in any order.
-template <bool LOG>
+template <int OUT>
 __device__ __forceinline__ void deposit(const StepCase &S, const CaseDev &G, Photon &p,
                                         Counters &c, int32_t vox, float e, int type,
                                         float Eafter) {
   const uint32_t q = (uint32_t)(e * kQScale);
   if (q) {
     bool cached = false;
-    if (S.ckeys) {
+    if constexpr (OUT == kOutRecords) {
+      record_deposit(S, vox, q);
+      cached = true;
+    } else if (S.ckeys) {
       // LDS sub-tally: the slot of vox belongs to the first voxel that took
       // it during this wave's case; other voxels go straight to the tally
       const uint32_t slot = ((uint32_t)vox * 2654435761u) >> (32 - kCacheBits);
@@ -431,14 +485,14 @@ __device__ __forceinline__ void deposit(const StepCase &S, const CaseDev &G, Pho
     c.add(ACC_Q_DEP, q);
   }
   c.add(ACC_N_DEPOSITS, 1);
-  log_event<LOG>(G, p, type, vox, e, Eafter);
+  log_event<OUT>(G, p, type, vox, e, Eafter);
 }
 
 // Source photon of history h from spectrum bin j (Sec. 2.2.5-2.2.6): its
 // entry point into the voxel box (voxel units) and energy in pe, its unit
 // direction in dir.xyz; returns false when the ray misses the box (the photon
 // escapes at once).  Its start event is logged here (event 0 of the history).
-template <bool LOG>
+template <int OUT>
 __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
                        const int32_t *__restrict__ mh_beam, uint64_t local, Counters &c,
                        float4 &pe, float4 &dir) {
@@ -506,7 +560,7 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
   }
   c.add(ACC_N_HIST, 1);
   c.add(ACC_Q_INC, (uint32_t)(E * kQScale));
-  log_event<LOG>(G, p, 0, beamlet, E, E);
+  log_event<OUT>(G, p, 0, beamlet, E, E);
   // slab entry into the box [0, n) in voxel units
   const float Sv[3] = {(sx - G.ox) * S.inv_dx, (sy - G.oy) * S.inv_dy, (sz - G.oz) * S.inv_dz};
   const float D[3] = {dx * S.inv_dx, dy * S.inv_dy, dz * S.inv_dz};
@@ -528,7 +582,7 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
   if (miss || !(tin < tf)) {
     c.add(ACC_N_MISS, 1);
     c.add(ACC_Q_ESC, (uint32_t)(E * kQScale));
-    log_event<LOG>(G, p, 6, -1, E, E);
+    log_event<OUT>(G, p, 6, -1, E, E);
     return false;
   }
   // entry point, kept inside [0, n) against rounding
@@ -544,13 +598,13 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
 }
 
 // The photon leaves the voxel box with its energy.
-template <bool LOG>
+template <int OUT>
 __device__ __forceinline__ bool escape(Photon &p, const CaseDev &G, Counters &c, uint32_t k) {
   c.add(ACC_N_STEPS, k);
   c.add(ACC_N_ESCAPES, 1);
   if (!(p.k & kScatBit)) c.add(ACC_N_UNSCATTERED, 1);
   c.add(ACC_Q_ESC, (uint32_t)(p.E * kQScale));
-  log_event<LOG>(G, p, 5, -1, p.E, p.E);
+  log_event<OUT>(G, p, 5, -1, p.E, p.E);
   return false;
 }
 
@@ -565,7 +619,7 @@ constexpr int kSelFict = 0, kSelCompton = 1, kSelRayleigh = 2, kSelPhoto = 3, kS
 // cumulative sums in that order.  A photoelectric absorption deposits E
 // locally here; nsteps is what the photon adds to the step counter when it
 // ends.
-template <bool LOG>
+template <int OUT>
 __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, const CaseDev &G,
                                               Counters &c, int32_t vox, float rho, float a,
                                               float b, float cr, float xi, uint32_t nsteps) {
@@ -574,7 +628,7 @@ __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, cons
   if (xi < mpe) {  // photoelectric: absorb, deposit E locally
     c.add(ACC_N_STEPS, nsteps);
     c.add(ACC_N_PHOTO, 1);
-    deposit<LOG>(S, G, p, c, vox, p.E, 1, 0.0f);
+    deposit<OUT>(S, G, p, c, vox, p.E, 1, 0.0f);
     return kSelPhoto;
   }
   if (xi < c1) return kSelCompton;
@@ -588,7 +642,7 @@ __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, cons
 // Tentative collision at voxel vox against majorant mumax with selection
 // word ry: read the voxel (1-byte palette index or 8-byte record) and its
 // table rows, then select; m receives the voxel's material.
-template <bool LOG, bool TAB>
+template <int OUT, bool TAB>
 __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const CaseDev &G,
                                          const LOCAL uint2 *pal, Counters &c, int32_t vox,
                                          uint32_t ry, float mumax, uint32_t nsteps,
@@ -608,7 +662,7 @@ __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const Cas
   table_rows<TAB>(S, ti, t0, t1);
   const float a = lerpf(t0.x, t1.x, p.we), b = lerpf(t0.y, t1.y, p.we);
   const float cr = S.rayleigh ? lerpf(t0.z, t1.z, p.we) : 0.0f;
-  return select_process<LOG>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
+  return select_process<OUT>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
                              unif(ry) * mumax, nsteps);
 }
 
@@ -616,7 +670,7 @@ __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const Cas
 // voxel vox of material m: the polar angle from the process's surface at
 // uniform w0, the azimuth from w1; returns false when the photon is done
 // (Compton below the cutoff).  nsteps as in select_process.
-template <bool LOG, bool TAB>
+template <int OUT, bool TAB>
 __device__ __forceinline__ bool scatter(Photon &p, const StepCase &S, const CaseDev &G,
                                         Counters &c, int sel, int32_t vox, uint32_t m,
                                         uint32_t w0, uint32_t w1, uint32_t nsteps) {
@@ -630,13 +684,13 @@ __device__ __forceinline__ bool scatter(Photon &p, const StepCase &S, const Case
     const float mu = surface(Q, nzc, p.je, p.we, unif(w0));
     const float E = p.E;
     const float Ep = E * __builtin_amdgcn_rcpf(fmaf(E * kInvMeC2, 1.0f - mu, 1.0f));
-    deposit<LOG>(S, G, p, c, vox, E - Ep, 2, Ep);  // exact: Ep > E/2 (Sterbenz)
+    deposit<OUT>(S, G, p, c, vox, E - Ep, 2, Ep);  // exact: Ep > E/2 (Sterbenz)
     rotate(p, mu, unif(w1));
     set_energy<TAB>(p, S, Ep);
     if (Ep < G.e_cut) {
       c.add(ACC_N_STEPS, nsteps);
       c.add(ACC_N_CUTOFF, 1);
-      deposit<LOG>(S, G, p, c, vox, Ep, 4, 0.0f);
+      deposit<OUT>(S, G, p, c, vox, Ep, 4, 0.0f);
       return false;
     }
     return true;
@@ -647,7 +701,7 @@ __device__ __forceinline__ bool scatter(Photon &p, const StepCase &S, const Case
       (const GLOBAL float4 *)G.rayl_quad + (size_t)m * (size_t)(S.ne - 1) * (size_t)(nzr - 1);
   const float mu = surface(Q, nzr, p.je, p.we, unif(w0));
   rotate(p, mu, unif(w1));
-  log_event<LOG>(G, p, 3, vox, 0.0f, p.E);
+  log_event<OUT>(G, p, 3, vox, 0.0f, p.E);
   return true;
 }
 
@@ -689,25 +743,25 @@ __device__ __forceinline__ uint4 pair_block(const Photon &p, const StepCase &S, 
 // Returns the selection; a Compton or Rayleigh scatter is left to the
 // caller, with the voxel and its material in vox and m.  The caller applies
 // the step guard, once per block.
-template <bool LOG, bool TAB>
+template <int OUT, bool TAB>
 __device__ __forceinline__ int step(Photon &p, const StepCase &S, const CaseDev &G,
                                     const LOCAL uint2 *pal, Counters &c, uint32_t w0,
                                     uint32_t w1, int32_t &vox, uint32_t &m) {
   const uint32_t P = p.k & kStepMask;
   p.k += 1;
-  if (LOG) p.ks += 1;
+  if (OUT == kOutEvents) p.ks += 1;
   const float s = -__log2f(unif(w0)) * p.sc;  // -ln(u) / mu_max
   p.px = fmaf(s, p.ux * S.inv_dx, p.px);
   p.py = fmaf(s, p.uy * S.inv_dy, p.py);
   p.pz = fmaf(s, p.uz * S.inv_dz, p.pz);
   const bool inside = inside_box(p, S);
   if (!inside) {
-    escape<LOG>(p, G, c, P + 1u);
+    escape<OUT>(p, G, c, P + 1u);
     return kSelDone;
   }
   const uint32_t ix = (uint32_t)p.px, iy = (uint32_t)p.py, iz = (uint32_t)p.pz;
   vox = (int32_t)__umul24(__umul24(iz, (uint32_t)S.ny) + iy, (uint32_t)S.nx) + (int32_t)ix;
-  return select_at<LOG, TAB>(p, S, G, pal, c, vox, w1, p.mumax, P + 1u, m);
+  return select_at<OUT, TAB>(p, S, G, pal, c, vox, w1, p.mumax, P + 1u, m);
 }
 
 // One Woodcock step with deferred collisions (bound grid present), words w0
@@ -722,12 +776,12 @@ __device__ __forceinline__ int step(Photon &p, const StepCase &S, const CaseDev 
 // guard, once per block.
 constexpr int kStepOn = 0, kStepPending = 1, kStepGone = 2;
 
-template <bool LOG, bool TAB>
+template <int OUT, bool TAB>
 __device__ __forceinline__ int step_fast(Photon &p, const StepCase &S, const LOCAL uint2 *cls_tab,
                                          const GLOBAL uint8_t *bgrid, int32_t &pvox,
                                          LOCAL uint32_t *u1, uint32_t w0, uint32_t w1) {
   p.k += 1;
-  if (LOG) p.ks += 1;
+  if (OUT == kOutEvents) p.ks += 1;
   const float s = -__log2f(unif(w0)) * p.sc;  // -ln(u) / mu_max
   p.px = fmaf(s, p.ux * S.inv_dx, p.px);
   p.py = fmaf(s, p.uy * S.inv_dy, p.py);
@@ -767,12 +821,12 @@ __device__ __forceinline__ int step_fast(Photon &p, const StepCase &S, const LOC
 // least one crossing or ends the flight.
 constexpr int kMacroCrossings = 4;
 
-template <bool LOG, bool TAB>
+template <int OUT, bool TAB>
 __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const CaseDev &G,
                                            const LOCAL uint2 *pal, Counters &c) {
   if (p.tau < 0.0f) {  // a new flight
     p.k += 1;
-    if (LOG) p.ks += 1;
+    if (OUT == kOutEvents) p.ks += 1;
     const uint32_t k0 = p.k & kStepMask;
     if (k0 > kStepGuard) {
       c.add(ACC_STEP_GUARD, 1);
@@ -846,7 +900,7 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
   if (crossings) c.add(ACC_N_CROSS, crossings);
   if (out) {
     p.tau = -1.0f;
-    return escape<LOG>(p, G, c, k);
+    return escape<OUT>(p, G, c, k);
   }
   if (!hit) {  // the flight goes on in the next call, from this cell
     p.tau = tau;
@@ -866,10 +920,10 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
   const int32_t vox = (int32_t)__umul24(__umul24((uint32_t)iz, (uint32_t)S.ny) + (uint32_t)iy,
                                          (uint32_t)S.nx) + ix;
   uint32_t m;
-  const int sel = select_at<LOG, TAB>(p, S, G, pal, c, vox, p.ry, mu_c, k, m);
+  const int sel = select_at<OUT, TAB>(p, S, G, pal, c, vox, p.ry, mu_c, k, m);
   if (sel == kSelFict) return true;
   if (sel == kSelPhoto) return false;
-  return scatter<LOG, TAB>(p, S, G, c, sel, vox, m, p.rz, p.rw, k);
+  return scatter<OUT, TAB>(p, S, G, c, sel, vox, m, p.rz, p.rw, k);
 }
 
 // ------------------------------------------------------- transport kernel
@@ -927,13 +981,13 @@ __device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseD
 // without spilling, the macro-cell step spills a few words outside its cell
 // walk and gains more from the fifth wave hiding its dependent cell/majorant
 // loads than the spills cost.
-template <bool LOG, int KIND, bool TAB>
+template <int OUT, int KIND, bool TAB>
 __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k_transport(const RoundCase *__restrict__ rcs, int nrc,
                                                    uint64_t total_chunks,
                                                    unsigned long long *chunk_ctr, int refill_min,
                                                    int chunk, int tally_mode, int bound_shift,
                                                    int defer_min, int tab_n, int tab_ne,
-                                                   int stash_cap) {
+                                                   int stash_cap, DepositLog dl) {
   extern __shared__ unsigned long long dyn_lds[];   // layout: see kWgSlotsOff
   const int lane = __lane_id();
   const int w = threadIdx.x >> 6;
@@ -956,8 +1010,20 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   unsigned char *after_cache = after_slots + (tally_mode == 2 ? nw * kCacheBytesPerWave : 0);
   LOCAL float4 *st_a = (LOCAL float4 *)(after_cache + w * stash_cap * kStashRecBytes);
   LOCAL float4 *st_b = st_a + stash_cap;
+  // deposit records: the header's two words (next segment, end of the
+  // workgroup's segments) and the cursors behind the stash
+  LOCAL uint32_t *seg_next = (LOCAL uint32_t *)(base + 4);
+  unsigned char *after_stash = after_cache + nw * stash_cap * kStashRecBytes;
+  LOCAL unsigned long long *cur = (LOCAL unsigned long long *)after_stash;
+  if constexpr (OUT == kOutRecords) {
+    after_stash += (size_t)dl.cursors * 8;
+    if (threadIdx.x == 0) {
+      seg_next[0] = 1u + blockIdx.x * dl.seg_per_wg;
+      seg_next[1] = seg_next[0] + dl.seg_per_wg;
+    }
+  }
   if (TAB) {
-    tabmax = (LOCAL float *)(after_cache + nw * stash_cap * kStashRecBytes);
+    tabmax = (LOCAL float *)after_stash;
     tab = (LOCAL float4 *)(tabmax + ((tab_ne + 3) & ~3));
     tabbnd = (LOCAL float *)(tab + tab_n);
   }
@@ -1006,6 +1072,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       for (int i = threadIdx.x; i < n_b; i += blockDim.x) tabbnd[i] = srcb[i];
     }
     stage_case(&G, pal, rcs[c].cd);
+    if constexpr (OUT == kOutRecords) {
+      const int nb = (int)rcs[c].buckets;
+      for (int i = threadIdx.x; i < nb; i += blockDim.x) cur[i] = (unsigned long long)kLogSeg;
+    }
     __syncthreads();   // case and tables staged before any wave steps
     pool_next = pool_end = 0;
     wbin = 0;
@@ -1021,7 +1091,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         // counters of photons that left the box since the last refill step
         if (!alive && (p.k & kGoneBit)) {
           p.k &= ~kGoneBit;
-          escape<LOG>(p, G, cnt, p.k & kStepMask);
+          escape<OUT>(p, G, cnt, p.k & kStepMask);
         }
         // idle lanes take the stash's records in order, lowest lanes first;
         // an empty stash is refilled from the pool (a chunk of case c is
@@ -1040,7 +1110,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
               p.hlo = (uint32_t)h;
               p.hhi = (uint32_t)(h >> 32);
               p.k = 0;
-              p.seq = LOG ? 1u : 0u;   // event 0 (the start) was logged at sampling
+              p.seq = OUT == kOutEvents ? 1u : 0u;   // event 0 (the start) was logged at sampling
               p.ks = 0;
               p.tau = -1.0f;
               p.px = a.x; p.py = a.y; p.pz = a.z;
@@ -1071,7 +1141,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
             // the wave's step constants at its first chunk; a wave's claims
             // of one case increase, so later bin searches start from the last
             if (first) {
-              S = make_step_case(G, tally_mode, bound_shift, cache);
+              S = make_step_case(G, rcs[c].tally, tally_mode, bound_shift, cache);
+              if constexpr (OUT == kOutRecords) {
+                S.cur = cur;
+                S.seg_next = seg_next;
+                S.rec = (GLOBAL uint2 *)dl.rec;
+                S.rec_prev = (GLOBAL uint32_t *)dl.prev;
+                S.bbits = uniform_i((int32_t)rcs[c].bucket_bits);
+              }
               S.tab = tab;
               S.tabmax = tabmax;
               S.tabbnd = tabbnd;
@@ -1092,7 +1169,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
           if ((uint32_t)lane < ng) {
             int j = wbin;
             while (j + 1 < G.nbins && local >= R.prefix[j + 1]) ++j;
-            ok = source<LOG>(S, G, R.h_begin + local, j, R.beamlets, local, cnt, pe, dir);
+            ok = source<OUT>(S, G, R.h_begin + local, j, R.beamlets, local, cnt, pe, dir);
           }
           const unsigned long long okm = __ballot(ok);
           __builtin_amdgcn_wave_barrier();   // the last records were read
@@ -1121,7 +1198,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       if constexpr (KIND == kStepMacro) {
         // one call per pass of the loop: a tight loop of macro-cell calls
         // spills more than it saves
-        if (alive) alive = step_macro<LOG, TAB>(p, S, G, pal_lds, cnt);
+        if (alive) alive = step_macro<OUT, TAB>(p, S, G, pal_lds, cnt);
       } else if constexpr (KIND == kStepDeferred) {
         // collision pass: the pending tentative collisions of the wave, once
         // defer_min of them have gathered (or every live lane waits on one)
@@ -1132,14 +1209,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
             const uint32_t P = p.k & kStepMask;
             uint32_t m;
             const int sel =
-                select_at<LOG, TAB>(p, S, G, pal_lds, cnt, pvox, lane_word->y, p.mumax, P, m);
+                select_at<OUT, TAB>(p, S, G, pal_lds, cnt, pvox, lane_word->y, p.mumax, P, m);
             if (sel == kSelPhoto) {
               alive = false;
             } else if (sel != kSelFict) {   // the scatter takes the next pair
               const uint4 q = pair_block(p, S, P);
               const bool odd = (P & 1u) != 0u;
               p.k += 1;
-              alive = scatter<LOG, TAB>(p, S, G, cnt, sel, pvox, m, odd ? q.z : q.x,
+              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, pvox, m, odd ? q.z : q.x,
                                         odd ? q.w : q.y, P + 1u);
             }
             pvox = -1;
@@ -1157,8 +1234,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
             // (held in vector registers, it was re-read before every step)
             const GLOBAL uint8_t *bg = uniform_ptr(S.bgrid);
             int st = kStepOn;
-            if ((P & 1u) == 0u) st = step_fast<LOG, TAB>(p, S, pal_lds, bg, pvox, u1, r.x, r.y);
-            if (st == kStepOn) st = step_fast<LOG, TAB>(p, S, pal_lds, bg, pvox, u1, r.z, r.w);
+            if ((P & 1u) == 0u) st = step_fast<OUT, TAB>(p, S, pal_lds, bg, pvox, u1, r.x, r.y);
+            if (st == kStepOn) st = step_fast<OUT, TAB>(p, S, pal_lds, bg, pvox, u1, r.z, r.w);
             alive = st <= kStepPending;
           }
           const unsigned long long al = __ballot(alive);
@@ -1187,16 +1264,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
               w0 = r.x;
               w1 = r.y;
             } else {
-              sel = step<LOG, TAB>(p, S, G, pal_lds, cnt, r.x, r.y, vox, m);
+              sel = step<OUT, TAB>(p, S, G, pal_lds, cnt, r.x, r.y, vox, m);
             }
             if (sel == kSelCompton || sel == kSelRayleigh) {
               p.k += 1;
-              alive = scatter<LOG, TAB>(p, S, G, cnt, sel, vox, m, w0, w1, p.k & kStepMask);
+              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, vox, m, w0, w1, p.k & kStepMask);
             } else if (sel >= kSelPhoto) {
               alive = false;
             }
             if (alive && (p.k & 1u)) {   // the block's second pair: a step
-              sel = step<LOG, TAB>(p, S, G, pal_lds, cnt, r.z, r.w, vox, m);
+              sel = step<OUT, TAB>(p, S, G, pal_lds, cnt, r.z, r.w, vox, m);
               if (sel == kSelCompton || sel == kSelRayleigh) {
                 *lane_word = make_uint2((uint32_t)vox, m | ((uint32_t)sel << 16));
                 p.k |= kDueBit;
@@ -1216,6 +1293,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
     // every wave of the workgroup has drained case c: pick the next case
     // with chunks left, scanning cyclically from c + 1 (c itself last)
     __syncthreads();
+    if constexpr (OUT == kOutRecords) {
+      // the case's cursors are final: the heads of this workgroup's chains
+      const int nb = (int)rcs[c].buckets;
+      unsigned long long *head = dl.head + (size_t)blockIdx.x * dl.buckets + rcs[c].bucket0;
+      for (int i = threadIdx.x; i < nb; i += blockDim.x) head[i] = cur[i];
+    }
     if (threadIdx.x == 0) {
       int nxt = -1;
       for (int i = 1; i <= nrc && nxt < 0; ++i) {
@@ -1231,6 +1314,59 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
     c = __builtin_amdgcn_readfirstlane(*wg_next);   // uniform: scalar from here on
     home = false;
     if (c < 0) break;
+  }
+}
+
+// Sum a round's deposit records into the batch tallies.  Workgroup (bucket,
+// slice) keeps the bucket's voxels as 64-bit sums in LDS, walks the record
+// chains that the slice's transport workgroups left for the bucket (16 lanes
+// per chain, a segment at a time, so short chains of a small round still fill
+// the waves' loads), then adds its non-zero sums to the tally.
+__global__ void __launch_bounds__(1024) k_collect(const RoundCase *__restrict__ rcs, int nrc,
+                                                  DepositLog dl, int wgs, int slices) {
+  extern __shared__ unsigned long long tile[];
+  const uint32_t gb = blockIdx.x / (uint32_t)slices;
+  const int slice = (int)(blockIdx.x - gb * (uint32_t)slices);
+  int lo = 0, hi = nrc - 1;
+  while (lo < hi) {   // last case whose first bucket is at or before gb
+    const int mid = (lo + hi + 1) >> 1;
+    if (rcs[mid].bucket0 <= gb) lo = mid; else hi = mid - 1;
+  }
+  const RoundCase &rc = rcs[lo];
+  const int64_t v0 = (int64_t)(gb - rc.bucket0) << rc.bucket_bits;
+  const int nv = (int)min((int64_t)1 << rc.bucket_bits, rc.cd->V - v0);
+  for (int i = threadIdx.x; i < nv; i += blockDim.x) tile[i] = 0ull;
+  __syncthreads();
+  const uint32_t sub = threadIdx.x & 15u;
+  const int w1 = (int)((int64_t)wgs * (slice + 1) / slices);
+  for (int w = (int)((int64_t)wgs * slice / slices) + (int)(threadIdx.x >> 4); w < w1;
+       w += blockDim.x >> 4) {
+    const unsigned long long h = dl.head[(size_t)w * dl.buckets + gb];
+    uint32_t seg = (uint32_t)(h >> 32), n = min((uint32_t)h, kLogSeg);
+    while (seg) {
+      const uint32_t nxt = dl.prev[seg];
+      const uint4 *r = (const uint4 *)(dl.rec + (size_t)seg * kLogSeg) + sub;
+      uint4 d[kLogSeg / 32];
+#pragma unroll
+      for (uint32_t k = 0; k < kLogSeg / 32; ++k)
+        if (32u * k + 2u * sub < n) d[k] = r[16 * k];
+#pragma unroll
+      for (uint32_t k = 0; k < kLogSeg / 32; ++k) {
+        const uint32_t i = 32u * k + 2u * sub;
+        if (i < n) atomicAdd(&tile[d[k].x], (unsigned long long)d[k].y);
+        if (i + 1u < n) atomicAdd(&tile[d[k].z], (unsigned long long)d[k].w);
+      }
+      n = kLogSeg;
+      seg = nxt;
+    }
+  }
+  __syncthreads();
+  unsigned long long *t = rc.tally + v0;
+  for (int i = threadIdx.x; i < nv; i += blockDim.x) {
+    const unsigned long long v = tile[i];
+    if (v == 0ull) continue;
+    if (slices == 1) t[i] += v;
+    else atomic_add_u64(t + i, v);
   }
 }
 
@@ -1608,6 +1744,8 @@ __global__ void __launch_bounds__(256) k_static_round_setup(unsigned char *table
     rc->n = a.n;
     rc->chunk_begin = 0;
     rc->beamlets = a.beamlets;
+    rc->tally = a.tally;
+    rc->bucket0 = rc->buckets = rc->bucket_bits = 0;
     rc->wg_lo = 0;
     rc->home_waves = a.home_waves;
   }
@@ -1630,48 +1768,61 @@ int launch_static_round_setup(void *table, const StaticRoundArgs &args, void *st
 }
 
 int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,
-                     unsigned long long *chunk_ctr, const LaunchCfg &cfg, bool with_log,
-                     int step_kind, void *stream) {
+                     unsigned long long *chunk_ctr, const LaunchCfg &cfg, int out,
+                     const DepositLog &dl, int step_kind, void *stream) {
   hipStream_t s = (hipStream_t)stream;
   // stage the tables (room for the round's largest case) only where the
   // workgroup's LDS then still allows the resident workgroups the grid is
   // sized for, with the largest source stash (64, 32 or 16 records per wave)
   // that fits beside them; without the tables, the largest stash that fits
   // (16 at least)
+  const int cursors = out == kOutRecords ? dl.cursors : 0;
   int tab_n = cfg.tab_n, cap = 0;
   if (tab_n > 0) {
     for (int c = 64; c >= 16 && !cap; c >>= 1)
-      if (transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, c) <= cfg.lds_budget)
+      if (transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, c, cursors) <=
+          cfg.lds_budget)
         cap = c;
     if (!cap) tab_n = 0;
   }
   if (!cap) {
     cap = 16;
     for (int c = 64; c > 16 && cap == 16; c >>= 1)
-      if (transport_lds_bytes(cfg.block, cfg.tally_mode, 0, 0, c) <= cfg.lds_budget) cap = c;
+      if (transport_lds_bytes(cfg.block, cfg.tally_mode, 0, 0, c, cursors) <= cfg.lds_budget)
+        cap = c;
   }
-  const size_t lds = transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, cap);
+  const size_t lds =
+      transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, cap, cursors);
   using Kern = void (*)(const RoundCase *, int, uint64_t, unsigned long long *, int, int, int,
-                        int, int, int, int, int);
-  static const Kern kerns[2][3][2] = {
-      {{k_transport<false, kStepPlain, false>, k_transport<false, kStepPlain, true>},
-       {k_transport<false, kStepDeferred, false>, k_transport<false, kStepDeferred, true>},
-       {k_transport<false, kStepMacro, false>, k_transport<false, kStepMacro, true>}},
-      {{k_transport<true, kStepPlain, false>, k_transport<true, kStepPlain, true>},
-       {k_transport<true, kStepDeferred, false>, k_transport<true, kStepDeferred, true>},
-       {k_transport<true, kStepMacro, false>, k_transport<true, kStepMacro, true>}}};
-  if (step_kind < kStepPlain || step_kind > kStepMacro) return -1;
-  const Kern kern = kerns[with_log ? 1 : 0][step_kind][tab_n > 0 ? 1 : 0];
+                        int, int, int, int, int, DepositLog);
+#define CTD_KINDS(OUT)                                                            \
+  {{k_transport<OUT, kStepPlain, false>, k_transport<OUT, kStepPlain, true>},       \
+   {k_transport<OUT, kStepDeferred, false>, k_transport<OUT, kStepDeferred, true>}, \
+   {k_transport<OUT, kStepMacro, false>, k_transport<OUT, kStepMacro, true>}}
+  static const Kern kerns[3][3][2] = {CTD_KINDS(kOutTally), CTD_KINDS(kOutEvents),
+                                      CTD_KINDS(kOutRecords)};
+#undef CTD_KINDS
+  if (step_kind < kStepPlain || step_kind > kStepMacro || out < kOutTally || out > kOutRecords)
+    return -1;
+  const Kern kern = kerns[out][step_kind][tab_n > 0 ? 1 : 0];
   hipLaunchKernelGGL(kern, dim3(cfg.grid), dim3(cfg.block), lds, s, rc_dev, nrc, total_chunks,
                      chunk_ctr, cfg.refill_min, cfg.chunk, cfg.tally_mode, cfg.bound_shift,
-                     cfg.defer_min, tab_n, tab_n > 0 ? cfg.tab_ne : 0, cap);
+                     cfg.defer_min, tab_n, tab_n > 0 ? cfg.tab_ne : 0, cap, dl);
   return check_launch();
 }
 
-size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap) {
+int launch_collect(const RoundCase *rc_dev, int nrc, const DepositLog &dl, int wgs,
+                   int tile_voxels, int slices, void *stream) {
+  hipLaunchKernelGGL(k_collect, dim3((unsigned)dl.buckets * (unsigned)slices), dim3(1024),
+                     (size_t)tile_voxels * 8, (hipStream_t)stream, rc_dev, nrc, dl, wgs, slices);
+  return check_launch();
+}
+
+size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap,
+                           int cursors) {
   const size_t nw = (size_t)(block / 64);
   size_t b = kWgSlotsOff + nw * kWaveSlotBytes + (tally_mode == 2 ? nw * kCacheBytesPerWave : 0);
-  b += nw * (size_t)stash_cap * kStashRecBytes;
+  b += nw * (size_t)stash_cap * kStashRecBytes + (size_t)cursors * 8;
   // majorant nodes, mu/rho rows and (room for) the bound-test sums
   if (tab_n > 0) b += (size_t)((tab_ne + 3) & ~3) * 4 + (size_t)tab_n * 20;
   return b;
@@ -1684,7 +1835,7 @@ bool transport_lds_fits(int block, int tally_mode, int device) {
     (void)hipGetLastError();  // not a launch error: leave nothing for check_launch
     return false;
   }
-  return transport_lds_bytes(block, tally_mode, 0, 0, 16) <= (size_t)lim;
+  return transport_lds_bytes(block, tally_mode, 0, 0, 16, 0) <= (size_t)lim;
 }
 
 static int grid_for(int64_t n, int block, int cap) {

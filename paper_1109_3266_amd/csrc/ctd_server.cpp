@@ -550,6 +550,8 @@ extern "C" int32_t ctd_server_start(int32_t device, const ctd_server_config *cfg
     delete sv;
     return rc;
   }
+  // the device memory a server may take is hbm_budget_bytes: no workspace beside it
+  sv->ctx->keep_records = sv->aux->keep_records = false;
   sv->cfg = *cfg;
   sv->t0 = std::chrono::steady_clock::now();
   try {
