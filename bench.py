@@ -96,10 +96,20 @@ PINNED_TUNING = {
 }
 
 
-def counter_commands(workload: str) -> list:
-    """rocprofv3 runs behind profiles/k_transport_<workload>_pmc.json (one
-    counter group per run, repository root, output under gpurun_out/)."""
-    b = (f"python -u bench.py --quick --no-cpu --workload {workload} --steps 2 --warmup 0")
+def counter_file(workload: str, records: bool = False) -> str:
+    """Committed counter summary of the workload's transport kernel: of the
+    launches that add every deposit to the tally (k_transport), or of those
+    that keep deposit records (k_records)."""
+    return os.path.join(ROOT, "profiles",
+                        f"{'k_records' if records else 'k_transport'}_{workload}_pmc.json")
+
+
+def counter_commands(workload: str, records: bool = False) -> list:
+    """rocprofv3 runs behind counter_file (one counter group per run,
+    repository root, output under gpurun_out/).  The static entry point adds
+    every deposit to the tally."""
+    b = (f"python -u bench.py --quick --no-cpu --workload {workload} --steps 2 --warmup 0"
+         + ("" if records else " --static"))
     return [
         f"rocprofv3 --pmc FETCH_SIZE -f csv -d gpurun_out/pmc_{workload}_fetch -o f -- {b}",
         f"rocprofv3 --pmc WRITE_SIZE -f csv -d gpurun_out/pmc_{workload}_write -o w -- {b}",
@@ -127,12 +137,12 @@ def _pmc_rows(d: str):
     return rows
 
 
-def summarize_counters(workload: str):
-    """Write profiles/k_transport_<workload>_pmc.json from the counter runs."""
+def summarize_counters(workload: str, records: bool = False):
+    """Write counter_file from the counter runs."""
     import statistics
-    # the unlogged global-majorant instances: plain steps (0) and steps
-    # with collision passes (1)
-    kerns = ("k_transport<false, 0,", "k_transport<false, 1,")
+    # the unlogged global-majorant instances: plain steps with deposit records
+    # (2, 0), or plain steps (0, 0) and steps with collision passes (0, 1)
+    kerns = ("k_transport<2, 0,",) if records else ("k_transport<0, 0,", "k_transport<0, 1,")
 
     def per_launch(d, name):
         v = [x for k, n, x, _ in _pmc_rows(d) if any(p in k for p in kerns) and n == name]
@@ -167,18 +177,17 @@ def summarize_counters(workload: str):
                          valu_utilization_pct=valu["VALUUtilization"],
                          sq_insts_valu_per_launch=valu["SQ_INSTS_VALU"],
                          sq_insts_salu_per_launch=valu["SQ_INSTS_SALU"]),
-               commands=counter_commands(workload))
-    p = os.path.join(ROOT, "profiles", f"k_transport_{workload}_pmc.json")
-    with open(p, "w") as f:
+               commands=counter_commands(workload, records))
+    with open(counter_file(workload, records), "w") as f:
         json.dump(out, f, indent=1)
     print(json.dumps(out, indent=1))
 
 
-def load_counters(workload: str, tuning=None):
+def load_counters(workload: str, tuning=None, records: bool = False):
     """The committed rocprofv3 counter summary of the transport kernel on
     this workload, if it was taken on the current kernel source and with the
     launch configuration being timed; else None."""
-    p = os.path.join(ROOT, "profiles", f"k_transport_{workload}_pmc.json")
+    p = counter_file(workload, records)
     if not os.path.exists(p):
         return None
     d = json.load(open(p))
@@ -609,7 +618,7 @@ def calibrate_copy():
 
 
 def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup: int,
-                  tracking=None, tune=None, tally_mode=None):
+                  tracking=None, tune=None, tally_mode=None, static=False):
     """One case of workload `name`, timed over `steps` batches of BATCH
     histories after `warmup` untimed ones, bracketed by synchronizations and
     HIP events on the library's stream.  tune: None = the pinned launch
@@ -630,7 +639,8 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     log(f"{name}: block={tuning.block} waves/simd={tuning.waves_per_simd} "
         f"refill_min={tuning.refill_min} chunk={tuning.chunk} tally_mode={tuning.tally_mode} "
         f"bound_block={tuning.bound_block} defer_min={tuning.defer_min}")
-    L.ctd_run_batches(ctx, case.cs, BATCH, warmup)
+    run_batches = L.ctd_run_batches_static if static else L.ctd_run_batches
+    run_batches(ctx, case.cs, BATCH, warmup)
     torch.cuda.synchronize()
     st0 = L.ctd_read_stats(ctx, case.cs)
     torch.cuda.synchronize()
@@ -638,7 +648,7 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     ev1 = torch.cuda.Event(enable_timing=True)
     t0 = time.perf_counter()
     ev0.record(stream)
-    L.ctd_run_batches(ctx, case.cs, BATCH, steps)
+    run_batches(ctx, case.cs, BATCH, steps)
     ev1.record(stream)
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
@@ -662,7 +672,8 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     ops = ((OPS_FLIGHT_MACRO if macro else OPS_STEP) * d_steps +
            (OPS_SCATTER_MACRO if macro else OPS_SCATTER) * d_scat + OPS_COMPTON * d_comp +
            OPS_HISTORY * n_timed)
-    launch_ms = (st1.transport_ms - st0.transport_ms) / steps
+    # (the static entry point records none: the batches' time, folds included)
+    launch_ms = gpu_ms / steps if static else (st1.transport_ms - st0.transport_ms) / steps
     launch_s = launch_ms * 1e-3
     alu = ops / steps / launch_s
     # algorithmic bytes: a 5 B voxel read (u8 material + f32 density) per
@@ -671,7 +682,11 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     hbm = alg_bytes / steps / launch_s
     atom_rate = d_dep / steps / launch_s
     atom_peak, _ = L.ctd_microbench(ctx, 1, wl.n_voxels * 8, 1 << 28)
-    counters = load_counters(name, tuning) if tracking == L.CTD_TRACK_GLOBAL else None
+    # deposits faster than the memory side's atomics went through deposit
+    # records (summed in LDS by k_collect): the atomics bound nothing then
+    recorded = atom_rate > atom_peak
+    counters = (load_counters(name, tuning, recorded) if tracking == L.CTD_TRACK_GLOBAL
+                else None)
     traffic = (counters["hbm_bytes_per_launch"] / counters["histories_per_launch"] * BATCH
                if counters else None)
     valu = None
@@ -680,9 +695,9 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
         valu = dict(busy_pct=v["valu_busy_pct"], utilization_pct=v["valu_utilization_pct"],
                     insts_per_history=v["sq_insts_valu_per_launch"] / counters["histories_per_launch"],
                     source=f"rocprofv3 VALUBusy, VALUUtilization, SQ_INSTS_VALU "
-                           f"(profiles/k_transport_{name}_pmc.json)")
+                           f"(profiles/{os.path.basename(counter_file(name, recorded))})")
     fracs = dict(alu=alu / PEAK_LANE_OPS, hbm=hbm / 8e12, atomic=atom_rate / atom_peak)
-    bound = max(fracs, key=fracs.get)
+    bound = max((k for k in fracs if k != "atomic" or not recorded), key=fracs.get)
     unit = dict(alu="T lane-ops/s", hbm="GB/s", atomic="int64 atomics/s")[bound]
     ach = dict(alu=alu / 1e12, hbm=hbm / 1e9, atomic=atom_rate)[bound]
     peak = dict(alu=PEAK_LANE_OPS / 1e12, hbm=8000.0, atomic=atom_peak)[bound]
@@ -702,7 +717,9 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
                             frac=fracs["atomic"],
                             peak_source="ctd_microbench random 64-bit atomics into a "
                                         "tally-sized array, measured in this run",
-                            note="tally updates per second; with tally_mode 2 part of them "
+                            note="deposits per second; above the peak: kept as records and "
+                                 "summed in LDS, not tally atomics" if recorded else
+                                 "tally updates per second; with tally_mode 2 part of them "
                                  "are LDS atomics" if tuning.tally_mode == 2 else ""))
     out = dict(workload=WORKLOADS[name] + ("" if tracking == L.CTD_TRACK_GLOBAL
                                            else "_macro_tracking"),
@@ -710,8 +727,7 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
                voxels=wl.n_voxels,
                tuning={k: getattr(tuning, k) for k in TUNING_KEYS},
                roofline=roof,
-               transport_only_histories_per_s=n_timed / ((st1.transport_ms - st0.transport_ms)
-                                                         * 1e-3),
+               transport_only_histories_per_s=n_timed / (launch_ms * steps * 1e-3),
                sigma_local=L.ctd_sigma(ctx, case.cs, L.CTD_SIGMA_LOCAL, 0.5),
                sigma_paper=L.ctd_sigma(ctx, case.cs, L.CTD_SIGMA_PAPER, 0.2))
     case.close()
@@ -752,6 +768,10 @@ def main():
                     help="mean arrival rate of the Poisson trace [requests/s]")
     ap.add_argument("--serving-modes", default="global,auto",
                     help="tracking modes of the serving leg: global, auto or both")
+    ap.add_argument("--static", action="store_true",
+                    help="run the main leg through ctd_run_batches_static")
+    ap.add_argument("--records", action="store_true",
+                    help="with --summarize-counters: of the launches with deposit records")
     ap.add_argument("--calibrate-copy", action="store_true")
     ap.add_argument("--summarize-counters", action="store_true")
     ap.add_argument("--trace-idle", metavar="DIR",
@@ -771,7 +791,7 @@ def main():
         calibrate_copy()
         return
     if args.summarize_counters:
-        summarize_counters(args.workload)
+        summarize_counters(args.workload, args.records)
         return
     if args.trace_idle:
         trace_idle(args.trace_idle)
@@ -800,7 +820,8 @@ def main():
 
     main_leg, wl, tuning = transport_leg(ctx, L, W, Case, torch, stream, args.workload,
                                          args.steps, args.warmup, tracking,
-                                         "auto" if args.autotune else None, args.tally_mode)
+                                         "auto" if args.autotune else None, args.tally_mode,
+                                         args.static)
     value = main_leg["histories_per_s"]
     out = dict(metric=METRIC, value=value, unit="histories/s", n_gpus=1, steps=args.steps,
                warmup=args.warmup, ms_per_step=main_leg["ms_per_step"], higher_is_better=True,
@@ -823,7 +844,7 @@ def main():
         log(f"time to 1% sigma {out['time_to_1pct_sigma']['seconds']:.2f} s")
     if "water" in legs and args.workload != "water_cbct":
         # the cone-beam water cylinder: 1-byte palette phantom, deposits spread
-        # over 1.6 M voxels, bound by the memory-side tally atomics
+        # over 1.6 M voxels (kept as records and summed in LDS)
         wleg, wwl, wtun = transport_leg(ctx, L, W, Case, torch, stream, "water_cbct",
                                         args.steps, args.warmup)
         if "sigma" in legs:

@@ -144,8 +144,8 @@ struct RoundCase {
 };
 
 // Where a transport launch leaves its deposits: added to the batch tallies
-// as they happen (also with the event log on), or appended to DepositLog for
-// k_collect.
+// as they happen (also with the event log on), or, with plain steps only,
+// appended to DepositLog for k_collect.
 constexpr int kOutTally = 0, kOutEvents = 1, kOutRecords = 2;
 
 // Deposit records of a launch.  Every workgroup owns seg_per_wg segments of
