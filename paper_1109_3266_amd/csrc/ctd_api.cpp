@@ -137,6 +137,7 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   dfree(ctx->pack_stats);
   dfree(ctx->rec);
   dfree(ctx->rec_head);
+  dfree(ctx->group_tally);
   if (ctx->sigma_host) (void)hipHostFree(ctx->sigma_host);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
   delete ctx;
@@ -1073,6 +1074,19 @@ static LaunchCfg launch_cfg(const ctd_ctx *ctx, const ctd_tuning &t) {
   return cfg;
 }
 
+// Histories per chunk of a launch: the tuning's, or fewer where that would
+// leave waves of the grid without work or end on a few waves' last chunks:
+// about kChunksPerWave chunks for every wave, at least 64 histories each
+// (2 / 4 / 8: the head 3.41 / 2.34 / 2.45 ms per 1e7 histories, water 1.63 /
+// 1.59 / 1.75 ms; 1024 always: the 1e4-history pencil batch had 10 of 5120
+// waves at work, 157 us).
+constexpr uint64_t kChunksPerWave = 4;
+static int launch_chunk(const LaunchCfg &cfg, uint64_t n) {
+  const uint64_t waves = (uint64_t)cfg.grid * (uint64_t)(cfg.block / 64);
+  const uint64_t c = (n / (waves * kChunksPerWave) + 63) / 64 * 64;
+  return (int)std::min<uint64_t>((uint64_t)cfg.chunk, std::max<uint64_t>(c, 64));
+}
+
 // Deposit records of a launch (DepositLog).  Fills the cases' buckets and dl
 // and returns true where the launch takes them.  They pay where the tally's
 // atomics, which the memory side performs at 2.4e10/s at best and far slower on
@@ -1101,8 +1115,8 @@ static LaunchCfg launch_cfg(const ctd_ctx *ctx, const ctd_tuning &t) {
 constexpr uint64_t kRecordMin = 200000, kRecordPerVoxel = 3;
 constexpr double kRecordShare = 0.45;
 constexpr int kRecordBuckets = 1024, kRecordMaxBits = 14;
-constexpr double kRecordsPerHistory = 3.5;   // room; deposits beyond it go to the tally
-constexpr size_t kRecordMaxBytes = (size_t)4 << 30;
+constexpr double kRecordsPerHistory = 5.0;   // room; deposits beyond it go to the tally
+constexpr size_t kRecordMaxBytes = (size_t)6 << 30;
 
 static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, RoundCase *rc,
                          const LaunchCfg &cfg, int kind, bool with_log, DepositLog &dl,
@@ -1182,7 +1196,7 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
 // Stage one round (RoundCase table, bin prefixes, chunk counter) through a
 // pinned slot and launch the transport kernel on the ctx stream.
 int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const ctd_tuning &t,
-                      bool with_log) {
+                      bool with_log, bool spread) {
   const int nrc = (int)items.size();
   if (nrc == 0) return CTD_OK;
   const int kind = items[0].step_kind;
@@ -1218,6 +1232,9 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
   DepositLog dl;
   int tile_voxels = 0;
   const bool records = plan_records(ctx, items, rc, cfg, kind, with_log, dl, tile_voxels);
+  uint64_t n_all = 0;
+  for (const RoundItem &it : items) n_all += it.n;
+  cfg.chunk = launch_chunk(cfg, n_all);
   uint64_t chunks = 0;
   for (int i = 0; i < nrc; ++i) {
     rc[i].cd = items[i].cd;
@@ -1229,10 +1246,10 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
     rc[i].tally = items[i].tally;
     if (!records) rc[i].bucket0 = rc[i].buckets = rc[i].bucket_bits = 0;
     rc[i].reserved = 0;
-    chunks += (items[i].n + (uint64_t)t.chunk - 1) / (uint64_t)t.chunk;
+    chunks += (items[i].n + (uint64_t)cfg.chunk - 1) / (uint64_t)cfg.chunk;
     std::memcpy(h + poff[i], items[i].prefix.data(), 8 * items[i].prefix.size());
   }
-  home_round_cases(rc, nrc, cfg.grid, cfg.block / 64);
+  home_round_cases(rc, nrc, chunks, cfg.grid, cfg.block / 64, spread);
   std::memset(h + ctr_off, 0, ctr_bytes);
   HIPCHK(ctx, hipMemcpyAsync(d, h, bytes, hipMemcpyHostToDevice, ctx->stream));
   // LDS room for the largest case's tables: each workgroup stages the
@@ -1309,45 +1326,136 @@ static void harvest_timing(ctd_case *cs) {
   cs->timing.erase(cs->timing.begin(), cs->timing.begin() + (long)done);
 }
 
-// Enqueue one round over several cases (each with its own batch size), then
-// fold every participating case.
-int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vector<uint64_t> &n,
-                   const ctd_tuning &t) {
-  std::vector<RoundItem> items;
-  bool with_log = false;
-  for (size_t i = 0; i < cases.size(); ++i)
-    if (n[i]) NEED_INTACT(ctx, cases[i]);
+// How many of the rounds from `r` on go into one launch, each batch with a
+// tally of its own, folded together after it.  A launch ends with its last
+// histories on few lanes (about 0.2 ms) and starts with set-up, so batches are
+// gathered until the launch has kGroupHistories (3e7 / 1e8 / 3e8: the head with
+// macro cells 36.3 / 34.3 / 33.4 ms per 3e8, six uneven cases 63.2 / 63.4 /
+// 60.4 ms per 6e8; kGroupRecorded where deposit records may be kept, whose
+// workspace is bounded), within kGroupMaxBytes of tallies (and an eighth of the
+// free memory), and while the headroom bounds hold without a read-back.  Per-XCD tallies and the event log run a batch at
+// a time, as does a context without workspaces (a server's).
+constexpr uint64_t kGroupHistories = 300000000, kGroupRecorded = 100000000, kGroupRounds = 64;
+constexpr size_t kGroupMaxBytes = (size_t)1 << 30;
+
+static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases, uint64_t r,
+                             uint64_t count,
+                             const std::function<uint64_t(uint64_t, size_t)> &size,
+                             const ctd_tuning &t) {
+  if (t.tally_mode != 0 || !ctx->keep_records || r + 1 >= count) return 1;
+  uint64_t voxels = 0, most = kGroupHistories;
+  for (const ctd_case *cs : cases) {
+    if (cs->log_cap > 0) return 1;
+    voxels += (uint64_t)cs->ph->V;
+    if (cs->deposit_share >= kRecordShare) most = kGroupRecorded;
+  }
+  std::vector<double> s1(cases.size()), s2(cases.size());
   for (size_t i = 0; i < cases.size(); ++i) {
-    if (n[i] == 0) continue;
-    int rc0 = check_headroom(ctx, cases[i], n[i]);
-    if (rc0 != CTD_OK) return rc0;
-    if (t.tally_mode != 0 && cases[i]->tally_copies < kTallyCopies) {
-      rc0 = ensure_tally_copies(ctx, cases[i], kTallyCopies);
+    s1[i] = cases[i]->s1_bound;
+    s2[i] = cases[i]->s2_bound;
+  }
+  uint64_t g = 0, n = 0;
+  for (; r + g < count && g < kGroupRounds; ++g) {
+    uint64_t more = 0;
+    bool fits = 8 * voxels * g <= kGroupMaxBytes;
+    for (size_t i = 0; i < cases.size() && fits; ++i) {
+      const uint64_t k = size(r + g, i);
+      more += k;
+      double a = 0.0, b = 0.0;
+      if (k && headroom_bounds((double)k, cases[i]->e_max, s1[i], s2[i], &a, &b) != kHeadroomOk)
+        fits = false;
+      else if (k) {
+        s1[i] = a;
+        s2[i] = b;
+      }
+    }
+    if (!fits || (g > 0 && n + more > most)) break;
+    n += more;
+  }
+  if (g <= 1) return 1;
+  const size_t words = (size_t)(voxels * (g - 1));
+  if (ctx->group_words >= words && !ctx->group_dirty) return g;
+  if (ctx->group_words < words) {
+    size_t free_b = 0, total_b = 0;
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || 8 * words > free_b / 8 ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return 1;
+    }
+    dfree(ctx->group_tally);
+    ctx->group_tally = nullptr;
+    ctx->group_words = 0;
+    if (hipMalloc(&ctx->group_tally, 8 * words) != hipSuccess) {
+      (void)hipGetLastError();
+      ctx->group_tally = nullptr;
+      return 1;
+    }
+    ctx->group_words = words;
+  }
+  ctx->group_dirty = true;
+  if (launch_zero(ctx->group_tally, 8 * ctx->group_words, ctx->stream) != 0) return 1;
+  ctx->group_dirty = false;
+  return g;
+}
+
+// Enqueue `count` rounds over several cases (batch sizes n[round][case]) as
+// one launch per step kind, then fold every participating case.
+static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
+                     const std::vector<std::vector<uint64_t>> &n, const ctd_tuning &t) {
+  std::vector<RoundItem> items;
+  const size_t rounds = n.size();
+  bool with_log = false;
+  std::vector<uint64_t> total(cases.size(), 0);
+  for (size_t i = 0; i < cases.size(); ++i) {
+    for (size_t r = 0; r < rounds; ++r) total[i] += n[r][i];
+    if (total[i]) NEED_INTACT(ctx, cases[i]);
+  }
+  size_t off = 0;   // words of the group's tallies taken
+  std::vector<unsigned long long *> more(cases.size(), nullptr);
+  for (size_t i = 0; i < cases.size(); ++i) {
+    ctd_case *cs = cases[i];
+    if (total[i] == 0) continue;
+    int rc0;
+    if (t.tally_mode != 0 && cs->tally_copies < kTallyCopies) {
+      rc0 = ensure_tally_copies(ctx, cs, kTallyCopies);
       if (rc0 != CTD_OK) return rc0;
     }
-    RoundItem it;
-    it.cd = cases[i]->d_desc;
-    it.h_begin = cases[i]->h_next;
-    it.n = n[i];
-    it.V = cases[i]->ph->V;
-    it.deposit_share = cases[i]->deposit_share;
-    it.tally = cases[i]->d_tally;
-    it.step_kind = step_kind(cases[i], t);
-    it.tab_n = cases[i]->ms->M * cases[i]->ms->eg.ne;
-    it.tab_ne = cases[i]->ms->eg.ne;
-    if (cases[i]->d_mh_state) {
-      rc0 = ensure_mh_buffer(ctx, cases[i], n[i]);
+    if (cs->d_mh_state) {
+      rc0 = ensure_mh_buffer(ctx, cs, total[i]);
       if (rc0 != CTD_OK) return rc0;
-      it.beamlets = cases[i]->d_mh_beam;
     }
-    int rc = batch_prefix(ctx, cases[i], n[i], it.prefix);
-    if (rc != CTD_OK) return rc;
-    items.push_back(std::move(it));
-    with_log |= cases[i]->log_cap > 0;
+    more[i] = ctx->group_tally + off;
+    off += (size_t)cs->ph->V * (rounds - 1);
+    uint64_t done = 0;
+    for (size_t r = 0; r < rounds; ++r) {
+      if (n[r][i] == 0) continue;
+      rc0 = check_headroom(ctx, cs, n[r][i]);
+      if (rc0 != CTD_OK) return rc0;
+      RoundItem it;
+      it.cd = cs->d_desc;
+      it.h_begin = cs->h_next + done;
+      it.n = n[r][i];
+      it.V = cs->ph->V;
+      it.deposit_share = cs->deposit_share;
+      it.tally = r == 0 ? cs->d_tally : more[i] + (size_t)(r - 1) * (size_t)cs->ph->V;
+      it.step_kind = step_kind(cs, t);
+      it.tab_n = cs->ms->M * cs->ms->eg.ne;
+      it.tab_ne = cs->ms->eg.ne;
+      if (cs->d_mh_state) it.beamlets = cs->d_mh_beam + done;
+      if (r > 0 && n[r][i] == n[r - 1][i] && !items.empty()) {
+        it.prefix = items.back().prefix;
+      } else {
+        const int rc = batch_prefix(ctx, cs, n[r][i], it.prefix);
+        if (rc != CTD_OK) return rc;
+      }
+      items.push_back(std::move(it));
+      done += n[r][i];
+    }
+    with_log |= cs->log_cap > 0;
   }
   if (items.empty()) return CTD_OK;
   ctd_case *first = cases[0];
-  // the round's timing events; destroyed here unless the round completes
+  // the launch's timing events; destroyed here unless it completes
   struct TimingGuard {
     ctd_case::Timing tm{};
     bool keep = false;
@@ -1359,17 +1467,19 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
   } guard;
   ctd_case::Timing &tm = guard.tm;
   // from the first enqueue that changes a case on, a failure leaves the
-  // round's cases part-way through it
+  // cases part-way through their batches and the group's tallies not zero
   struct FailMark {
+    ctd_ctx *ctx;
     const std::vector<ctd_case *> &cases;
-    const std::vector<uint64_t> &n;
+    const std::vector<uint64_t> &total;
     bool armed = false;
     ~FailMark() {
       if (!armed) return;
+      ctx->group_dirty = true;
       for (size_t i = 0; i < cases.size(); ++i)
-        if (n[i]) cases[i]->failed = true;
+        if (total[i]) cases[i]->failed = true;
     }
-  } mark{cases, n};
+  } mark{ctx, cases, total};
   const bool timed = cases.size() == 1;
   if (timed) {
     HIPCHK(ctx, hipEventCreate(&tm.a));
@@ -1378,15 +1488,13 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
     HIPCHK(ctx, hipEventRecord(tm.a, ctx->stream));
   }
   mark.armed = true;
-  // Alg. A1 chains of this round's histories (same stream: ordered before the
-  // transport that reads them and after the previous round's)
-  for (size_t i = 0, k = 0; i < cases.size(); ++i) {
-    if (n[i] == 0) continue;
+  // Alg. A1 chains of the batches' histories (same stream: ordered before the
+  // transport that reads them and after the previous launch's)
+  for (size_t i = 0; i < cases.size(); ++i) {
     ctd_case *cs = cases[i];
-    const RoundItem &it = items[k++];
-    if (!it.beamlets) continue;
+    if (total[i] == 0 || !cs->d_mh_state) continue;
     if (launch_mh_fill(cs->d_fl_f, (int)cs->geo->fl_f.size(), cs->geo->g.fluence_chains,
-                       it.h_begin, it.n, cs->desc.key0, cs->desc.key1, cs->d_mh_state,
+                       cs->h_next, total[i], cs->desc.key0, cs->desc.key1, cs->d_mh_state,
                        cs->d_mh_beam, ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "Metropolis-Hastings fill launch");
   }
@@ -1395,7 +1503,7 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
   for (auto &it : items) group[it.step_kind].push_back(std::move(it));
   for (int gi = 0; gi < 3 && rc == CTD_OK; ++gi) {
     if (group[gi].empty()) continue;
-    rc = submit_round(ctx, group[gi], t, with_log);
+    rc = submit_round(ctx, group[gi], t, with_log, timed);
     if (rc == CTD_OK && ctx->fail_next_round) {
       ctx->fail_next_round = false;
       rc = set_err(ctx, CTD_EDEVICE, "failure injected after a transport launch");
@@ -1404,15 +1512,18 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
   if (rc != CTD_OK) return rc;
   if (timed) HIPCHK(ctx, hipEventRecord(tm.b, ctx->stream));
   for (size_t i = 0; i < cases.size(); ++i) {
-    if (n[i] == 0) continue;
+    if (total[i] == 0) continue;
     ctd_case *cs = cases[i];
-    if (launch_fold(cs->d_tally, t.tally_mode ? kTallyCopies : 1, cs->d_s1, cs->d_s2, cs->ph->V,
-                    cs->d_acc, ctx->stream) != 0)
+    if (launch_fold(cs->d_tally, t.tally_mode ? kTallyCopies : 1, more[i], (int)rounds, cs->d_s1,
+                    cs->d_s2, cs->ph->V, cs->d_acc, ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "fold launch");
-    cs->h_next += n[i];
-    cs->batches += 1;
-    cs->batch_min = std::min(cs->batch_min, n[i]);
-    cs->batch_max = std::max(cs->batch_max, n[i]);
+    for (size_t r = 0; r < rounds; ++r) {
+      if (n[r][i] == 0) continue;
+      cs->h_next += n[r][i];
+      cs->batches += 1;
+      cs->batch_min = std::min(cs->batch_min, n[r][i]);
+      cs->batch_max = std::max(cs->batch_max, n[r][i]);
+    }
   }
   if (timed) {
     HIPCHK(ctx, hipEventRecord(tm.c, ctx->stream));
@@ -1422,6 +1533,25 @@ int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vect
     guard.keep = true;
   }
   mark.armed = false;
+  return CTD_OK;
+}
+
+int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vector<uint64_t> &n,
+                   const ctd_tuning &t) {
+  return run_group(ctx, cases, {n}, t);
+}
+
+int ctd::run_rounds(ctd_ctx *ctx, std::vector<ctd_case *> &cases, uint64_t count,
+                    const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t) {
+  for (uint64_t r = 0; r < count;) {
+    const uint64_t g = group_rounds(ctx, cases, r, count, size, t);
+    std::vector<std::vector<uint64_t>> n((size_t)g, std::vector<uint64_t>(cases.size()));
+    for (uint64_t k = 0; k < g; ++k)
+      for (size_t i = 0; i < cases.size(); ++i) n[k][i] = size(r + k, i);
+    const int rc = run_group(ctx, cases, n, t);
+    if (rc != CTD_OK) return rc;
+    r += g;
+  }
   return CTD_OK;
 }
 
@@ -1435,15 +1565,11 @@ extern "C" int32_t ctd_run(ctd_ctx *ctx, ctd_case *cs, uint64_t n_histories) {
   if (!ctx || !cs) return CTD_EINVAL;
   HIPCHK(ctx, hipSetDevice(ctx->device));
   if (n_histories == 0) return CTD_OK;
-  const auto sizes = split_batches(n_histories, cs->p.n_batches);
+  auto sizes = split_batches(n_histories, cs->p.n_batches);
+  sizes.erase(std::remove(sizes.begin(), sizes.end(), (uint64_t)0), sizes.end());
   std::vector<ctd_case *> one{cs};
-  int rc = CTD_OK;
-  for (uint64_t nb : sizes) {
-    if (nb == 0) continue;
-    rc = run_round(ctx, one, std::vector<uint64_t>{nb}, cs->tune);
-    if (rc != CTD_OK) return rc;
-  }
-  return CTD_OK;
+  return run_rounds(ctx, one, sizes.size(), [&](uint64_t r, size_t) { return sizes[r]; },
+                    cs->tune);
 }
 
 extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_t *n,
@@ -1460,14 +1586,9 @@ extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_
   }
   const ctd_tuning t = cs[0]->tune;
   std::vector<ctd_case *> cases(cs, cs + count);
-  for (size_t r = 0; r < rounds; ++r) {
-    std::vector<uint64_t> nr((size_t)count, 0);
-    for (int i = 0; i < count; ++i)
-      if (r < sizes[i].size()) nr[i] = sizes[i][r];
-    int rc = run_round(ctx, cases, nr, t);
-    if (rc != CTD_OK) return rc;
-  }
-  return CTD_OK;
+  return run_rounds(
+      ctx, cases, rounds,
+      [&](uint64_t r, size_t i) { return r < sizes[i].size() ? sizes[i][r] : (uint64_t)0; }, t);
 }
 
 extern "C" int32_t ctd_sync(ctd_ctx *ctx, ctd_case *cs) {
@@ -1537,13 +1658,8 @@ uint64_t ctd::sigma_plan(uint64_t have, double sig, double target, uint64_t max_
 }
 
 int ctd::run_batches(ctd_ctx *ctx, ctd_case *cs, uint64_t batch, uint64_t count) {
-  int rc = CTD_OK;
   std::vector<ctd_case *> one{cs};
-  for (uint64_t b = 0; b < count; ++b) {
-    rc = run_round(ctx, one, std::vector<uint64_t>{batch}, cs->tune);
-    if (rc != CTD_OK) return rc;
-  }
-  return CTD_OK;
+  return run_rounds(ctx, one, count, [&](uint64_t, size_t) { return batch; }, cs->tune);
 }
 
 extern "C" int32_t ctd_run_batches(ctd_ctx *ctx, ctd_case *cs, uint64_t batch_histories,
@@ -1585,7 +1701,8 @@ extern "C" int32_t ctd_run_batches_static(ctd_ctx *ctx, ctd_case *cs, uint64_t b
   cfg.tab_n = cs->ms->M * cs->ms->eg.ne;
   cfg.tab_ne = cs->ms->eg.ne;
   a.home_waves = (uint32_t)cfg.grid * (uint32_t)(cfg.block / 64);
-  const uint64_t chunks = (batch_histories + (uint64_t)t.chunk - 1) / (uint64_t)t.chunk;
+  cfg.chunk = launch_chunk(cfg, batch_histories);
+  const uint64_t chunks = (batch_histories + (uint64_t)cfg.chunk - 1) / (uint64_t)cfg.chunk;
   unsigned char *table = (unsigned char *)ctx->static_table;
   const bool with_log = cs->log_cap > 0;
   for (uint64_t b = 0; b < count; ++b) {
@@ -1613,8 +1730,8 @@ extern "C" int32_t ctd_run_batches_static(ctd_ctx *ctx, ctd_case *cs, uint64_t b
                          (unsigned long long *)(table + kStaticCounterOff), cfg,
                          with_log ? kOutEvents : kOutTally, DepositLog{}, step_kind(cs, t),
                          ctx->stream) != 0 ||
-        launch_fold(cs->d_tally, t.tally_mode ? kTallyCopies : 1, cs->d_s1, cs->d_s2,
-                    cs->ph->V, cs->d_acc, ctx->stream) != 0)
+        launch_fold(cs->d_tally, t.tally_mode ? kTallyCopies : 1, nullptr, 1, cs->d_s1,
+                    cs->d_s2, cs->ph->V, cs->d_acc, ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "static round launch");
     cs->failed = false;
     cs->s1_bound = s1;

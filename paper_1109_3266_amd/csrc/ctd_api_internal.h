@@ -5,6 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <atomic>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -53,6 +54,12 @@ struct ctd_ctx {
   bool keep_records = true;
   void *rec = nullptr, *rec_head = nullptr;
   size_t rec_segs = 0, rec_heads = 0;
+  // batch tallies of the launches that run several batches at once
+  // (run_group), zero between launches unless group_dirty; grown on demand,
+  // at most kGroupMaxBytes, freed with the context; kept where the records are
+  unsigned long long *group_tally = nullptr;
+  size_t group_words = 0;
+  bool group_dirty = false;
   bool xcd_tally_ok = false;  // every XCC id < kTallyCopies
   unsigned int max_xcc = 0;
   int lds_per_cu = 160 * 1024, lds_per_block = 64 * 1024;  // device LDS limits
@@ -174,15 +181,20 @@ int upload_desc(ctd_ctx *ctx, ctd_case *cs);
 void fill_desc(ctd_case *cs);
 void free_case_buffers(ctd_case *cs);
 // One transport launch over items, which share one step kind.
+// spread: the items are batches of one case (spread_workgroups).
 int submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const ctd_tuning &t,
-                 bool with_log);
+                 bool with_log, bool spread);
 ctd_tuning default_tuning(const ctd_ctx *ctx);
 // The step a case's histories take under tuning t (kStep*).
 int step_kind(const ctd_case *cs, const ctd_tuning &t);
 int batch_prefix(ctd_ctx *ctx, const ctd_case *cs, uint64_t n,
                  std::vector<unsigned long long> &prefix);
+// One round: n[i] histories of case i, one batch each.
 int run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vector<uint64_t> &n,
               const ctd_tuning &t);
+// `count` rounds in order, round r taking size(r, i) histories of case i.
+int run_rounds(ctd_ctx *ctx, std::vector<ctd_case *> &cases, uint64_t count,
+               const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t);
 std::vector<uint64_t> split_batches(uint64_t n, int nb);
 int sigma_now(ctd_ctx *ctx, ctd_case *cs, int kind, double frac, double *out);
 // Enqueue the sigma-bar reduction of a case on ctx->stream and the copy of

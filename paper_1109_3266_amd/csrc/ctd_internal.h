@@ -164,12 +164,17 @@ struct DepositLog {
 };
 
 // Fill wg_lo and home_waves of a round's cases (chunk_begin already set) for
-// a grid of `grid` workgroups of `waves` waves (ctd_schedule.h).
-inline void home_round_cases(RoundCase *rc, int nrc, int grid, int waves) {
+// a grid of `grid` workgroups of `waves` waves (ctd_schedule.h); spread:
+// workgroups in proportion to the cases' shares of total_chunks.
+inline void home_round_cases(RoundCase *rc, int nrc, uint64_t total_chunks, int grid, int waves,
+                             bool spread) {
   std::vector<uint64_t> begin((size_t)nrc);
   std::vector<uint32_t> lo((size_t)nrc), hw((size_t)nrc);
   for (int i = 0; i < nrc; ++i) begin[i] = rc[i].chunk_begin;
-  home_workgroups(begin.data(), nrc, grid, waves, lo.data(), hw.data());
+  if (spread)
+    spread_workgroups(begin.data(), nrc, total_chunks, grid, waves, lo.data(), hw.data());
+  else
+    home_workgroups(begin.data(), nrc, grid, waves, lo.data(), hw.data());
   for (int i = 0; i < nrc; ++i) {
     rc[i].wg_lo = lo[i];
     rc[i].home_waves = hw[i];
@@ -238,11 +243,13 @@ bool transport_lds_fits(int block, int tally_mode, int device);
 // deposit-record cursors.
 size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap,
                            int cursors);
-// Fold ncopies batch tallies [ncopies][V]: S1 += sum, S2 += sum^2, zero them;
-// fold the batch counters of acc into its 128-bit totals and record the
+// Fold nbatch batches in order, the first from its ncopies tallies
+// tally[ncopies][V], the others from more[nbatch - 1][V]: S1 += T, S2 += T^2,
+// zero them; fold the counters of acc into its 128-bit totals and record the
 // per-voxel maxima of S1 and of S2's high word.
-int launch_fold(unsigned long long *tally, int ncopies, long long *s1, unsigned long long *s2,
-                int64_t V, unsigned long long *acc, void *stream);
+int launch_fold(unsigned long long *tally, int ncopies, unsigned long long *more, int nbatch,
+                long long *s1, unsigned long long *s2, int64_t V, unsigned long long *acc,
+                void *stream);
 // Largest XCC id seen by `blocks` workgroups (written to *out, device).
 int launch_xcc_probe(unsigned int *out, int blocks, void *stream);
 // stats[kPackStats]: [0,256) max density bits per material, [256,512) voxel

@@ -1472,11 +1472,14 @@ __global__ void __launch_bounds__(256) k_mh_fill(const float *__restrict__ f, in
 
 // --------------------------------------------------------------- fold etc.
 
-// S1 += T_b, S2 += T_b^2 (128-bit), T_b = 0 (Sec. 2.2.1 batch statistics);
-// T_b is the exact sum of the ncopies per-XCD batch tallies.  Block 0 also
-// folds the batch counters into their 128-bit totals; every block records
-// the largest S1 and S2 high word it produced (overflow headroom).
+// S1 += T_b, S2 += T_b^2 (128-bit), T_b = 0 (Sec. 2.2.1 batch statistics) for
+// each batch b of a launch in order: batch 0 in T, the exact sum of its
+// ncopies per-XCD copies, the others in `more` ([nbatch - 1][V], one copy).
+// The sums are read and written once for all of them.  Block 0 also folds the
+// counters into their 128-bit totals; every block records the largest S1 and
+// S2 high word it produced (overflow headroom; both only grow with b).
 __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T, int ncopies,
+                                              unsigned long long *__restrict__ more, int nbatch,
                                               long long *__restrict__ S1,
                                               unsigned long long *__restrict__ S2, int64_t V,
                                               unsigned long long *__restrict__ acc) {
@@ -1502,13 +1505,21 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
         T[(int64_t)c * V + i] = 0ull;
       }
     }
-    if (t == 0ull) continue;
-    const long long s1 = S1[i] + (long long)t;
+    unsigned long long sum = t, lo = t * t, hi = __umul64hi(t, t);
+    for (int b = 1; b < nbatch; ++b) {
+      const unsigned long long v = more[(int64_t)(b - 1) * V + i];
+      if (v == 0ull) continue;
+      more[(int64_t)(b - 1) * V + i] = 0ull;
+      sum += v;
+      const unsigned long long plo = v * v;
+      lo += plo;
+      hi += __umul64hi(v, v) + (lo < plo ? 1ull : 0ull);
+    }
+    if (sum == 0ull) continue;
+    const long long s1 = S1[i] + (long long)sum;
     S1[i] = s1;
-    const unsigned long long lo = S2[2 * i], hi = S2[2 * i + 1];
-    const unsigned long long plo = t * t, phi = __umul64hi(t, t);
-    const unsigned long long nlo = lo + plo;
-    const unsigned long long nhi = hi + phi + (nlo < lo ? 1ull : 0ull);
+    const unsigned long long nlo = S2[2 * i] + lo;
+    const unsigned long long nhi = S2[2 * i + 1] + hi + (nlo < lo ? 1ull : 0ull);
     S2[2 * i] = nlo;
     S2[2 * i + 1] = nhi;
     mx1 = max(mx1, (unsigned long long)s1);
@@ -1851,12 +1862,13 @@ static int grid_for(int64_t n, int block, int cap) {
   return (int)g;
 }
 
-int launch_fold(unsigned long long *tally, int ncopies, long long *s1, unsigned long long *s2,
-                int64_t V, unsigned long long *acc, void *stream) {
+int launch_fold(unsigned long long *tally, int ncopies, unsigned long long *more, int nbatch,
+                long long *s1, unsigned long long *s2, int64_t V, unsigned long long *acc,
+                void *stream) {
   // 1024 groups stream the arrays at full rate and keep the per-group
   // maximum records (two loads, at most two atomics each) few
   hipLaunchKernelGGL(k_fold, dim3(grid_for(V, 256, 1024)), dim3(256), 0, (hipStream_t)stream,
-                     tally, ncopies, s1, s2, V, acc);
+                     tally, ncopies, more, nbatch, s1, s2, V, acc);
   return check_launch();
 }
 

@@ -25,4 +25,20 @@ inline void home_workgroups(const uint64_t *chunk_begin, int nrc, int grid, int 
   }
 }
 
+// The same table with the grid spread over all cases at once, in proportion to
+// their chunks: case i's home workgroups start at grid * chunk_begin[i] /
+// total_chunks.  For batches of one case, which share the phantom and tables:
+// every workgroup then drains and changes batch about once.
+inline void spread_workgroups(const uint64_t *chunk_begin, int nrc, uint64_t total_chunks,
+                              int grid, int waves, uint32_t *wg_lo, uint32_t *home_waves) {
+  for (int i = 0; i < nrc; ++i)
+    wg_lo[i] = total_chunks == 0 ? 0u
+                                 : (uint32_t)((double)grid * (double)chunk_begin[i] /
+                                              (double)total_chunks);
+  for (int i = 0; i < nrc; ++i) {
+    const uint32_t hi = i + 1 < nrc ? wg_lo[i + 1] : (uint32_t)grid;
+    home_waves[i] = (hi - wg_lo[i]) * (uint32_t)waves;
+  }
+}
+
 }  // namespace ctd
