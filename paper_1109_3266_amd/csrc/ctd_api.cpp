@@ -11,8 +11,11 @@
 #include <cstdarg>
 #include <cstdio>
 #include <cstring>
+#include <functional>
+#include <mutex>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "ctd_api_internal.h"
@@ -139,6 +142,7 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   dfree(ctx->rec_head);
   dfree(ctx->group_tally);
   if (ctx->sigma_host) (void)hipHostFree(ctx->sigma_host);
+  if (ctx->read_host) (void)hipHostFree(ctx->read_host);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
   delete ctx;
   return CTD_OK;
@@ -1785,76 +1789,100 @@ extern "C" int32_t ctd_tally_device(ctd_ctx *ctx, ctd_case *cs, void **s1, void 
   return CTD_OK;
 }
 
+// Read V voxels as `planes` arrays of 8-byte words into dst (null: plane not
+// wanted).  A kernel writes each piece of voxels straight into pinned memory;
+// a few host threads, one staging slot each, copy the pieces to the caller's
+// arrays: filling fresh pages of those is the slow part (4 GB/s on one
+// thread, against 57 GB/s over the link), so it is spread and overlapped.
+// launch(v0, n, out) enqueues the kernel for n voxels from v0.
+static int read_planes(ctd_ctx *ctx, int64_t V, int planes, void *const *dst,
+                       const std::function<int(int64_t, int, void *)> &launch) {
+  const int64_t fit = (int64_t)(kReadSlotBytes / (8 * (size_t)planes));
+  // two pieces per thread at least, of 64 K voxels or more
+  const int64_t piece =
+      std::min(fit, std::max<int64_t>(65536, (V + 2 * kReadSlots - 1) / (2 * kReadSlots)));
+  const int64_t pieces = (V + piece - 1) / piece;
+  const int threads = (int)std::min<int64_t>(kReadSlots, pieces);
+  const size_t slot_bytes = 8 * (size_t)planes * (size_t)std::min(piece, V);
+  if (ctx->read_cap < slot_bytes * (size_t)threads) {
+    if (ctx->read_host) (void)hipHostFree(ctx->read_host);
+    ctx->read_host = nullptr;
+    ctx->read_cap = 0;
+    HIPCHK(ctx, hipHostMalloc(&ctx->read_host, slot_bytes * (size_t)threads,
+                              hipHostMallocDefault));
+    ctx->read_cap = slot_bytes * (size_t)threads;
+  }
+  std::vector<hipError_t> status((size_t)threads, hipSuccess);
+  std::atomic<int64_t> next{0};
+  std::mutex enqueue;   // an event is recorded right behind its own kernel
+  auto work = [&](int t) {
+    char *slot = (char *)ctx->read_host + (size_t)t * slot_bytes;
+    hipError_t e = hipSetDevice(ctx->device);
+    hipEvent_t ev = nullptr;
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+    for (int64_t k; e == hipSuccess && (k = next.fetch_add(1)) < pieces;) {
+      const int64_t v0 = k * piece;
+      const int n = (int)std::min(piece, V - v0);
+      {
+        std::lock_guard<std::mutex> lk(enqueue);
+        if (launch(v0, n, slot) != 0) e = hipErrorLaunchFailure;
+        else e = hipEventRecord(ev, ctx->stream);
+      }
+      if (e == hipSuccess) e = hipEventSynchronize(ev);
+      for (int p = 0; e == hipSuccess && p < planes; ++p)
+        if (dst[p])
+          std::memcpy((char *)dst[p] + 8 * v0, slot + 8 * (size_t)p * (size_t)n, 8 * (size_t)n);
+    }
+    if (ev) (void)hipEventDestroy(ev);
+    status[(size_t)t] = e;
+  };
+  std::vector<std::thread> helpers;
+  for (int t = 1; t < threads; ++t) {
+    try {
+      helpers.emplace_back(work, t);
+    } catch (...) {   // fewer threads: the others take its pieces
+      break;
+    }
+  }
+  work(0);
+  for (std::thread &h : helpers) h.join();
+  for (hipError_t e : status) HIPCHK(ctx, e);
+  return CTD_OK;
+}
+
 extern "C" int32_t ctd_read_tally(ctd_ctx *ctx, ctd_case *cs, int64_t *s1, uint64_t *s2_hi,
                                   uint64_t *s2_lo, uint32_t *n_batches) {
   if (!ctx || !cs) return CTD_EINVAL;
   NEED_INTACT(ctx, cs);
   HIPCHK(ctx, hipSetDevice(ctx->device));
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
-  const int64_t V = cs->ph->V;
-  if (s1) HIPCHK(ctx, hipMemcpy(s1, cs->d_s1, 8 * V, hipMemcpyDeviceToHost));
-  if (s2_hi || s2_lo) {
-    std::vector<uint64_t> s2((size_t)V * 2);
-    HIPCHK(ctx, hipMemcpy(s2.data(), cs->d_s2, 16 * V, hipMemcpyDeviceToHost));
-    for (int64_t v = 0; v < V; ++v) {
-      if (s2_lo) s2_lo[v] = s2[2 * v];
-      if (s2_hi) s2_hi[v] = s2[2 * v + 1];
-    }
+  if (s1 || s2_hi || s2_lo) {
+    void *dst[3] = {s1, s2_hi, s2_lo};
+    const int rc = read_planes(ctx, cs->ph->V, 3, dst, [&](int64_t v0, int n, void *out) {
+      return launch_read_tally(cs->d_s1, cs->d_s2, v0, n, (unsigned long long *)out, ctx->stream);
+    });
+    if (rc != CTD_OK) return rc;
   }
   if (n_batches) *n_batches = cs->batches;
   return CTD_OK;
-}
-
-// (nb*S2 - S1^2) exactly in 192-bit unsigned arithmetic, returned as double.
-static double var_numerator(int64_t s1, uint64_t hi, uint64_t lo, uint32_t nb) {
-  const unsigned __int128 plo = (unsigned __int128)lo * nb;
-  const unsigned __int128 pmid = (unsigned __int128)hi * nb + (uint64_t)(plo >> 64);
-  const uint64_t a0 = (uint64_t)plo, a1 = (uint64_t)pmid, a2 = (uint64_t)(pmid >> 64);
-  const unsigned __int128 B = (unsigned __int128)(uint64_t)s1 * (uint64_t)s1;
-  const uint64_t b0 = (uint64_t)B, b1 = (uint64_t)(B >> 64);
-  const uint64_t r0 = a0 - b0;
-  const uint64_t br0 = a0 < b0 ? 1 : 0;
-  const uint64_t r1 = a1 - b1 - br0;
-  const uint64_t br1 = (a1 < b1 || (a1 - b1) < br0) ? 1 : 0;
-  if (a2 < br1) return 0.0;  // cannot happen for consistent sums
-  const uint64_t r2 = a2 - br1;
-  return (double)r2 * 0x1p128 + (double)r1 * 0x1p64 + (double)r0;
 }
 
 extern "C" int32_t ctd_read_dose(ctd_ctx *ctx, ctd_case *cs, double *dose, double *var_of_mean) {
   if (!ctx || !cs) return CTD_EINVAL;
   NEED(ctx, cs->batches >= 2, "dose needs >= 2 folded batches");
   if (int rc0 = check_batch_sizes(ctx, cs, 0); rc0 != CTD_OK) return rc0;
-  const int64_t V = cs->ph->V;
-  std::vector<int64_t> s1((size_t)V);
-  std::vector<uint64_t> hi((size_t)V), lo((size_t)V);
-  uint32_t nb = 0;
-  int rc = ctd_read_tally(ctx, cs, s1.data(), hi.data(), lo.data(), &nb);
-  if (rc != CTD_OK) return rc;
-  std::vector<uint2> rec((size_t)V);
-  HIPCHK(ctx, hipMemcpy(rec.data(), cs->ph->vox, 8 * V, hipMemcpyDeviceToHost));
+  NEED_INTACT(ctx, cs);
+  HIPCHK(ctx, hipSetDevice(ctx->device));
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   const ctd_grid &g = cs->ph->g;
   const double vol = g.dx * g.dy * g.dz;
   const double N = (double)cs->h_next;
-  const double per_batch = N / (double)nb;
-  for (int64_t v = 0; v < V; ++v) {
-    float r;
-    std::memcpy(&r, &rec[v].x, 4);
-    const double mass_kg = (double)r * vol * 1e-3;
-    if (!(mass_kg > 0.0)) {
-      if (dose) dose[v] = 0.0;
-      if (var_of_mean) var_of_mean[v] = 0.0;
-      continue;
-    }
-    const double conv = 1.602176634e-16 / (16777216.0 * mass_kg);  // q -> Gy
-    if (dose) dose[v] = (double)s1[v] / N * conv;
-    if (var_of_mean) {
-      const double num = var_numerator(s1[v], hi[v], lo[v], nb);
-      const double var_t = num / ((double)nb * nb * (double)(nb - 1));
-      var_of_mean[v] = var_t / (per_batch * per_batch) * conv * conv;
-    }
-  }
-  return CTD_OK;
+  const uint32_t nb = cs->batches;
+  void *dst[2] = {dose, var_of_mean};
+  return read_planes(ctx, cs->ph->V, 2, dst, [&](int64_t v0, int n, void *out) {
+    return launch_read_dose(cs->d_s1, cs->d_s2, cs->ph->vox, v0, n, vol, N, N / (double)nb, nb,
+                            (double *)out, ctx->stream);
+  });
 }
 
 extern "C" int32_t ctd_read_balance(ctd_ctx *ctx, ctd_case *cs, ctd_balance *out) {

@@ -15,6 +15,8 @@
 namespace ctd {
 
 constexpr int kSigmaBlocks = 1024;
+constexpr int kReadSlots = 8;
+constexpr size_t kReadSlotBytes = (size_t)6 << 20;
 
 struct RoundItem {
   const CaseDev *cd;
@@ -46,6 +48,10 @@ struct ctd_ctx {
   size_t next_slot = 0;
   double *sigma_scratch = nullptr;
   double *sigma_host = nullptr;
+  // pinned staging of the readouts (read_planes), grown on demand to at most
+  // kReadSlots slots of kReadSlotBytes
+  void *read_host = nullptr;
+  size_t read_cap = 0;
   unsigned int *pack_stats = nullptr;  // [kPackStats] phantom statistics of k_pack
   // workspace of the deposit records (plan_records): the segments with their
   // links behind them, and the chain heads; grown on demand, at most

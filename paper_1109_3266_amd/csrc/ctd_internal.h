@@ -269,6 +269,13 @@ int launch_static_round_setup(void *table, const StaticRoundArgs &args, void *st
 int launch_sigma(const long long *s1, const unsigned long long *s2, const uint2 *vox, int64_t V,
                  uint32_t nb, double rho_min, double frac, int kind, double *scratch,
                  int nblocks, double *out, void *stream);
+// Readout of voxels [v0, v0 + n) into pinned host memory: dose and variance of
+// the mean (two planes of n), or S1 and S2's high and low words (three).
+int launch_read_dose(const long long *s1, const unsigned long long *s2, const uint2 *vox,
+                     int64_t v0, int n, double vol, double n_hist, double per_batch, uint32_t nb,
+                     double *out, void *stream);
+int launch_read_tally(const long long *s1, const unsigned long long *s2, int64_t v0, int n,
+                      unsigned long long *out, void *stream);
 // kind 0 copy (n bytes), 1 random atomics / 2 hot-spot atomics (ops on an
 // n-byte uint64 array), 3 random 8-byte gathers (ops over n bytes).
 int launch_microbench(int kind, void *buf_a, void *buf_b, int64_t n, int64_t ops, int grid,

@@ -375,17 +375,17 @@ def ctd_sigma(ctx, cs, kind=CTD_SIGMA_LOCAL, dose_frac=0.5) -> float:
 
 
 def ctd_read_tally(ctx, cs, V: int):
-    s1 = np.zeros(V, np.int64)
-    hi = np.zeros(V, np.uint64)
-    lo = np.zeros(V, np.uint64)
+    s1 = np.empty(V, np.int64)    # written whole (np.empty asks for huge pages)
+    hi = np.empty(V, np.uint64)
+    lo = np.empty(V, np.uint64)
     nb = C.c_uint32()
     check(lib().ctd_read_tally(ctx, cs, ptr(s1), ptr(hi), ptr(lo), C.byref(nb)), ctx)
     return s1, hi, lo, nb.value
 
 
 def ctd_read_dose(ctx, cs, V: int):
-    d = np.zeros(V)
-    v = np.zeros(V)
+    d = np.empty(V)
+    v = np.empty(V)
     check(lib().ctd_read_dose(ctx, cs, ptr(d), ptr(v)), ctx)
     return d, v
 
