@@ -138,6 +138,7 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   }
   dfree(ctx->sigma_scratch);
   dfree(ctx->pack_stats);
+  dfree(ctx->tool_ws);
   dfree(ctx->rec);
   dfree(ctx->rec_head);
   dfree(ctx->group_tally);
@@ -1789,21 +1790,15 @@ extern "C" int32_t ctd_tally_device(ctd_ctx *ctx, ctd_case *cs, void **s1, void 
   return CTD_OK;
 }
 
-// Read V voxels as `planes` arrays of 8-byte words into dst (null: plane not
-// wanted).  A kernel writes each piece of voxels straight into pinned memory;
-// a few host threads, one staging slot each, copy the pieces to the caller's
-// arrays: filling fresh pages of those is the slow part (4 GB/s on one
-// thread, against 57 GB/s over the link), so it is spread and overlapped.
-// launch(v0, n, out) enqueues the kernel for n voxels from v0.
-static int read_planes(ctd_ctx *ctx, int64_t V, int planes, void *const *dst,
-                       const std::function<int(int64_t, int, void *)> &launch) {
-  const int64_t fit = (int64_t)(kReadSlotBytes / (8 * (size_t)planes));
+int ctd::read_planes(ctd_ctx *ctx, int64_t V, int planes, size_t elem, void *const *dst,
+                     const std::function<int(int64_t, int, void *)> &launch) {
+  const int64_t fit = (int64_t)(kReadSlotBytes / (elem * (size_t)planes));
   // two pieces per thread at least, of 64 K voxels or more
   const int64_t piece =
       std::min(fit, std::max<int64_t>(65536, (V + 2 * kReadSlots - 1) / (2 * kReadSlots)));
   const int64_t pieces = (V + piece - 1) / piece;
   const int threads = (int)std::min<int64_t>(kReadSlots, pieces);
-  const size_t slot_bytes = 8 * (size_t)planes * (size_t)std::min(piece, V);
+  const size_t slot_bytes = (elem * (size_t)planes * (size_t)std::min(piece, V) + 255) & ~(size_t)255;
   if (ctx->read_cap < slot_bytes * (size_t)threads) {
     if (ctx->read_host) (void)hipHostFree(ctx->read_host);
     ctx->read_host = nullptr;
@@ -1831,7 +1826,8 @@ static int read_planes(ctd_ctx *ctx, int64_t V, int planes, void *const *dst,
       if (e == hipSuccess) e = hipEventSynchronize(ev);
       for (int p = 0; e == hipSuccess && p < planes; ++p)
         if (dst[p])
-          std::memcpy((char *)dst[p] + 8 * v0, slot + 8 * (size_t)p * (size_t)n, 8 * (size_t)n);
+          std::memcpy((char *)dst[p] + elem * (size_t)v0, slot + elem * (size_t)p * (size_t)n,
+                      elem * (size_t)n);
     }
     if (ev) (void)hipEventDestroy(ev);
     status[(size_t)t] = e;
@@ -1858,7 +1854,7 @@ extern "C" int32_t ctd_read_tally(ctd_ctx *ctx, ctd_case *cs, int64_t *s1, uint6
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   if (s1 || s2_hi || s2_lo) {
     void *dst[3] = {s1, s2_hi, s2_lo};
-    const int rc = read_planes(ctx, cs->ph->V, 3, dst, [&](int64_t v0, int n, void *out) {
+    const int rc = read_planes(ctx, cs->ph->V, 3, 8, dst, [&](int64_t v0, int n, void *out) {
       return launch_read_tally(cs->d_s1, cs->d_s2, v0, n, (unsigned long long *)out, ctx->stream);
     });
     if (rc != CTD_OK) return rc;
@@ -1879,7 +1875,7 @@ extern "C" int32_t ctd_read_dose(ctd_ctx *ctx, ctd_case *cs, double *dose, doubl
   const double N = (double)cs->h_next;
   const uint32_t nb = cs->batches;
   void *dst[2] = {dose, var_of_mean};
-  return read_planes(ctx, cs->ph->V, 2, dst, [&](int64_t v0, int n, void *out) {
+  return read_planes(ctx, cs->ph->V, 2, 8, dst, [&](int64_t v0, int n, void *out) {
     return launch_read_dose(cs->d_s1, cs->d_s2, cs->ph->vox, v0, n, vol, N, N / (double)nb, nb,
                             (double *)out, ctx->stream);
   });

@@ -52,6 +52,8 @@ struct ctd_ctx {
   // kReadSlots slots of kReadSlotBytes
   void *read_host = nullptr;
   size_t read_cap = 0;
+  void *tool_ws = nullptr;   // device block of ctd_gamma, at most kToolMaxBytes
+  size_t tool_cap = 0;
   unsigned int *pack_stats = nullptr;  // [kPackStats] phantom statistics of k_pack
   // workspace of the deposit records (plan_records): the segments with their
   // links behind them, and the chain heads; grown on demand, at most
@@ -223,6 +225,13 @@ uint64_t case_footprint(const ctd_grid &g, const ctd_geometry *geo, const ctd_pa
                         int ne, int tally_copies, uint64_t round_histories);
 // Alg. A1 beamlet buffer of at least n entries.
 int ensure_mh_buffer(ctd_ctx *ctx, ctd_case *cs, uint64_t n);
+// Read V voxels as `planes` arrays of elem-byte words into dst (null: plane
+// not wanted).  launch(v0, n, out) enqueues on ctx->stream what writes the
+// planes of n voxels from v0 one behind the other into pinned memory; a few host threads, one staging slot each, copy the pieces to
+// the caller's arrays: filling fresh pages of those is the slow part (4 GB/s on
+// one thread, against 57 GB/s over the link), so it is spread and overlapped.
+int read_planes(ctd_ctx *ctx, int64_t V, int planes, size_t elem, void *const *dst,
+                const std::function<int(int64_t, int, void *)> &launch);
 // MACRO tracking (ctd_macro.cpp): cells per axis for edge cs (returns the
 // cell count) and the per-band, per-cell majorant factors of a case.
 int macro_edge(const ctd_grid &g, int requested);

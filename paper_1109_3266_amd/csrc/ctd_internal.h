@@ -295,11 +295,26 @@ int launch_block_class(const uint2 *vox, int nx, int ny, int nz, int shift, cons
                        const int2 *range, uint8_t *out, void *stream);
 int launch_mh_fill(const float *f, int n_f, int C, uint64_t h_begin, uint64_t n, uint32_t key0,
                    uint32_t key1, int32_t *state, int32_t *out, void *stream);
-// Gamma index of ev against ref on an nx*ny*nz grid (ctd_gamma.hip); offs is
-// a device double4 table sorted by distance; gamma may be null; counts[2]
-// (region voxels, passing voxels) are accumulated, not cleared.
-int launch_gamma(const float *ref, const float *ev, int nx, int ny, int nz, const void *offs,
-                 int n_off, double inv_dd2, double region, double cap2, float *gamma,
+// Gamma search lattice (ctd_gamma.hip): offsets i, j, k of -L .. L lattice
+// steps per axis, i^2 + j^2 + k^2 <= r2max.  An offset lies in the cell of
+// eight voxel centres (cx, cy, cz) relative to its voxel, at the weights
+// fx[i + L], fy[j + L], fz[k + L]; a cell holds the offsets of index ranges
+// per axis, the nearest at squared distance r2min.
+struct GammaCell {
+  int32_t cx, cy, cz, r2min;
+  int32_t i0, i1, j0, j1, k0, k1;
+  int32_t reserved[2];
+};
+struct GammaTables {
+  const GammaCell *cells;            // [n_cells], ascending in r2min
+  const double *fx, *fy, *fz;        // [2 L + 1]
+  int32_t n_cells, L, r2max, s2;     // s2 = substeps^2
+};
+constexpr int kGammaSlots = 64;      // counter pairs, 128 bytes apart
+// Gamma index of ev against ref on an nx*ny*nz grid: scale = substeps /
+// dose_tol, cap2 = (gamma_cap substeps)^2; gamma [V] may be null; counts[kGammaSlots][16] (region voxels, passing voxels) accumulate.
+int launch_gamma(const float *ref, const float *ev, int nx, int ny, int nz, const GammaTables &t,
+                 double scale, double region, double cap2, float *gamma,
                  unsigned long long *counts, void *stream);
 
 }  // namespace ctd
