@@ -969,7 +969,8 @@ ctd_tuning ctd::default_tuning(const ctd_ctx *ctx) {
 
 int ctd::step_kind(const ctd_case *cs, const ctd_tuning &t) {
   if (cs->mc_cs > 0) return kStepMacro;
-  return cs->use_bound_grid && t.bound_block != 0 ? kStepDeferred : kStepPlain;
+  if (cs->use_bound_grid && t.bound_block != 0) return kStepDeferred;
+  return cs->ph->npal > 0 ? kStepPlain : kStepRecord;
 }
 
 static bool tuning_ok(const ctd_tuning &t) {
@@ -1098,8 +1099,8 @@ static int launch_chunk(const LaunchCfg &cfg, uint64_t n) {
 // few addresses, bound the launch, and cost a little where it is bound by its
 // steps:
 //  - plain steps: the water phantom ran at 94 % of the atomic rate (36.2 ms
-//    per 3e8 histories, 24.9 with records), the 32^3 pencil-beam cube at 3 %
-//    of it on contended words (122 and 8.0 ms per 1e8).  Deferred and
+//    per 3e8 histories, 16.8 with records), the 32^3 pencil-beam cube at 3 %
+//    of it on contended words (122 and 6.3 ms per 1e8).  Deferred and
 //    macro-cell steps are bound by instruction issue (head: 22.3 and 26.7 ms,
 //    14.2 and 19.2 ms per 1e8);
 //  - a deposit share (ctd_case::deposit_share) of kRecordShare or more: water
@@ -1149,6 +1150,8 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
     voxels += (uint64_t)items[i].V;
   }
   if (n < kRecordMin || n < kRecordPerVoxel * voxels) return false;
+  // a cursor's 32-bit count holds every deposit its workgroup may add to it
+  if (n / (uint64_t)cfg.grid >= ((uint64_t)1 << 28)) return false;
   dl.buckets = total;
   dl.cursors = (int32_t)((most + 1) & ~1u);
   if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors) > cfg.lds_budget) return false;
@@ -1504,9 +1507,9 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
       return hip_err(ctx, hipGetLastError(), "Metropolis-Hastings fill launch");
   }
   int rc = CTD_OK;
-  std::vector<RoundItem> group[3];
+  std::vector<RoundItem> group[kStepKinds];
   for (auto &it : items) group[it.step_kind].push_back(std::move(it));
-  for (int gi = 0; gi < 3 && rc == CTD_OK; ++gi) {
+  for (int gi = 0; gi < kStepKinds && rc == CTD_OK; ++gi) {
     if (group[gi].empty()) continue;
     rc = submit_round(ctx, group[gi], t, with_log, timed);
     if (rc == CTD_OK && ctx->fail_next_round) {
@@ -1891,10 +1894,13 @@ extern "C" int32_t ctd_read_balance(ctd_ctx *ctx, ctd_case *cs, ctd_balance *out
   uint64_t a[ACC_COUNT];
   for (int i = 0; i < ACC_COUNT; ++i) a[i] = w[kAccTotal + 2 * i];
   out->q_incident = a[ACC_Q_INC];
-  out->q_deposited = a[ACC_Q_DEP];
+  unsigned __int128 dep = 0;
+  for (int b = 0; b < kFoldBlocks; ++b)
+    dep += ((unsigned __int128)w[kAccDeposited + 2 * b + 1] << 64) + w[kAccDeposited + 2 * b];
+  out->q_deposited = (uint64_t)dep;
   out->q_escaped = a[ACC_Q_ESC];
   out->q_incident_hi = w[kAccTotal + 2 * ACC_Q_INC + 1];
-  out->q_deposited_hi = w[kAccTotal + 2 * ACC_Q_DEP + 1];
+  out->q_deposited_hi = (uint64_t)(dep >> 64);
   out->q_escaped_hi = w[kAccTotal + 2 * ACC_Q_ESC + 1];
   out->n_histories = a[ACC_N_HIST];
   out->n_missed = a[ACC_N_MISS];
@@ -1927,11 +1933,15 @@ extern "C" int32_t ctd_read_stats(ctd_ctx *ctx, ctd_case *cs, ctd_stats *out) {
   // (global majorant: one per step and one per scatter) or its flights (MACRO)
   out->n_steps = cs->mc_cs > 0 ? a[ACC_N_STEPS]
                                : a[ACC_N_STEPS] - a[ACC_N_COMPTON] - a[ACC_N_RAYLEIGH];
-  out->n_photo = a[ACC_N_PHOTO];
+  // a history that entered the box and did not escape, was not cut off and not
+  // guarded was absorbed; photoelectric, Compton and cutoff events deposit
+  const uint64_t photo =
+      a[ACC_N_HIST] - a[ACC_N_MISS] - a[ACC_N_ESCAPES] - a[ACC_N_CUTOFF] - a[ACC_STEP_GUARD];
+  out->n_photo = photo;
   out->n_compton = a[ACC_N_COMPTON];
   out->n_rayleigh = a[ACC_N_RAYLEIGH];
-  out->n_real = a[ACC_N_PHOTO] + a[ACC_N_COMPTON] + a[ACC_N_RAYLEIGH];
-  out->n_deposits = a[ACC_N_DEPOSITS];
+  out->n_real = photo + a[ACC_N_COMPTON] + a[ACC_N_RAYLEIGH];
+  out->n_deposits = photo + a[ACC_N_COMPTON] + a[ACC_N_CUTOFF];
   out->n_escapes = a[ACC_N_ESCAPES];
   out->n_refills = a[ACC_N_REFILLS];
   out->transport_ms = cs->transport_ms;

@@ -26,7 +26,7 @@ struct RoundItem {
   unsigned long long *tally = nullptr; // the batch tally the deposits go to
   std::vector<unsigned long long> prefix;
   const int32_t *beamlets = nullptr;   // Alg. A1 beamlets of the round, or null
-  int step_kind = 0;                   // kStepPlain, kStepDeferred or kStepMacro
+  int step_kind = 0;                   // kStep*
   int tab_n = 0, tab_ne = 0;           // the case's mu/rho rows and energy nodes
 };
 

@@ -18,16 +18,12 @@ namespace ctd {
 // Per-case accumulators (device, uint64 each).
 enum Acc : int {
   ACC_Q_INC = 0,     // incident energy, q units
-  ACC_Q_DEP,         // deposited energy, q units
   ACC_Q_ESC,         // escaped energy (including misses), q units
   ACC_N_HIST,
   ACC_N_STEPS,
-  ACC_N_REAL,
-  ACC_N_PHOTO,
+  ACC_N_ESCAPES,
   ACC_N_COMPTON,
   ACC_N_RAYLEIGH,
-  ACC_N_DEPOSITS,
-  ACC_N_ESCAPES,
   ACC_N_MISS,
   ACC_N_UNSCATTERED,
   ACC_N_CUTOFF,
@@ -40,11 +36,14 @@ enum Acc : int {
 // Layout of a case's counter block (uint64 words): [0, ACC_COUNT) counters of
 // the current batch (kernel atomics), [ACC_COUNT, 3 ACC_COUNT) exact 128-bit
 // totals as (lo, hi) pairs, folded after every batch, then the per-voxel
-// maxima seen by the folds: max S1, max high word of S2.
+// maxima seen by the folds: max S1, max high word of S2; then per block of
+// the fold its 128-bit part (lo, hi) of the energy deposited in all batches.
 constexpr int kAccTotal = ACC_COUNT;
 constexpr int kAccMaxS1 = 3 * ACC_COUNT;
 constexpr int kAccMaxS2Hi = 3 * ACC_COUNT + 1;
-constexpr int kAccWords = 3 * ACC_COUNT + 4;
+constexpr int kFoldBlocks = 1024;       // most blocks of k_fold
+constexpr int kAccDeposited = 3 * ACC_COUNT + 2;
+constexpr int kAccWords = (kAccDeposited + 2 * kFoldBlocks + 1) & ~1;
 
 constexpr float kQScale = 16777216.0f;  // 2^24: tally unit q = 2^-24 keV
 constexpr int kTallyCopies = 8;         // one batch tally per XCD of an MI355X
@@ -216,13 +215,14 @@ struct LaunchCfg {
   size_t lds_budget; // LDS a workgroup may take without lowering the residency
 };
 
-// Step of a transport launch, the same for every case of it: kStepPlain
-// (GLOBAL tracking, every tentative collision read from its voxel),
-// kStepDeferred (GLOBAL tracking with the bound grid's early rejection and
-// collision passes: every case has a bound grid in use),
-// kStepMacro (MACRO tracking).  A round whose cases need different steps is
-// split into one launch per step.
-constexpr int kStepPlain = 0, kStepDeferred = 1, kStepMacro = 2;
+// Step of a transport launch, the same for every case of it: GLOBAL tracking
+// with every tentative collision read from its voxel, a palette index
+// (kStepPlain) or an 8-byte record (kStepRecord); GLOBAL tracking with the
+// bound grid's early rejection and collision passes (kStepDeferred: every case
+// has a bound grid in use); MACRO tracking (kStepMacro).  A round whose cases
+// need different steps is split into one launch per step.
+constexpr int kStepPlain = 0, kStepDeferred = 1, kStepMacro = 2, kStepRecord = 3;
+constexpr int kStepKinds = 4;
 
 // Kernel launchers (ctd_kernels.hip).  All enqueue on `stream`.
 int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,

@@ -113,13 +113,13 @@ __device__ __forceinline__ float cos_turns(float t) { return __builtin_amdgcn_co
 
 // Inverse-CDF surface mu(zeta, E): one 16-byte cell gives both zeta
 // neighbours at both energy neighbours; bilinear, clamped to [-1, 1].
-__device__ __forceinline__ float surface(const GLOBAL float4 *__restrict__ Q, int nz, int je,
-                                         float we,
-                                         float zeta) {
+// Q: row 0 of the surfaces; row: energy cell, past the rows of other materials
+__device__ __forceinline__ float surface(const GLOBAL float4 *__restrict__ Q, int nz,
+                                         uint32_t row, float we, float zeta) {
   const float f = zeta * (float)(nz - 1);
   const int i = min((int)f, nz - 2);
   const float wz = f - (float)i;
-  const float4 q = Q[(size_t)je * (size_t)(nz - 1) + (size_t)i];
+  const float4 q = Q[(uint64_t)row * (uint32_t)(nz - 1) + (uint32_t)i];
   const float s0 = lerpf(q.x, q.y, wz);
   const float s1 = lerpf(q.z, q.w, wz);
   return fminf(fmaxf(lerpf(s0, s1, we), -1.0f), 1.0f);
@@ -253,7 +253,12 @@ __device__ __forceinline__ uint64_t lane0_u64(uint64_t v) {
 // Per-wave event counters in LDS (one slot of ACC_COUNT words per wave),
 // bumped with LDS atomics when an event happens and added to the case's
 // device counters when the wave switches case or exits.  Keeping them out of
-// registers leaves room for more resident waves.
+// registers leaves room for more resident waves.  Lanes that add to one word
+// take turns in the LDS (half of the CU's cycles on water), so what follows
+// from other sums is not counted here: the deposited energy is the sum of the
+// batch tallies (k_fold), absorptions and deposits follow from the counts of
+// how histories go on and end (water 76.3 -> 71.0 ms per 1e9 histories, the
+// pencil beam 15.3 -> 13.1 ms per 2e8).
 struct Counters {
   unsigned long long *s;
   __device__ __forceinline__ void add(int i, unsigned long long v) { atomicAdd(s + i, v); }
@@ -276,44 +281,46 @@ __device__ __forceinline__ void tally_add(const StepCase &S, int32_t vox, unsign
 
 // Deposit records (kOutRecords): append (voxel within its bucket, q) to the
 // bucket's segment of this workgroup.  A cursor word holds the segment and
-// the records appended to it; the lane whose append finds the segment full
-// (exactly one per segment) takes the workgroup's next segment, links it to
-// the full one and installs it, while later lanes add again a bounded number
-// of times.  A lane without a slot after that, or in a workgroup without
-// segments left adds straight to the tally.  Against the tally's atomics a
-// deposit costs the wave an LDS round trip and 8 bytes into a line that stays
-// in L2 until it is full (water 128x128x100, 1e8 histories: 11.4 ms at 94 % of
-// the memory-side atomic rate, 7.1 ms with records).  The loop's condition is the
-// wave's (a ballot), so the installing lane always runs inside it.
+// the records appended to it: one LDS add gives a lane its place, unless the
+// segment is full.  The lane whose add finds it so first (exactly one per
+// segment) takes the workgroup's next segment, links it to the full one and
+// installs it, while later lanes add again a bounded number of times.  A lane
+// without a slot after that, or in a workgroup without segments left, adds
+// straight to the tally.  Against the tally's atomics a deposit costs the wave
+// an LDS round trip and 8 bytes into a line that mostly stays in L2 until it is
+// full (water 128x128x100, 1e8 histories: 11.4 ms at 94 % of the memory-side
+// atomic rate, 5.1 ms with records, bound by instruction issue).  The slow
+// path's loop condition is the wave's (a ballot), so the installing lane
+// always runs inside it.
 __device__ __forceinline__ void record_deposit(const StepCase &S, int32_t vox, uint32_t q) {
   LOCAL unsigned long long *cur = S.cur + ((uint32_t)vox >> S.bbits);
-  bool todo = true;
-  for (int t = 0; __ballot(todo) != 0ull; ++t) {
-    if (!todo) continue;
-    const unsigned long long w =
-        __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
-    uint32_t seg = (uint32_t)(w >> 32), pos = (uint32_t)w;
-    if (pos >= kLogSeg) {
-      const bool mine = pos == kLogSeg;
+  unsigned long long w =
+      __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  if ((uint32_t)w >= kLogSeg) {
+    bool todo = true;
+    for (int t = 0; __ballot(todo) != 0ull; ++t) {
+      if (!todo) continue;
+      const bool mine = (uint32_t)w == kLogSeg;
       const uint32_t next = __hip_atomic_fetch_add(S.seg_next, mine ? 1u : 0u, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
       if (next >= S.seg_next[1] || (!mine && t >= 16)) {
         tally_add(S, vox, q);
+        w = kLogSeg;
         todo = false;
       } else if (mine) {
-        S.rec_prev[next] = seg;
-        seg = next;
-        pos = 0;
-        __hip_atomic_store(cur, ((unsigned long long)next << 32) | 1ull, __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_WORKGROUP);
+        S.rec_prev[next] = (uint32_t)(w >> 32);
+        w = (unsigned long long)next << 32;
+        __hip_atomic_store(cur, w | 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        todo = false;
+      } else {
+        w = __hip_atomic_fetch_add(cur, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        todo = (uint32_t)w >= kLogSeg;
       }
     }
-    if (todo && pos < kLogSeg) {
-      S.rec[(size_t)seg * kLogSeg + pos] =
-          make_uint2((uint32_t)vox & ((1u << S.bbits) - 1u), q);
-      todo = false;
-    }
+    if ((uint32_t)w == kLogSeg) return;   // it went to the tally
   }
+  const uint32_t i = (uint32_t)(w >> 32) * kLogSeg | (uint32_t)w;
+  S.rec[i] = make_uint2((uint32_t)vox & ((1u << S.bbits) - 1u), q);
 }
 
 // Tally mode 2: add the wave's LDS sub-tally to the case's tally and empty it
@@ -366,14 +373,16 @@ struct Photon {
 
 // Photon.k: in the low bits the random pairs the photon has taken (global
 // majorant) or its flights (MACRO tracking), kScatBit once the photon has
-// scattered, kGoneBit while an escaped photon's counters wait for the wave's
-// next refill step (deferred collisions), kDueBit while a scatter selected
+// scattered, kEndBit once its history has ended (and kGoneBit if it left the
+// box) until the wave's next refill step counts it, with the other histories
+// that ended meanwhile, kDueBit while a scatter selected
 // at a block's second pair waits for the next block (plain steps; the
 // voxel, material and process wait in the lane's LDS slot).
 constexpr uint32_t kScatBit = 0x80000000u;
 constexpr uint32_t kGoneBit = 0x40000000u;
 constexpr uint32_t kDueBit = 0x20000000u;
-constexpr uint32_t kStepMask = 0x1FFFFFFFu;
+constexpr uint32_t kEndBit = 0x10000000u;
+constexpr uint32_t kStepMask = 0x0FFFFFFFu;
 
 // mu/rho rows ti and ti + 1 (energy nodes je, je + 1 of one material): from
 // the workgroup's LDS copy (TAB) or through the caches.
@@ -485,9 +494,7 @@ __device__ __forceinline__ void deposit(const StepCase &S, const CaseDev &G, Pho
       }
     }
     if (!cached) tally_add(S, vox, q);
-    c.add(ACC_Q_DEP, q);
   }
-  c.add(ACC_N_DEPOSITS, 1);
   log_event<OUT>(G, p, type, vox, e, Eafter);
 }
 
@@ -505,7 +512,7 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
   p.seq = 0;
   p.ks = 0;
   const uint4 r = philox10(0u, p.hlo, p.hhi, 0u, S.key0, S.key1);
-  const float E = fmaf(unif(r.x), G.bin_width, G.bin_lo[j]);
+  const float E = fmaf(unif(r.x), G.bin_width, ((const GLOBAL float *)G.bin_lo)[j]);
   float sx, sy, sz, dx, dy, dz;
   int beamlet = -1;
   if (G.kind == CTD_GEOM_PENCIL) {
@@ -517,7 +524,7 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
       // exact in double: 24-bit uniform times an integer < 2^31
       int pi = (int)((double)unif(r.y) * (double)G.nproj);
       pi = min(pi, G.nproj - 1);
-      const float4 sc = G.proj_sc[pi];
+      const float4 sc = ((const GLOBAL float4 *)G.proj_sc)[pi];
       sp = sc.x;
       cp = sc.y;
       zoff = sc.z;
@@ -535,15 +542,15 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
     if (G.fl_n > 0) {
       int I;
       if (G.fl_chains > 0) {
-        I = mh_beam[local];               // Alg. A1 chain step of this history
+        I = ((const GLOBAL int32_t *)mh_beam)[local];               // Alg. A1 chain step of this history
       } else {
         // beamlet I = min{I : C_I > u F}, decided in FP64 (exact inputs: u has
         // 24 bits, k / 2^gbits <= u exactly, so the guide entry is a lower bound)
         const uint4 r2 = philox10(0u, p.hlo, p.hhi, 1u, S.key0, S.key1);
         const double u = (double)unif(r2.x);
         const double x = u * G.fl_total;
-        I = G.fl_guide[(int)(u * (double)(1 << G.fl_gbits))];
-        while (I < G.fl_n - 1 && G.fl_cdf[I] <= x) ++I;
+        I = ((const GLOBAL int32_t *)G.fl_guide)[(int)(u * (double)(1 << G.fl_gbits))];
+        while (I < G.fl_n - 1 && ((const GLOBAL double *)G.fl_cdf)[I] <= x) ++I;
       }
       const int ib = I / G.fl_na;
       const int ia = I - ib * G.fl_na;
@@ -600,15 +607,19 @@ __device__ bool source(const StepCase &S, const CaseDev &G, uint64_t h, int j,
   return true;
 }
 
-// The photon leaves the voxel box with its energy.
+// Counters of a history that has ended (kEndBit), at the wave's next refill
+// step: one pass over all of them instead of one inside each step (water 63.8
+// -> 60.4 ms per 1e9 histories, with the voxel layout fixed per instance).
 template <int OUT>
-__device__ __forceinline__ bool escape(Photon &p, const CaseDev &G, Counters &c, uint32_t k) {
-  c.add(ACC_N_STEPS, k);
-  c.add(ACC_N_ESCAPES, 1);
-  if (!(p.k & kScatBit)) c.add(ACC_N_UNSCATTERED, 1);
-  c.add(ACC_Q_ESC, (uint32_t)(p.E * kQScale));
-  log_event<OUT>(G, p, 5, -1, p.E, p.E);
-  return false;
+__device__ __forceinline__ void count_ended(Photon &p, const CaseDev &G, Counters &c) {
+  c.add(ACC_N_STEPS, p.k & kStepMask);
+  if (p.k & kGoneBit) {   // left the voxel box with its energy
+    c.add(ACC_N_ESCAPES, 1);
+    if (!(p.k & kScatBit)) c.add(ACC_N_UNSCATTERED, 1);
+    c.add(ACC_Q_ESC, (uint32_t)(p.E * kQScale));
+    log_event<OUT>(G, p, 5, -1, p.E, p.E);
+  }
+  p.k &= ~(kGoneBit | kEndBit);
 }
 
 // Outcome of the selection at a tentative collision; kSelPhoto and kSelDone
@@ -620,22 +631,20 @@ constexpr int kSelFict = 0, kSelCompton = 1, kSelRayleigh = 2, kSelPhoto = 3, kS
 // Compton, Rayleigh) interpolated at E and xi = u1 * the majorant:
 // photoelectric, Compton, Rayleigh or fictitious by comparing xi with the
 // cumulative sums in that order.  A photoelectric absorption deposits E
-// locally here; nsteps is what the photon adds to the step counter when it
-// ends.
-template <int OUT>
+// locally here.
+template <int OUT, bool TAB>
 __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, const CaseDev &G,
                                               Counters &c, int32_t vox, float rho, float a,
-                                              float b, float cr, float xi, uint32_t nsteps) {
+                                              float b, float cr, float xi) {
   const float mpe = rho * a;
   const float c1 = mpe + rho * b;
   if (xi < mpe) {  // photoelectric: absorb, deposit E locally
-    c.add(ACC_N_STEPS, nsteps);
-    c.add(ACC_N_PHOTO, 1);
+    p.k |= kEndBit;
     deposit<OUT>(S, G, p, c, vox, p.E, 1, 0.0f);
     return kSelPhoto;
   }
   if (xi < c1) return kSelCompton;
-  if (S.rayleigh) {
+  if (TAB || S.rayleigh) {
     const float c2 = c1 + rho * cr;
     if (xi < c2) return kSelRayleigh;
   }
@@ -645,13 +654,14 @@ __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, cons
 // Tentative collision at voxel vox against majorant mumax with selection
 // word ry: read the voxel (1-byte palette index or 8-byte record) and its
 // table rows, then select; m receives the voxel's material.
-template <int OUT, bool TAB>
+// LAYOUT: voxels as palette indices or 8-byte records, or as the case has them.
+constexpr int kVoxAny = 0, kVoxPalette = 1, kVoxRecord = 2;
+template <int OUT, bool TAB, int LAYOUT>
 __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const CaseDev &G,
                                          const LOCAL uint2 *pal, Counters &c, int32_t vox,
-                                         uint32_t ry, float mumax, uint32_t nsteps,
-                                         uint32_t &m) {
+                                         uint32_t ry, float mumax, uint32_t &m) {
   uint32_t rbits;
-  if (S.npal) {  // 1-byte index into the workgroup's LDS palette
+  if (LAYOUT == kVoxPalette || (LAYOUT == kVoxAny && S.npal)) {  // 1-byte index into the workgroup's LDS palette
     const uint32_t i8 = S.vox8[vox];
     rbits = pal[i8].x;
     m = pal[i8].y;
@@ -664,47 +674,46 @@ __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const Cas
   float4 t0, t1;
   table_rows<TAB>(S, ti, t0, t1);
   const float a = lerpf(t0.x, t1.x, p.we), b = lerpf(t0.y, t1.y, p.we);
-  const float cr = S.rayleigh ? lerpf(t0.z, t1.z, p.we) : 0.0f;
-  return select_process<OUT>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
-                             unif(ry) * mumax, nsteps);
+  // (the staged rows hold 0 for Rayleigh where the case has none)
+  const float cr = TAB || S.rayleigh ? lerpf(t0.z, t1.z, p.we) : 0.0f;
+  return select_process<OUT, TAB>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
+                             unif(ry) * mumax);
 }
 
 // Compton (sel = kSelCompton, Sec. 2.2.3) or Rayleigh (Sec. 2.2.2) scatter in
 // voxel vox of material m: the polar angle from the process's surface at
 // uniform w0, the azimuth from w1; returns false when the photon is done
-// (Compton below the cutoff).  nsteps as in select_process.
+// (Compton below the cutoff).  Both processes go through the surface lookup
+// and the rotation together: most waves have lanes of each, and the rotation
+// is half of a scatter (water 60.4 -> 57.2 ms per 1e9 histories, macro-cell
+// head 32.8 -> 32.0 ms, six uneven cases 58.8 -> 56.9 ms).
 template <int OUT, bool TAB>
 __device__ __forceinline__ bool scatter(Photon &p, const StepCase &S, const CaseDev &G,
                                         Counters &c, int sel, int32_t vox, uint32_t m,
-                                        uint32_t w0, uint32_t w1, uint32_t nsteps) {
+                                        uint32_t w0, uint32_t w1) {
   p.k |= kScatBit;
-  if (sel == kSelCompton) {
-    c.add(ACC_N_COMPTON, 1);
-    // surface fields from the workgroup's LDS copy of the case (read only here)
-    const int nzc = G.nzc;
-    const GLOBAL float4 *Q = (const GLOBAL float4 *)G.comp_quad;
-    if (G.comp_per_mat) Q += (size_t)m * (size_t)(S.ne - 1) * (size_t)(nzc - 1);
-    const float mu = surface(Q, nzc, p.je, p.we, unif(w0));
-    const float E = p.E;
-    const float Ep = E * __builtin_amdgcn_rcpf(fmaf(E * kInvMeC2, 1.0f - mu, 1.0f));
-    deposit<OUT>(S, G, p, c, vox, E - Ep, 2, Ep);  // exact: Ep > E/2 (Sterbenz)
-    rotate(p, mu, unif(w1));
-    set_energy<TAB>(p, S, Ep);
-    if (Ep < G.e_cut) {
-      c.add(ACC_N_STEPS, nsteps);
-      c.add(ACC_N_CUTOFF, 1);
-      deposit<OUT>(S, G, p, c, vox, Ep, 4, 0.0f);
-      return false;
-    }
+  const bool compton = sel == kSelCompton;
+  c.add(compton ? ACC_N_COMPTON : ACC_N_RAYLEIGH, 1);
+  // surface fields from the workgroup's LDS copy of the case (read only here)
+  const uint32_t mrow = __umul24(m, (uint32_t)(S.ne - 1)) + (uint32_t)p.je;
+  const float mu = surface((const GLOBAL float4 *)(compton ? G.comp_quad : G.rayl_quad),
+                           compton ? G.nzc : G.nzr,
+                           compton && !G.comp_per_mat ? (uint32_t)p.je : mrow, p.we, unif(w0));
+  rotate(p, mu, unif(w1));
+  if (!compton) {
+    log_event<OUT>(G, p, 3, vox, 0.0f, p.E);
     return true;
   }
-  c.add(ACC_N_RAYLEIGH, 1);
-  const int nzr = G.nzr;
-  const GLOBAL float4 *Q =
-      (const GLOBAL float4 *)G.rayl_quad + (size_t)m * (size_t)(S.ne - 1) * (size_t)(nzr - 1);
-  const float mu = surface(Q, nzr, p.je, p.we, unif(w0));
-  rotate(p, mu, unif(w1));
-  log_event<OUT>(G, p, 3, vox, 0.0f, p.E);
+  const float E = p.E;
+  const float Ep = E * __builtin_amdgcn_rcpf(fmaf(E * kInvMeC2, 1.0f - mu, 1.0f));
+  deposit<OUT>(S, G, p, c, vox, E - Ep, 2, Ep);  // exact: Ep > E/2 (Sterbenz)
+  set_energy<TAB>(p, S, Ep);
+  if (Ep < G.e_cut) {
+    c.add(ACC_N_CUTOFF, 1);
+    p.k |= kEndBit;
+    deposit<OUT>(S, G, p, c, vox, Ep, 4, 0.0f);
+    return false;
+  }
   return true;
 }
 
@@ -736,8 +745,17 @@ __device__ __forceinline__ bool guard_ok(const Photon &p, Counters &c) {
 // Photon.k count the pairs taken) is words 2 (P mod 2), 2 (P mod 2) + 1 of
 // block P / 2 + 1.  A step takes a pair (free path, selection), a Compton or
 // Rayleigh scatter the pair after its step (polar angle, azimuth).
+template <int OUT>
 __device__ __forceinline__ uint4 pair_block(const Photon &p, const StepCase &S, uint32_t P) {
-  return philox10((P >> 1) + 1u, p.hlo, p.hhi, 0u, S.key0, S.key1);
+  uint32_t k0 = S.key0, k1 = S.key1;
+#if defined(__HIP_DEVICE_COMPILE__)
+  // the record-keeping instance recomputes the 18 round keys (scalar adds)
+  // instead of holding them over the step loop, where they push its pointers
+  // into vector registers (water 57.2 -> 55.9 ms per 1e9; the head, whose step
+  // has scalar registers left, 124.6 -> 125.2 ms, keeps them)
+  if constexpr (OUT == kOutRecords) asm volatile("" : "+s"(k0), "+s"(k1));
+#endif
+  return philox10((P >> 1) + 1u, p.hlo, p.hhi, 0u, k0, k1);
 }
 
 // One Woodcock step (Sec. 2.1) against the global majorant with words w0
@@ -746,11 +764,10 @@ __device__ __forceinline__ uint4 pair_block(const Photon &p, const StepCase &S, 
 // Returns the selection; a Compton or Rayleigh scatter is left to the
 // caller, with the voxel and its material in vox and m.  The caller applies
 // the step guard, once per block.
-template <int OUT, bool TAB>
+template <int OUT, bool TAB, int LAYOUT>
 __device__ __forceinline__ int step(Photon &p, const StepCase &S, const CaseDev &G,
                                     const LOCAL uint2 *pal, Counters &c, uint32_t w0,
                                     uint32_t w1, int32_t &vox, uint32_t &m) {
-  const uint32_t P = p.k & kStepMask;
   p.k += 1;
   if (OUT == kOutEvents) p.ks += 1;
   const float s = -__log2f(unif(w0)) * p.sc;  // -ln(u) / mu_max
@@ -759,12 +776,12 @@ __device__ __forceinline__ int step(Photon &p, const StepCase &S, const CaseDev 
   p.pz = fmaf(s, p.uz * S.inv_dz, p.pz);
   const bool inside = inside_box(p, S);
   if (!inside) {
-    escape<OUT>(p, G, c, P + 1u);
+    p.k |= kGoneBit | kEndBit;
     return kSelDone;
   }
   const uint32_t ix = (uint32_t)p.px, iy = (uint32_t)p.py, iz = (uint32_t)p.pz;
   vox = (int32_t)__umul24(__umul24(iz, (uint32_t)S.ny) + iy, (uint32_t)S.nx) + (int32_t)ix;
-  return select_at<OUT, TAB>(p, S, G, pal, c, vox, w1, p.mumax, P + 1u, m);
+  return select_at<OUT, TAB, LAYOUT>(p, S, G, pal, c, vox, w1, p.mumax, m);
 }
 
 // One Woodcock step with deferred collisions (bound grid present), words w0
@@ -791,7 +808,7 @@ __device__ __forceinline__ int step_fast(Photon &p, const StepCase &S, const LOC
   p.pz = fmaf(s, p.uz * S.inv_dz, p.pz);
   const bool inside = inside_box(p, S);
   if (!inside) {
-    p.k |= kGoneBit;
+    p.k |= kGoneBit | kEndBit;
     return kStepGone;
   }
   const uint32_t ix = (uint32_t)p.px, iy = (uint32_t)p.py, iz = (uint32_t)p.pz;
@@ -843,7 +860,6 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
     p.rw = r.w;
     p.cell = 0xFFFFFFFFu;
   }
-  const uint32_t k = p.k & kStepMask;
   float tau = p.tau;
   const int ncx = G.mc_nx, ncy = G.mc_ny, ncz = G.mc_nz;
   const float fcs = G.mc_fcs;
@@ -903,7 +919,8 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
   if (crossings) c.add(ACC_N_CROSS, crossings);
   if (out) {
     p.tau = -1.0f;
-    return escape<OUT>(p, G, c, k);
+    p.k |= kGoneBit | kEndBit;
+    return false;
   }
   if (!hit) {  // the flight goes on in the next call, from this cell
     p.tau = tau;
@@ -923,10 +940,10 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
   const int32_t vox = (int32_t)__umul24(__umul24((uint32_t)iz, (uint32_t)S.ny) + (uint32_t)iy,
                                          (uint32_t)S.nx) + ix;
   uint32_t m;
-  const int sel = select_at<OUT, TAB>(p, S, G, pal, c, vox, p.ry, mu_c, k, m);
+  const int sel = select_at<OUT, TAB, kVoxAny>(p, S, G, pal, c, vox, p.ry, mu_c, m);
   if (sel == kSelFict) return true;
   if (sel == kSelPhoto) return false;
-  return scatter<OUT, TAB>(p, S, G, c, sel, vox, m, p.rz, p.rw, k);
+  return scatter<OUT, TAB>(p, S, G, c, sel, vox, m, p.rz, p.rw);
 }
 
 // ------------------------------------------------------- transport kernel
@@ -977,7 +994,7 @@ __device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseD
 }
 
 // KIND selects the step for every case of the launch (kStepPlain,
-// kStepDeferred, kStepMacro; a round whose cases need different steps is
+// kStepDeferred, kStepMacro, kStepRecord; a round whose cases need different steps is
 // split into one launch per step), so each instance carries only its own
 // step's registers and a tight loop of its steps between refills.  Every
 // instance is held to 96 VGPRs (5 waves per SIMD): the global steps fit
@@ -1068,7 +1085,12 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       const int n_rows = cd->nmat * cd->ne, n_e = cd->ne;
       const float4 *src = cd->mu_rho;
       const float *srcm = cd->mu_max;
-      for (int i = threadIdx.x; i < n_rows; i += blockDim.x) tab[i] = src[i];
+      const bool rayl = cd->rayleigh != 0;
+      for (int i = threadIdx.x; i < n_rows; i += blockDim.x) {
+        float4 r = src[i];
+        if (!rayl) r.z = 0.0f;
+        tab[i] = r;
+      }
       for (int i = threadIdx.x; i < n_e; i += blockDim.x) tabmax[i] = srcm[i];
       const float *srcb = cd->bnd;
       const int n_b = cd->nmat * (n_e - 1);
@@ -1091,11 +1113,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       const unsigned long long dead = __ballot(!alive);
       const int ndead = __popcll(dead);
       if (ndead == 64 || ndead >= refill_min) {
-        // counters of photons that left the box since the last refill step
-        if (!alive && (p.k & kGoneBit)) {
-          p.k &= ~kGoneBit;
-          escape<OUT>(p, G, cnt, p.k & kStepMask);
-        }
+        // counters of the histories that ended since the last refill step
+        if (!alive && (p.k & kEndBit)) count_ended<OUT>(p, G, cnt);
         // idle lanes take the stash's records in order, lowest lanes first;
         // an empty stash is refilled from the pool (a chunk of case c is
         // claimed when the pool is empty) with the sources of the pool's
@@ -1171,7 +1190,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
           float4 pe, dir;
           if ((uint32_t)lane < ng) {
             int j = wbin;
-            while (j + 1 < G.nbins && local >= R.prefix[j + 1]) ++j;
+            const GLOBAL unsigned long long *pre = (const GLOBAL unsigned long long *)R.prefix;
+            while (j + 1 < G.nbins && local >= pre[j + 1]) ++j;
             ok = source<OUT>(S, G, R.h_begin + local, j, R.beamlets, local, cnt, pe, dir);
           }
           const unsigned long long okm = __ballot(ok);
@@ -1188,7 +1208,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
           st_n = (uint32_t)__popcll(okm);
           pool_next += ng;
           if (pool_next < pool_end) {
-            while (wbin + 1 < G.nbins && pool_next >= R.prefix[wbin + 1]) ++wbin;
+            const GLOBAL unsigned long long *pre = (const GLOBAL unsigned long long *)R.prefix;
+            while (wbin + 1 < G.nbins && pool_next >= pre[wbin + 1]) ++wbin;
           }
         }
         if (filled > 0) refills += 1;
@@ -1211,16 +1232,17 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
             // the step's selection word waited in the lane's LDS word
             const uint32_t P = p.k & kStepMask;
             uint32_t m;
-            const int sel =
-                select_at<OUT, TAB>(p, S, G, pal_lds, cnt, pvox, lane_word->y, p.mumax, P, m);
+            // (a bound grid comes with the 8-byte records only)
+            const int sel = select_at<OUT, TAB, kVoxRecord>(p, S, G, pal_lds, cnt, pvox,
+                                                            lane_word->y, p.mumax, m);
             if (sel == kSelPhoto) {
               alive = false;
             } else if (sel != kSelFict) {   // the scatter takes the next pair
-              const uint4 q = pair_block(p, S, P);
+              const uint4 q = pair_block<OUT>(p, S, P);
               const bool odd = (P & 1u) != 0u;
               p.k += 1;
               alive = scatter<OUT, TAB>(p, S, G, cnt, sel, pvox, m, odd ? q.z : q.x,
-                                        odd ? q.w : q.y, P + 1u);
+                                              odd ? q.w : q.y);
             }
             pvox = -1;
           }
@@ -1231,7 +1253,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         for (;;) {
           if (alive && pvox < 0 && (alive = guard_ok(p, cnt))) {
             const uint32_t P = p.k & kStepMask;
-            const uint4 r = pair_block(p, S, P);
+            const uint4 r = pair_block<OUT>(p, S, P);
             LOCAL uint32_t *u1 = &lane_word->y;
             // the bound grid's address into scalar registers once per block
             // (held in vector registers, it was re-read before every step)
@@ -1252,9 +1274,10 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         // or the scatter a photon left waiting; its second pair takes the
         // next step, whose scatter then waits for the next block.  A photon
         // starts every pass at an even pair.
+        constexpr int kLayout = KIND == kStepPlain ? kVoxPalette : kVoxRecord;
         for (;;) {
           if (alive && (alive = guard_ok(p, cnt))) {
-            const uint4 r = pair_block(p, S, p.k & kStepMask);
+            const uint4 r = pair_block<OUT>(p, S, p.k & kStepMask);
             int sel;
             int32_t vox = 0;
             uint32_t m = 0, w0 = r.z, w1 = r.w;
@@ -1267,16 +1290,16 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
               w0 = r.x;
               w1 = r.y;
             } else {
-              sel = step<OUT, TAB>(p, S, G, pal_lds, cnt, r.x, r.y, vox, m);
+              sel = step<OUT, TAB, kLayout>(p, S, G, pal_lds, cnt, r.x, r.y, vox, m);
             }
             if (sel == kSelCompton || sel == kSelRayleigh) {
               p.k += 1;
-              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, vox, m, w0, w1, p.k & kStepMask);
+              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, vox, m, w0, w1);
             } else if (sel >= kSelPhoto) {
               alive = false;
             }
             if (alive && (p.k & 1u)) {   // the block's second pair: a step
-              sel = step<OUT, TAB>(p, S, G, pal_lds, cnt, r.z, r.w, vox, m);
+              sel = step<OUT, TAB, kLayout>(p, S, G, pal_lds, cnt, r.z, r.w, vox, m);
               if (sel == kSelCompton || sel == kSelRayleigh) {
                 *lane_word = make_uint2((uint32_t)vox, m | ((uint32_t)sel << 16));
                 p.k |= kDueBit;
@@ -1475,7 +1498,8 @@ __global__ void __launch_bounds__(256) k_mh_fill(const float *__restrict__ f, in
 // S1 += T_b, S2 += T_b^2 (128-bit), T_b = 0 (Sec. 2.2.1 batch statistics) for
 // each batch b of a launch in order: batch 0 in T, the exact sum of its
 // ncopies per-XCD copies, the others in `more` ([nbatch - 1][V], one copy).
-// The sums are read and written once for all of them.  Block 0 also folds the
+// The sums are read and written once for all of them; each block adds what it
+// folded to its words of the deposited energy (kAccDeposited).  Block 0 also folds the
 // counters into their 128-bit totals; every block records the largest S1 and
 // S2 high word it produced (overflow headroom; both only grow with b).
 __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T, int ncopies,
@@ -1483,7 +1507,7 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
                                               long long *__restrict__ S1,
                                               unsigned long long *__restrict__ S2, int64_t V,
                                               unsigned long long *__restrict__ acc) {
-  __shared__ unsigned long long m1[256], m2[256];
+  __shared__ unsigned long long m1[256], m2[256], ms[256];
   if (blockIdx.x == 0 && threadIdx.x < ACC_COUNT) {
     const unsigned long long v = acc[threadIdx.x];
     if (v) {
@@ -1494,7 +1518,7 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
       acc[threadIdx.x] = 0ull;
     }
   }
-  unsigned long long mx1 = 0ull, mx2 = 0ull;
+  unsigned long long mx1 = 0ull, mx2 = 0ull, dep = 0ull;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < V; i += stride) {
     unsigned long long t = 0ull;
@@ -1516,6 +1540,7 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
       hi += __umul64hi(v, v) + (lo < plo ? 1ull : 0ull);
     }
     if (sum == 0ull) continue;
+    dep += sum;
     const long long s1 = S1[i] + (long long)sum;
     S1[i] = s1;
     const unsigned long long nlo = S2[2 * i] + lo;
@@ -1527,11 +1552,13 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
   }
   m1[threadIdx.x] = mx1;
   m2[threadIdx.x] = mx2;
+  ms[threadIdx.x] = dep;
   __syncthreads();
   for (int o = 128; o > 0; o >>= 1) {
     if ((int)threadIdx.x < o) {
       m1[threadIdx.x] = max(m1[threadIdx.x], m1[threadIdx.x + o]);
       m2[threadIdx.x] = max(m2[threadIdx.x], m2[threadIdx.x + o]);
+      ms[threadIdx.x] += ms[threadIdx.x + o];
     }
     __syncthreads();
   }
@@ -1540,6 +1567,12 @@ __global__ void __launch_bounds__(256) k_fold(unsigned long long *__restrict__ T
   // maxima only grow (until the host clears them between launches), so a
   // stale read can only add an atomic, never drop a needed one.
   if (threadIdx.x == 0) {
+    // the block's part of the deposited energy, 128 bits (its own words; the
+    // batches of a launch together stay below 2^63)
+    unsigned long long *q = acc + kAccDeposited + 2 * blockIdx.x;
+    const unsigned long long lo = q[0] + ms[0];
+    q[1] += lo < ms[0] ? 1ull : 0ull;
+    q[0] = lo;
     const unsigned long long r1 =
         __hip_atomic_load(acc + kAccMaxS1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const unsigned long long r2 =
@@ -1893,14 +1926,15 @@ int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,
   using Kern = void (*)(const RoundCase *, int, uint64_t, unsigned long long *, int, int, int,
                         int, int, int, int, int, DepositLog);
 #define CTD_KIND(OUT, KIND) {k_transport<OUT, KIND, false>, k_transport<OUT, KIND, true>}
-  static const Kern kerns[3][3][2] = {
+  static const Kern kerns[3][kStepKinds][2] = {
       {CTD_KIND(kOutTally, kStepPlain), CTD_KIND(kOutTally, kStepDeferred),
-       CTD_KIND(kOutTally, kStepMacro)},
+       CTD_KIND(kOutTally, kStepMacro), CTD_KIND(kOutTally, kStepRecord)},
       {CTD_KIND(kOutEvents, kStepPlain), CTD_KIND(kOutEvents, kStepDeferred),
-       CTD_KIND(kOutEvents, kStepMacro)},
-      {CTD_KIND(kOutRecords, kStepPlain), {nullptr, nullptr}, {nullptr, nullptr}}};
+       CTD_KIND(kOutEvents, kStepMacro), CTD_KIND(kOutEvents, kStepRecord)},
+      {CTD_KIND(kOutRecords, kStepPlain), {nullptr, nullptr}, {nullptr, nullptr},
+       {nullptr, nullptr}}};
 #undef CTD_KIND
-  if (step_kind < kStepPlain || step_kind > kStepMacro || out < kOutTally || out > kOutRecords)
+  if (step_kind < 0 || step_kind >= kStepKinds || out < kOutTally || out > kOutRecords)
     return -1;
   const Kern kern = kerns[out][step_kind][tab_n > 0 ? 1 : 0];
   if (!kern) return -1;
@@ -1949,7 +1983,7 @@ int launch_fold(unsigned long long *tally, int ncopies, unsigned long long *more
                 void *stream) {
   // 1024 groups stream the arrays at full rate and keep the per-group
   // maximum records (two loads, at most two atomics each) few
-  hipLaunchKernelGGL(k_fold, dim3(grid_for(V, 256, 1024)), dim3(256), 0, (hipStream_t)stream,
+  hipLaunchKernelGGL(k_fold, dim3(grid_for(V, 256, kFoldBlocks)), dim3(256), 0, (hipStream_t)stream,
                      tally, ncopies, more, nbatch, s1, s2, V, acc);
   return check_launch();
 }
