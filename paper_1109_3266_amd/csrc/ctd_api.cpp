@@ -1103,13 +1103,15 @@ static int launch_chunk(const LaunchCfg &cfg, uint64_t n) {
 //    of it on contended words (122 and 6.3 ms per 1e8).  Deferred and
 //    macro-cell steps are bound by instruction issue (head: 22.3 and 26.7 ms,
 //    14.2 and 19.2 ms per 1e8);
-//  - a deposit share (ctd_case::deposit_share) of kRecordShare or more: water
-//    0.65, the water box and cube 0.95, while bodies in air (0.3 and below,
-//    0.15-0.2 deposits per step) ran 3-20 % slower with records;
-//  - kRecordMin histories and kRecordPerVoxel per voxel or more in the launch:
-//    below, the chains' set-up and the tally's flush outweigh the atomics
-//    (water, 1.6e6 voxels: 3e6 histories 472 and 493 us, 1e7 1318 and 1038 us;
-//    cube: 1e5 203 and 265 us, 3e5 432 and 280 us);
+//  - enough histories for the chains' set-up and the tally's flush, against
+//    the voxels of all batches in the launch.  Phantoms that mostly deposit
+//    (ctd_case::deposit_share: water 0.65, the water cube 0.95): 3e6 and one
+//    per 4 voxels, or 3 per voxel (small tallies contend): water of 1.6e6
+//    voxels 0.63 and 0.52 ms at 3e6 histories, 0.40 and 0.41 at 1e6; ten
+//    batches of 4.7e6 voxels 1.86 and 1.70 ms at 1e7, 0.93 and 1.12 at 3e6;
+//    the cube 0.21 and 0.14 ms at 1e5.  Others (bodies in air, 0.3 and below):
+//    1e8 and 4 per voxel (2e8 histories 12.4 and 11.0 ms on 6e5 voxels, 13.4
+//    and 13.0 ms on 4.8e6; 1e7 1.35 and 1.51 ms);
 //  - tally mode 0 (modes 1 and 2 name another place for the deposits) without
 //    the event log, in a context that keeps the workspace;
 //  - at most kRecordBuckets buckets per case, so its cursors fit beside the
@@ -1118,11 +1120,13 @@ static int launch_chunk(const LaunchCfg &cfg, uint64_t n) {
 // best, 128 and more cost the cube 8 % and more: a bucket's open line stays in
 // L2 while a workgroup fills it), at most the 2^14 whose sums fill 128 KB of
 // LDS.
-constexpr uint64_t kRecordMin = 200000, kRecordPerVoxel = 3;
-constexpr double kRecordShare = 0.45;
+constexpr double kDenseShare = 0.45;
 constexpr int kRecordBuckets = 1024, kRecordMaxBits = 14;
-constexpr double kRecordsPerHistory = 5.0;   // room; deposits beyond it go to the tally
 constexpr size_t kRecordMaxBytes = (size_t)6 << 30;
+// Records to make room for per history, by the case's deposit share: water
+// 2.6, the pencil beam 4, bodies in air 0.7-1.3.  Deposits beyond it go to the
+// tally.
+static double record_room(double share) { return share >= kDenseShare ? 5.0 : 2.5; }
 
 static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, RoundCase *rc,
                          const LaunchCfg &cfg, int kind, bool with_log, DepositLog &dl,
@@ -1132,10 +1136,11 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
   int max_bits = kRecordMaxBits;
   while (max_bits > 0 && ((size_t)8 << max_bits) > (size_t)ctx->lds_per_block) --max_bits;
   uint64_t n = 0, voxels = 0;
+  double room = 0.0;
+  bool dense = true;
   uint32_t total = 0, most = 0;
   tile_voxels = 0;
   for (size_t i = 0; i < items.size(); ++i) {
-    if (items[i].deposit_share < kRecordShare) return false;
     int bits = 0;
     while (bits < max_bits && ((items[i].V - 1) >> bits) >= 64) ++bits;
     const uint64_t nb = (uint64_t)((items[i].V - 1) >> bits) + 1;
@@ -1148,15 +1153,20 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
     tile_voxels = std::max(tile_voxels, (int)std::min<int64_t>((int64_t)1 << bits, items[i].V));
     n += items[i].n;
     voxels += (uint64_t)items[i].V;
+    room += record_room(items[i].deposit_share) * (double)items[i].n;
+    dense = dense && items[i].deposit_share >= kDenseShare;
   }
-  if (n < kRecordMin || n < kRecordPerVoxel * voxels) return false;
+  const uint64_t least =
+      dense ? std::max<uint64_t>(100000, std::min(3 * voxels, std::max<uint64_t>(3000000, voxels / 4)))
+            : std::max<uint64_t>(100000000, 4 * voxels);
+  if (n < least) return false;
   // a cursor's 32-bit count holds every deposit its workgroup may add to it
   if (n / (uint64_t)cfg.grid >= ((uint64_t)1 << 28)) return false;
   dl.buckets = total;
   dl.cursors = (int32_t)((most + 1) & ~1u);
   if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors) > cfg.lds_budget) return false;
   const size_t seg_bytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
-  double want = kRecordsPerHistory * (double)n / ((double)cfg.grid * kLogSeg);
+  double want = room / ((double)cfg.grid * kLogSeg);
   want += (double)std::min(total, 2 * most);   // a part-filled segment per bucket
   size_t per_wg = (size_t)std::ceil(std::min(want, 1e9));
   const size_t heads = (size_t)cfg.grid * total;
@@ -1339,11 +1349,11 @@ static void harvest_timing(ctd_case *cs) {
 // histories on few lanes (about 0.2 ms) and starts with set-up, so batches are
 // gathered until the launch has kGroupHistories (3e7 / 1e8 / 3e8: the head with
 // macro cells 36.3 / 34.3 / 33.4 ms per 3e8, six uneven cases 63.2 / 63.4 /
-// 60.4 ms per 6e8; kGroupRecorded where deposit records may be kept, whose
-// workspace is bounded), within kGroupMaxBytes of tallies (and an eighth of the
+// 60.4 ms per 6e8; no more than the room for deposit records where they are
+// kept), within kGroupMaxBytes of tallies (and an eighth of the
 // free memory), and while the headroom bounds hold without a read-back.  Per-XCD tallies and the event log run a batch at
 // a time, as does a context without workspaces (a server's).
-constexpr uint64_t kGroupHistories = 300000000, kGroupRecorded = 100000000, kGroupRounds = 64;
+constexpr uint64_t kGroupHistories = 300000000, kGroupRounds = 64;
 constexpr size_t kGroupMaxBytes = (size_t)1 << 30;
 
 static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases, uint64_t r,
@@ -1355,7 +1365,9 @@ static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases,
   for (const ctd_case *cs : cases) {
     if (cs->log_cap > 0) return 1;
     voxels += (uint64_t)cs->ph->V;
-    if (cs->deposit_share >= kRecordShare) most = kGroupRecorded;
+    if (step_kind(cs, t) == kStepPlain)   // within the room for deposit records
+      most = std::min(most, (uint64_t)((double)kRecordMaxBytes /
+                                       (sizeof(uint2) * 1.2 * record_room(cs->deposit_share))));
   }
   std::vector<double> s1(cases.size()), s2(cases.size());
   for (size_t i = 0; i < cases.size(); ++i) {
