@@ -166,45 +166,30 @@ extern "C" int32_t ctd_set_stream(ctd_ctx *ctx, void *hip_stream) {
 
 // Piecewise-constant phantoms (at most 256 distinct (rho, material) records)
 // also get a 1-byte-per-voxel index into a 256-entry table: an 8x smaller
-// gather footprint for the same numbers.  Scanned in slices so a phantom
-// with many distinct densities is rejected after a few thousand voxels.
-static int build_palette(ctd_ctx *ctx, ctd_phantom *ph) {
-  const int64_t V = ph->V;
-  const int64_t slice = (int64_t)1 << 20;
-  std::vector<uint2> rec((size_t)std::min<int64_t>(V, slice));
-  std::vector<uint8_t> idx((size_t)V);
-  uint64_t keys[256];
-  int n = 0;
-  for (int64_t b = 0; b < V; b += slice) {
-    const int64_t m = std::min<int64_t>(slice, V - b);
-    HIPCHK(ctx, hipMemcpy(rec.data(), ph->vox + b, sizeof(uint2) * m, hipMemcpyDeviceToHost));
-    uint64_t last = ~0ull;
-    int last_i = -1;
-    for (int64_t i = 0; i < m; ++i) {
-      const uint64_t key = ((uint64_t)rec[i].y << 32) | rec[i].x;
-      int k = -1;
-      if (key == last) {
-        k = last_i;
-      } else {
-        for (int j = 0; j < n; ++j)
-          if (keys[j] == key) { k = j; break; }
-        if (k < 0) {
-          if (n == 256) return CTD_OK;  // too many distinct records: keep 8-byte layout
-          keys[n] = key;
-          k = n++;
-        }
-        last = key;
-        last_i = k;
-      }
-      idx[(size_t)(b + i)] = (uint8_t)k;
-    }
+// gather footprint for the same numbers.  The distinct records come from
+// k_pack's statistics, in ascending order.
+static int build_palette(ctd_ctx *ctx, ctd_phantom *ph, const unsigned int *stats) {
+  if (stats[kPackOver] != 0 || stats[kPackCount] > 256) return CTD_OK;  // keep 8-byte layout
+  std::vector<uint64_t> keys;
+  for (int i = 0; i < kPackSlots; ++i) {
+    uint64_t k;
+    std::memcpy(&k, stats + kPackKeys + 2 * i, 8);
+    if (k != ~0ull) keys.push_back(k);
   }
-  std::vector<uint2> pal(256, make_uint2(0u, 0u));
+  std::sort(keys.begin(), keys.end());
+  const int n = (int)keys.size();
+  // the palette with the keys behind it
+  std::vector<uint2> pal(512, make_uint2(0u, 0u));
   for (int j = 0; j < n; ++j) pal[j] = make_uint2((uint32_t)keys[j], (uint32_t)(keys[j] >> 32));
-  HIPCHK(ctx, hipMalloc(&ph->vox8, (size_t)V));
-  HIPCHK(ctx, hipMalloc(&ph->palette, sizeof(uint2) * 256));
-  HIPCHK(ctx, hipMemcpy(ph->vox8, idx.data(), (size_t)V, hipMemcpyHostToDevice));
-  HIPCHK(ctx, hipMemcpy(ph->palette, pal.data(), sizeof(uint2) * 256, hipMemcpyHostToDevice));
+  std::memcpy(pal.data() + 256, keys.data(), 8 * (size_t)n);
+  HIPCHK(ctx, hipMalloc(&ph->vox8, (size_t)ph->V));
+  HIPCHK(ctx, hipMalloc(&ph->palette, sizeof(uint2) * 512));
+  HIPCHK(ctx, hipMemcpyAsync(ph->palette, pal.data(), sizeof(uint2) * 512, hipMemcpyHostToDevice,
+                             ctx->stream));
+  if (launch_palette_index(ph->vox, ph->V, (const unsigned long long *)(ph->palette + 256), n,
+                           ph->vox8, ctx->stream) != 0)
+    return hip_err(ctx, hipGetLastError(), "palette kernel");
+  HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   ph->npal = n;
   return CTD_OK;
 }
@@ -309,25 +294,24 @@ extern "C" int32_t ctd_phantom_load(ctd_ctx *ctx, const ctd_grid *g, const uint8
     pm = dmat;
     pr = drho;
   }
-  if ((e = hipMemsetAsync(dstat, 0, sizeof(unsigned int) * kPackStats, ctx->stream)) != hipSuccess)
-    return fail(hip_err(ctx, e, "phantom stats clear"));
   if (launch_pack(pm, pr, ph->vox, V, dstat, ctx->stream) != 0)
     return fail(hip_err(ctx, hipGetLastError(), "pack kernel"));
   unsigned int hstat[kPackStats];
+  static_assert(kPackKeys % 2 == 0, "keys are 8-byte aligned");
   if ((e = hipMemcpyAsync(hstat, dstat, sizeof hstat, hipMemcpyDeviceToHost, ctx->stream)) !=
           hipSuccess ||
       (e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
     return fail(hip_err(ctx, e, "phantom stats readback"));
-  if (hstat[513] != 0) {
-    rc = set_err(ctx, CTD_EINVAL, "%u voxels with a negative or non-finite density", hstat[513]);
+  if (hstat[kPackBad] != 0) {
+    rc = set_err(ctx, CTD_EINVAL, "%u voxels with a negative or non-finite density", hstat[kPackBad]);
     return fail(rc);
   }
-  ph->max_mat = (int)hstat[512];
+  ph->max_mat = (int)hstat[kPackMat];
   for (int m = 0; m < 256; ++m) {
     float f;
     std::memcpy(&f, &hstat[m], 4);
     ph->rho_max[m] = (double)f;
-    const unsigned int mn = ~hstat[514 + m];
+    const unsigned int mn = ~hstat[kPackMin + m];
     std::memcpy(&f, &mn, 4);
     ph->rho_min[m] = hstat[256 + m] ? (double)f : 0.0;
     ph->present[m] = hstat[256 + m] != 0;
@@ -337,7 +321,7 @@ extern "C" int32_t ctd_phantom_load(ctd_ctx *ctx, const ctd_grid *g, const uint8
   dfree(drho);
   dmat = nullptr;
   drho = nullptr;
-  if ((rc = build_palette(ctx, ph)) != CTD_OK) return fail(rc);
+  if ((rc = build_palette(ctx, ph, hstat)) != CTD_OK) return fail(rc);
   if (ph->npal == 0 && (rc = build_bound_grids(ctx, ph)) != CTD_OK) return fail(rc);
   *out = ph;
   return CTD_OK;

@@ -84,7 +84,7 @@ struct ctd_phantom {
   int64_t V = 0;
   uint2 *vox = nullptr;   // packed (rho bits, material) records
   uint8_t *vox8 = nullptr;  // palette indices when npal > 0
-  uint2 *palette = nullptr; // [256] distinct records when npal > 0
+  uint2 *palette = nullptr; // [256] distinct records when npal > 0 (and as sorted keys)
   int npal = 0;
   // bound grids (8-byte record layout): block classes for blocks of 1, 2, 4
   // voxels per edge, the class table [256] (density level bits, material)

@@ -48,7 +48,14 @@ constexpr int kAccWords = (kAccDeposited + 2 * kFoldBlocks + 1) & ~1;
 constexpr float kQScale = 16777216.0f;  // 2^24: tally unit q = 2^-24 keV
 constexpr int kTallyCopies = 8;         // one batch tally per XCD of an MI355X
 constexpr int kMacroBands = 16;         // MACRO tracking: most energy bands
-constexpr int kPackStats = 770;         // words of k_pack's statistics
+// k_pack's statistics, 32-bit words: [0, 256) max density bits and [256, 512)
+// voxel count per material, [512] largest material id, [513] voxels with a bad
+// density, [514, 770) complemented min density bits per material, [770]
+// distinct records found, [771] not zero where there are too many; then
+// kPackSlots 64-bit keys (material << 32 | density bits, all ones: empty).
+constexpr int kPackMat = 512, kPackBad = 513, kPackMin = 514, kPackCount = 770, kPackOver = 771;
+constexpr int kPackKeys = 772, kPackSlots = 1024;
+constexpr int kPackStats = kPackKeys + 2 * kPackSlots;
 constexpr uint32_t kMixedClass = 255;   // bound grid: a block of several materials
 constexpr uint32_t kStepGuard = 1000000u;  // random pairs (MACRO: flights) a history may take
 constexpr float kInvMeC2 = (float)(1.0 / 510.99895);
@@ -252,11 +259,12 @@ int launch_fold(unsigned long long *tally, int ncopies, unsigned long long *more
                 void *stream);
 // Largest XCC id seen by `blocks` workgroups (written to *out, device).
 int launch_xcc_probe(unsigned int *out, int blocks, void *stream);
-// stats[kPackStats]: [0,256) max density bits per material, [256,512) voxel
-// count per material, [512] largest material id, [513] voxels with a bad
-// density, [514,770) complemented min density bits per material.
+// Clear stats[kPackStats], pack the voxels and fill the statistics.
 int launch_pack(const uint8_t *mat, const float *rho, uint2 *vox, int64_t V, unsigned int *stats,
                 void *stream);
+// out[v] = position of voxel v's record among the n ascending 64-bit keys.
+int launch_palette_index(const uint2 *vox, int64_t V, const unsigned long long *keys, int n,
+                         uint8_t *out, void *stream);
 int launch_zero(void *ptr, size_t bytes, void *stream);
 // Device address of this device's static round table (hipGetSymbolAddress
 // with the device current); 0 on success.
