@@ -227,13 +227,17 @@ typedef struct {
                             and so results, are those of 0, bit for bit. */
   int32_t defer_min;     /* With a bound grid: a tentative collision the
                             bound cannot reject waits, and the wave resolves
-                            its waiting collisions together once this many
-                            lanes hold one (or every live lane does), so the
-                            voxel reads and interaction code run with more
-                            lanes active; photons that leave the box add
-                            their counters at the wave's next refill.  0:
-                            every collision at once (1..64).  Each history's
-                            steps are unchanged: same results bit for bit. */
+                            its waiting collisions together, so the voxel
+                            reads and interaction code run with more lanes
+                            active: once 4 x defer_min (at most 68) of them
+                            are parked in LDS, or, where the LDS has no room
+                            to park them, once defer_min lanes hold one (or
+                            every live lane does); photons that leave the box
+                            add their counters at the wave's next refill.  0:
+                            none is parked, and they are resolved whenever
+                            the wave leaves its step loop (1..64).  Each
+                            history's steps are unchanged: same results bit
+                            for bit. */
 } ctd_tuning;
 
 /* Deposit/event record of the debug log (test use). type: 0 source, 1

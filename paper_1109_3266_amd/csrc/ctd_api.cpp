@@ -729,10 +729,28 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
   {
     const std::vector<float> bnd = bound_sums(ms, p->rayleigh != 0);
     cs->use_bound_grid = ph->nclass > 0 && bound_test_in_range(ph, bnd, eg.ne);
-    if ((e = hipMalloc(&cs->d_bnd, 4 * bnd.size())) != hipSuccess ||
-        (e = hipMemcpy(cs->d_bnd, bnd.data(), 4 * bnd.size(), hipMemcpyHostToDevice)) !=
-            hipSuccess)
+    // bnd, then the materials' shares and the coarse grid made from them
+    std::vector<float> up(bnd);
+    up.resize(bnd.size() + (size_t)ms->M);
+    bound_shares(bnd.data(), cs->mu_max.data(), ms->M, eg.ne, up.data() + bnd.size());
+    if ((e = hipMalloc(&cs->d_bnd, 4 * up.size() + kCoarseCells)) != hipSuccess ||
+        (e = hipMemcpy(cs->d_bnd, up.data(), 4 * up.size(), hipMemcpyHostToDevice)) != hipSuccess)
       return cleanup(hip_err(ctx, e, "bound-test sums"));
+    if (cs->use_bound_grid && cs->p.tracking != CTD_TRACK_MACRO) {
+      const ctd_grid &g = ph->g;
+      int s = 0;
+      const auto cells = [&] {
+        const int64_t e1 = ((int64_t)1 << s) - 1;
+        return ((g.nx + e1) >> s) * ((g.ny + e1) >> s) * ((g.nz + e1) >> s);
+      };
+      while (cells() > kCoarseCells) ++s;
+      cs->d_coarse = (uint8_t *)(cs->d_bnd + up.size());
+      cs->coarse_shift = s;
+      cs->n_coarse = (int)cells();
+      if (launch_coarse(ph->vox, g.nx, g.ny, g.nz, s, cs->d_bnd + bnd.size(), cs->d_coarse,
+                        ctx->stream) != 0)
+        return cleanup(hip_err(ctx, hipGetLastError(), "coarse bound grid"));
+    }
   }
   if (!geo->proj_sc.empty() &&
       (e = hipMalloc(&cs->d_proj, sizeof(float4) * geo->proj_sc.size())) != hipSuccess)
@@ -802,6 +820,9 @@ void ctd::fill_desc(ctd_case *cs) {
   for (int s = 0; s < 3; ++s) d.bgrid[s] = cs->ph->bgrid[s];
   d.bclass = cs->use_bound_grid ? cs->ph->bclass : nullptr;
   d.bnd = cs->d_bnd;
+  d.coarse = cs->d_coarse;
+  d.cshift = cs->coarse_shift;
+  d.ncoarse = cs->n_coarse;
   const ctd_matset *ms = cs->ms;
   d.ne = ms->eg.ne;
   d.nzc = ms->nzc;
@@ -1148,7 +1169,7 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
   if (n / (uint64_t)cfg.grid >= ((uint64_t)1 << 28)) return false;
   dl.buckets = total;
   dl.cursors = (int32_t)((most + 1) & ~1u);
-  if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors) > cfg.lds_budget) return false;
+  if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors, -1, 0) > cfg.lds_budget) return false;
   const size_t seg_bytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
   double want = room / ((double)cfg.grid * kLogSeg);
   want += (double)std::min(total, 2 * most);   // a part-filled segment per bucket

@@ -153,6 +153,8 @@ struct ctd_case {
   uint64_t mh_cap = 0;
   float *d_mc_f = nullptr;         // MACRO tracking: majorant factors [n_band][cells]
   float *d_bnd = nullptr;          // bound-test sums per material and energy cell
+  uint8_t *d_coarse = nullptr;     // coarse bound grid, in d_bnd's allocation
+  int coarse_shift = 0, n_coarse = 0;
   bool use_bound_grid = false;     // the phantom's bound grid serves this case
   int mc_cs = 0, mc_n[3] = {0, 0, 0}, mc_classes = 0, mc_shift = 0, mc_bands = 0;
   unsigned long long *d_tally = nullptr;

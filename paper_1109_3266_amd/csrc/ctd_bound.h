@@ -45,4 +45,35 @@ inline void bound_sums(const float *mu_rho, int M, int ne, bool rayleigh, float 
   }
 }
 
+// Coarse bound grid: rejection without the energy.  The share of a voxel is its
+// density times f[m], a float at or above material m's selection sum per unit
+// density over the majorant anywhere on the energy grid (bnd from bound_sums,
+// the majorant's nodes mu_max [ne]): the majorant interpolated in a cell is at
+// least the smaller of its ends (the top cell's reaching w = 1 + 4u ne), and
+// the margin of 2^-18 = 64u covers its float interpolation and the product
+// u1 * majorant of the selection.  Infinite where the majorant may vanish.
+inline void bound_shares(const float *bnd, const float *mu_max, int M, int ne, float *f) {
+  const double w_top = 1.0 + 4.0 * 0x1p-24 * ne;
+  for (int m = 0; m < M; ++m) {
+    double top = 0.0;
+    for (int j = 0; j + 1 < ne; ++j) {
+      const double m0 = mu_max[j], m1 = mu_max[j + 1];
+      const double end = j + 2 == ne ? m0 + w_top * (m1 - m0) : m1;
+      const double low = std::min(m0, std::min(m1, end)), b = bnd[(size_t)m * (ne - 1) + j];
+      top = std::max(top, b == 0.0 ? 0.0 : low > 0.0 ? b / low : INFINITY);
+    }
+    f[m] = round_up_float(top * (1.0 + 0x1p-18));
+  }
+}
+
+// The byte c of a cell from its voxels' largest share: share * 256 rounded
+// down, with a margin of 2^-20 for the float product rho * f.  A selection word
+// w1 whose top byte is above c has a uniform u1 >= (c + 1) / 256 > share, so
+// its collision is fictitious in every voxel of the cell; 255 rejects nothing.
+constexpr unsigned char coarse_byte(float share) {
+  const float x = share * (256.0f * (1.0f + 0x1p-20f));
+  return x < 255.0f ? (unsigned char)x : (unsigned char)255;
+}
+constexpr bool coarse_rejects(unsigned int w1, unsigned char c) { return (w1 >> 24) > c; }
+
 }  // namespace ctd

@@ -56,6 +56,7 @@ constexpr int kMacroBands = 16;         // MACRO tracking: most energy bands
 constexpr int kPackMat = 512, kPackBad = 513, kPackMin = 514, kPackCount = 770, kPackOver = 771;
 constexpr int kPackKeys = 772, kPackSlots = 1024;
 constexpr int kPackStats = kPackKeys + 2 * kPackSlots;
+constexpr int kCoarseCells = 2560;      // most cells (bytes) of the coarse bound grid
 constexpr uint32_t kMixedClass = 255;   // bound grid: a block of several materials
 constexpr uint32_t kStepGuard = 1000000u;  // random pairs (MACRO: flights) a history may take
 constexpr float kInvMeC2 = (float)(1.0 / 510.99895);
@@ -118,6 +119,12 @@ struct CaseDev {
   // selection forms anywhere in the cell, so rho_c * bnd bounds the selection
   // at class level rho_c without the table rows  [nmat][ne - 1]
   const float *bnd;
+  // Coarse bound grid, staged in the workgroups' LDS: per cell of 2^cshift
+  // voxels per edge (x fastest, ncoarse cells) a byte c such that a selection
+  // word whose top byte is above c is fictitious in every voxel of the cell at
+  // every energy.  Null where not built.
+  const uint8_t *coarse;
+  int32_t cshift, ncoarse;
   // random stream key
   uint32_t key0, key1;
   // tallies
@@ -217,7 +224,7 @@ struct LaunchCfg {
   int chunk;
   int tally_mode;
   int bound_shift;   // bound grid of 2^s-voxel blocks, or -1 (no early rejection)
-  int defer_min;     // with a bound grid: collision pass once this many wait (0: at once)
+  int defer_min;     // with a bound grid: when a collision pass is due (ctd_tuning)
   int tab_n, tab_ne; // the round's largest case: mu/rho rows and energy nodes to stage in LDS
   size_t lds_budget; // LDS a workgroup may take without lowering the residency
 };
@@ -247,9 +254,11 @@ bool transport_lds_fits(int block, int tally_mode, int device);
 // class table, per-wave counters, the tally-mode-2 sub-tallies, and room for
 // tab_n mu/rho rows, tab_ne majorant nodes and tab_n bound-test sums (0:
 // none), a source stash of stash_cap records per wave, and `cursors` words of
-// deposit-record cursors.
+// deposit-record cursors; park_cap >= 0 (deferred launches without the event
+// log): park_cap parked photons per wave, coarse_cap bytes of coarse bound grid
+// and no mu/rho rows.
 size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap,
-                           int cursors);
+                           int cursors, int park_cap, int coarse_cap);
 // Fold nbatch batches in order, the first from its ncopies tallies
 // tally[ncopies][V], the others from more[nbatch - 1][V]: S1 += T, S2 += T^2,
 // zero them; fold the counters of acc into its 128-bit totals and record the
@@ -301,6 +310,11 @@ int launch_cell_max(const uint2 *vox, int nx, int ny, int nz, int cs, int ncx, i
 // class of material m, level count), levels ascending within a material.
 int launch_block_class(const uint2 *vox, int nx, int ny, int nz, int shift, const uint2 *cls,
                        const int2 *range, uint8_t *out, void *stream);
+// Coarse bound grid of cells of 2^shift voxels per edge (CaseDev::coarse): f[m]
+// is at or above material m's largest interaction sum per density over the
+// majorant.
+int launch_coarse(const uint2 *vox, int nx, int ny, int nz, int shift, const float *f,
+                  uint8_t *out, void *stream);
 int launch_mh_fill(const float *f, int n_f, int C, uint64_t h_begin, uint64_t n, uint32_t key0,
                    uint32_t key1, int32_t *state, int32_t *out, void *stream);
 // Gamma search lattice (ctd_gamma.hip): offsets i, j, k of -L .. L lattice

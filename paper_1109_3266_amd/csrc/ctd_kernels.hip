@@ -32,6 +32,7 @@
 // (0, c, 0, 2) the starting beamlet of Metropolis-Hastings chain c.
 #include <hip/hip_runtime.h>
 
+#include "ctd_bound.h"
 #include "ctd_internal.h"
 
 namespace ctd {
@@ -58,15 +59,19 @@ constexpr int kCacheBytesPerWave = kCacheSlots * (8 + 4);
 // Dynamic LDS of a transport workgroup, in this order: a 16-byte header
 // (the workgroup's next case); the descriptor of the case the workgroup works
 // on and its 256-entry palette or bound-class table (every wave of a
-// workgroup works on the same case); per wave, its event counters and an
-// 8-byte word per lane (what a lane's waiting collision or scatter needs
+// workgroup works on the same case); deferred kind without the event log, the
+// case's coarse bound grid (coarse_cap bytes); per wave, its event counters and
+// (other kinds) an 8-byte word per lane (what a lane's waiting scatter needs
 // later); in tally mode 2, each wave's sub-tally; per wave, its source
 // stash of stash_cap records (stash_cap entry points and energies as float4,
 // then stash_cap directions as float4, w = the record's history offset);
-// where the tables fit, the case's majorant nodes (padded to 16 B) and mu/rho
-// rows.
+// with the coarse grid, per wave, its parked photons (three planes of park_cap
+// float4); where the tables fit, the case's majorant nodes (padded to 16 B),
+// mu/rho rows (not with the coarse grid: there only collision passes read them)
+// and bound-test sums.
 constexpr int kWaveAccBytes = (ACC_COUNT * 8 + 15) & ~15;
 constexpr int kStashRecBytes = 32;
+constexpr int kParkRecBytes = 48;
 constexpr int kWaveSlotBytes = kWaveAccBytes + 64 * 8;
 constexpr int kWaveCaseBytes = ((int)sizeof(CaseDev) + 15) & ~15;
 constexpr int kWgHeaderBytes = 16;
@@ -171,6 +176,8 @@ struct StepCase {
   // blocks per axis); null: every tentative collision reads its voxel
   const GLOBAL uint8_t *bgrid;
   int32_t bshift;
+  // coarse bound grid (in LDS; deferred kind): cell edge
+  int32_t cshift;
   uint32_t key0, key1;
 };
 
@@ -199,7 +206,7 @@ __device__ __forceinline__ int32_t uniform_i(int32_t x) {
 // bound_shift: the bound grid used (-1: none).
 __device__ __forceinline__ StepCase make_step_case(const CaseDev &c, unsigned long long *tally,
                                                    int tally_mode, int bound_shift,
-                                                   LOCAL unsigned char *cache) {
+                                                   int coarse_cap, LOCAL unsigned char *cache) {
   StepCase s;
   s.cur = nullptr;
   s.seg_next = nullptr;
@@ -208,6 +215,7 @@ __device__ __forceinline__ StepCase make_step_case(const CaseDev &c, unsigned lo
   s.bbits = 0;
   s.bgrid = nullptr;
   s.bshift = 0;
+  s.cshift = c.coarse && uniform_i(c.ncoarse) <= coarse_cap ? uniform_i(c.cshift) : 31;
   if (bound_shift >= 0 && c.bclass) {
     s.bgrid = uniform_ptr(c.bgrid[bound_shift]);
     s.bshift = bound_shift;
@@ -397,12 +405,12 @@ __device__ __forceinline__ void table_rows(const StepCase &S, uint32_t ti, float
   }
 }
 
-// Bound-test sum of material m in energy cell j (CaseDev::bnd).
+// Bound-test sum in energy cell j (CaseDev::bnd) of the material whose row is
+// the staged class's: an LDS address (TAB) or an index.
 template <bool TAB>
-__device__ __forceinline__ float bound_sum(const StepCase &S, uint32_t m, int j) {
-  const uint32_t i = __umul24(m, (uint32_t)(S.ne - 1)) + (uint32_t)j;
-  if constexpr (TAB) return S.tabbnd[i];
-  else return S.bnd[i];
+__device__ __forceinline__ float bound_sum(const StepCase &S, uint32_t row, int j) {
+  if constexpr (TAB) return *(const LOCAL float *)(uintptr_t)(row + 4u * (uint32_t)j);
+  else return S.bnd[row + (uint32_t)j];
 }
 
 template <bool TAB>
@@ -651,6 +659,22 @@ __device__ __forceinline__ int select_process(Photon &p, const StepCase &S, cons
   return kSelFict;
 }
 
+// Selection in voxel vox of density bits rbits and material m against majorant
+// mumax with selection word ry.
+template <int OUT, bool TAB>
+__device__ __forceinline__ int select_in(Photon &p, const StepCase &S, const CaseDev &G,
+                                         Counters &c, int32_t vox, uint32_t rbits, uint32_t m,
+                                         uint32_t ry, float mumax) {
+  const uint32_t ti = __umul24(m, (uint32_t)S.ne) + (uint32_t)p.je;
+  float4 t0, t1;
+  table_rows<TAB>(S, ti, t0, t1);
+  const float a = lerpf(t0.x, t1.x, p.we), b = lerpf(t0.y, t1.y, p.we);
+  // (the staged rows hold 0 for Rayleigh where the case has none)
+  const float cr = TAB || S.rayleigh ? lerpf(t0.z, t1.z, p.we) : 0.0f;
+  return select_process<OUT, TAB>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
+                             unif(ry) * mumax);
+}
+
 // Tentative collision at voxel vox against majorant mumax with selection
 // word ry: read the voxel (1-byte palette index or 8-byte record) and its
 // table rows, then select; m receives the voxel's material.
@@ -670,14 +694,7 @@ __device__ __forceinline__ int select_at(Photon &p, const StepCase &S, const Cas
     rbits = rec.x;
     m = rec.y;
   }
-  const uint32_t ti = __umul24(m, (uint32_t)S.ne) + (uint32_t)p.je;
-  float4 t0, t1;
-  table_rows<TAB>(S, ti, t0, t1);
-  const float a = lerpf(t0.x, t1.x, p.we), b = lerpf(t0.y, t1.y, p.we);
-  // (the staged rows hold 0 for Rayleigh where the case has none)
-  const float cr = TAB || S.rayleigh ? lerpf(t0.z, t1.z, p.we) : 0.0f;
-  return select_process<OUT, TAB>(p, S, G, c, vox, __uint_as_float(rbits), a, b, cr,
-                             unif(ry) * mumax);
+  return select_in<OUT, TAB>(p, S, G, c, vox, rbits, m, ry, mumax);
 }
 
 // Compton (sel = kSelCompton, Sec. 2.2.3) or Rayleigh (Sec. 2.2.2) scatter in
@@ -727,6 +744,12 @@ __device__ __forceinline__ bool inside_box(const Photon &p, const StepCase &S) {
   return (__float_as_uint(p.px) < __float_as_uint(S.fnx)) &
          (__float_as_uint(p.py) < __float_as_uint(S.fny)) &
          (__float_as_uint(p.pz) < __float_as_uint(S.fnz));
+}
+
+// Voxel of a position inside the box.
+__device__ __forceinline__ int32_t voxel_at(const Photon &p, const StepCase &S) {
+  return (int32_t)__umul24(__umul24((uint32_t)p.pz, (uint32_t)S.ny) + (uint32_t)p.py,
+                           (uint32_t)S.nx) + (int32_t)(uint32_t)p.px;
 }
 
 // Step guard of the global-majorant steps, checked once per block: a photon
@@ -786,47 +809,47 @@ __device__ __forceinline__ int step(Photon &p, const StepCase &S, const CaseDev 
 
 // One Woodcock step with deferred collisions (bound grid present), words w0
 // (free path) and w1 (selection): the fast part of step() -- free path,
-// move, exit test and the bound-grid rejection of fictitious collisions --
-// for every live lane of the wave, leaving the rest to the wave's next
-// collision pass.  Returns kStepOn (fictitious, decided by the bound),
-// kStepPending (a tentative collision at *pvox that needs the voxel; w1 is
-// kept in the lane's LDS word *u1 for the pass, which reads the voxel and
-// selects as step() does) or kStepGone (left the box: kGoneBit set, its
-// counters added at the next refill step).  The caller applies the step
-// guard, once per block.
-constexpr int kStepOn = 0, kStepPending = 1, kStepGone = 2;
+// move, exit test and the rejection of fictitious collisions by the bound
+// grids -- leaving the rest to the wave's next collision pass.  halt stays
+// kGoing after a fictitious collision; kWaiting: a tentative collision that
+// needs its voxel, w1 kept in u1 for the pass, which selects as step() does;
+// kGone: left the box.  The caller applies the step guard, once per block.
+// The coarse grid in LDS comes first: a byte per cell, no energy, and most of
+// the air and half of the soft tissue's collisions are decided there; only the
+// rest read the bound grid, a random byte of 1.3 MB that L1 hardly holds.
+constexpr uint32_t kGoing = 0, kWaiting = 1, kGone = 2, kStopped = 3;
 
 template <int OUT, bool TAB>
-__device__ __forceinline__ int step_fast(Photon &p, const StepCase &S, const LOCAL uint2 *cls_tab,
-                                         const GLOBAL uint8_t *bgrid, int32_t &pvox,
-                                         LOCAL uint32_t *u1, uint32_t w0, uint32_t w1) {
+__device__ __forceinline__ void step_fast(Photon &p, const StepCase &S, const LOCAL uint2 *cls_tab,
+                                          const LOCAL uint8_t *coarse,
+                                          const GLOBAL uint8_t *bgrid, uint32_t &u1,
+                                          uint32_t &halt, uint32_t w0, uint32_t w1) {
   p.k += 1;
   if (OUT == kOutEvents) p.ks += 1;
   const float s = -__log2f(unif(w0)) * p.sc;  // -ln(u) / mu_max
   p.px = fmaf(s, p.ux * S.inv_dx, p.px);
   p.py = fmaf(s, p.uy * S.inv_dy, p.py);
   p.pz = fmaf(s, p.uz * S.inv_dz, p.pz);
-  const bool inside = inside_box(p, S);
-  if (!inside) {
-    p.k |= kGoneBit | kEndBit;
-    return kStepGone;
+  if (!inside_box(p, S)) {
+    halt = kGone;
+    return;
   }
   const uint32_t ix = (uint32_t)p.px, iy = (uint32_t)p.py, iz = (uint32_t)p.pz;
-  const int32_t vox = (int32_t)__umul24(__umul24(iz, (uint32_t)S.ny) + iy, (uint32_t)S.nx) +
-                      (int32_t)ix;
+  if constexpr (OUT == kOutTally) {
+    const uint32_t ce = (1u << S.cshift) - 1u;
+    const uint32_t cnx = ((uint32_t)S.nx + ce) >> S.cshift, cny = ((uint32_t)S.ny + ce) >> S.cshift;
+    const uint32_t cell = __umul24(__umul24(iz >> S.cshift, cny) + (iy >> S.cshift), cnx) +
+                          (ix >> S.cshift);
+    if ((w1 >> 24) > coarse[cell]) return;
+  }
   const uint32_t e = (1u << S.bshift) - 1u;
   const uint32_t bgx = ((uint32_t)S.nx + e) >> S.bshift, bgy = ((uint32_t)S.ny + e) >> S.bshift;
   const uint32_t blk = __umul24(__umul24(iz >> S.bshift, bgy) + (iy >> S.bshift), bgx) +
                        (ix >> S.bshift);
-  const uint32_t cls = bgrid[blk];
-  if (cls != kMixedClass) {
-    const uint2 ce = cls_tab[cls];
-    const float rho_c = __uint_as_float(ce.x);
-    if (unif(w1) * p.mumax >= rho_c * bound_sum<TAB>(S, ce.y, p.je)) return kStepOn;
-  }
-  pvox = vox;
-  *u1 = w1;
-  return kStepPending;
+  const uint2 ce = cls_tab[bgrid[blk]];
+  if (unif(w1) * p.mumax >= __uint_as_float(ce.x) * bound_sum<TAB>(S, ce.y, p.je)) return;
+  u1 = w1;
+  halt = kWaiting;
 }
 
 // Woodcock tracking with the macro-cell majorant (MACRO tracking).  A flight
@@ -946,6 +969,27 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
   return scatter<OUT, TAB>(p, S, G, c, sel, vox, m, p.rz, p.rw);
 }
 
+// Parked photons (deferred kind).  A lane whose collision waits gives its photon
+// to the wave's store in LDS and takes another one, so nearly every lane steps
+// until pass_min collisions have gathered; then every lane swaps what it holds
+// for a waiting photon, the pass runs on a full wave, and the photons swapped
+// out are handed to the lanes that next fall idle.  Bound by instruction issue:
+// before, 45 of 64 lanes stepped (the others waited or were idle) and a pass
+// had 17; now 56 and 63.  With fewer wave-level steps the L2 became the limit
+// (96 % of its cycles on random bytes of the bound grid), which the coarse grid
+// below relieves.  Head, 1e9 histories: 124.8 ms without both, 122.8 parked
+// only, 102.5 with the coarse grid, 88.4 with the states of a lane in one
+// register (halt), staged row addresses and passes of 64.
+// Three planes of cap 16-byte words per wave; what set_energy derives from the
+// energy is derived again.
+__device__ __forceinline__ void park(const Photon &p, LOCAL float4 *pl, uint32_t cap, uint32_t i,
+                                     uint32_t u1) {
+  pl[i] = make_float4(p.px, p.py, p.pz, p.E);
+  pl[cap + i] = make_float4(p.ux, p.uy, p.uz, __uint_as_float(u1));
+  pl[2 * cap + i] = make_float4(__uint_as_float(p.hlo), __uint_as_float(p.hhi),
+                                __uint_as_float(p.k), 0.0f);
+}
+
 // ------------------------------------------------------- transport kernel
 
 __device__ __forceinline__ int find_bin(const unsigned long long *__restrict__ prefix, int nbins,
@@ -981,7 +1025,8 @@ static_assert(sizeof(CaseDev) % 4 == 0 && sizeof(CaseDev) <= 512, "CaseDev copy 
 // Copy a case descriptor (and its voxel palette, or else its bound-grid class
 // table, if any) into the workgroup's LDS (threads copy words; the caller's
 // barrier publishes them).
-__device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseDev *src) {
+__device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseDev *src,
+                                           uint32_t bnd0, uint32_t bnd_step) {
   const uint32_t *s = reinterpret_cast<const uint32_t *>(src);
   uint32_t *d = reinterpret_cast<uint32_t *>(dst);
   for (int i = threadIdx.x; i < (int)(sizeof(CaseDev) / 4); i += blockDim.x) d[i] = s[i];
@@ -990,7 +1035,9 @@ __device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseD
   if (__builtin_amdgcn_readfirstlane(src->npal) > 0)
     for (int i = threadIdx.x; i < 256; i += blockDim.x) pal[i] = sp[i];
   else if (sc)
-    for (int i = threadIdx.x; i < 256; i += blockDim.x) pal[i] = sc[i];
+    for (int i = threadIdx.x; i < 256; i += blockDim.x)
+      pal[i] = i == (int)kMixedClass ? make_uint2(__float_as_uint(INFINITY), bnd0)
+                                     : make_uint2(sc[i].x, bnd0 + __umul24(sc[i].y, bnd_step));
 }
 
 // KIND selects the step for every case of the launch (kStepPlain,
@@ -1007,7 +1054,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
                                                    unsigned long long *chunk_ctr, int refill_min,
                                                    int chunk, int tally_mode, int bound_shift,
                                                    int defer_min, int tab_n, int tab_ne,
-                                                   int stash_cap, DepositLog dl) {
+                                                   int stash_cap, int park_cap, int coarse_cap,
+                                                   DepositLog dl) {
   extern __shared__ unsigned long long dyn_lds[];   // layout: see kWgSlotsOff
   const int lane = __lane_id();
   const int w = threadIdx.x >> 6;
@@ -1018,8 +1066,13 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   CaseDev &G = *(CaseDev *)(base + kWgCaseOff);
   uint2 *pal = (uint2 *)(base + kWgPalOff);
   const LOCAL uint2 *pal_lds = (const LOCAL uint2 *)pal;
-  unsigned char *slot = base + kWgSlotsOff + w * kWaveSlotBytes;
-  unsigned char *after_slots = base + kWgSlotsOff + nw * kWaveSlotBytes;
+  constexpr bool kDefer = KIND == kStepDeferred;
+  constexpr bool kPark = kDefer && OUT == kOutTally;
+  const int slots_off = kWgSlotsOff + (kPark ? coarse_cap : 0);
+  constexpr int kSlotBytes = kDefer ? kWaveAccBytes : kWaveSlotBytes;
+  LOCAL uint8_t *coarse = (LOCAL uint8_t *)(base + kWgSlotsOff);
+  unsigned char *slot = base + slots_off + w * kSlotBytes;
+  unsigned char *after_slots = base + slots_off + nw * kSlotBytes;
   LOCAL uint2 *lane_word = (LOCAL uint2 *)(slot + kWaveAccBytes) + lane;
   // staged tables: the majorant nodes and mu/rho rows of the workgroup's
   // current case and its bound-test sums, shared by its waves (room for the
@@ -1034,6 +1087,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   // workgroup's segments) and the cursors behind the stash
   LOCAL uint32_t *seg_next = (LOCAL uint32_t *)(base + 4);
   unsigned char *after_stash = after_cache + nw * stash_cap * kStashRecBytes;
+  LOCAL float4 *pl = (LOCAL float4 *)after_stash + w * 3 * park_cap;
+  if constexpr (kPark) after_stash += nw * park_cap * kParkRecBytes;
   LOCAL unsigned long long *cur = (LOCAL unsigned long long *)after_stash;
   if constexpr (OUT == kOutRecords) {
     after_stash += (size_t)dl.cursors * 8;
@@ -1045,7 +1100,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   if (TAB) {
     tabmax = (LOCAL float *)after_stash;
     tab = (LOCAL float4 *)(tabmax + ((tab_ne + 3) & ~3));
-    tabbnd = (LOCAL float *)(tab + tab_n);
+    tabbnd = (LOCAL float *)(tab + (kPark ? 0 : tab_n));
   }
 
   Counters cnt;
@@ -1078,7 +1133,14 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   Photon p;
   p.k = 0;
   bool alive = false;
-  int32_t pvox = -1;   // deferred collisions: voxel of the lane's pending collision
+  // deferred collisions: whether the lane's photon waits for a pass, and its
+  // selection word; the wave's parked photons, n_wait that wait in [0, n_wait)
+  // and n_on that go on in [park_cap - n_on, park_cap)
+  bool wait = false;
+  uint32_t u1 = 0, n_wait = 0, n_on = 0;
+  const uint32_t pass_min = kPark && park_cap > 0
+                                ? min((uint32_t)park_cap - 4u, 4u * (uint32_t)defer_min)
+                                : (uint32_t)max(defer_min, 1);
   for (;;) {
     if (TAB) {
       const CaseDev *cd = rcs[c].cd;
@@ -1086,17 +1148,29 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       const float4 *src = cd->mu_rho;
       const float *srcm = cd->mu_max;
       const bool rayl = cd->rayleigh != 0;
-      for (int i = threadIdx.x; i < n_rows; i += blockDim.x) {
-        float4 r = src[i];
-        if (!rayl) r.z = 0.0f;
-        tab[i] = r;
+      if constexpr (!kPark) {
+        for (int i = threadIdx.x; i < n_rows; i += blockDim.x) {
+          float4 r = src[i];
+          if (!rayl) r.z = 0.0f;
+          tab[i] = r;
+        }
       }
       for (int i = threadIdx.x; i < n_e; i += blockDim.x) tabmax[i] = srcm[i];
       const float *srcb = cd->bnd;
       const int n_b = cd->nmat * (n_e - 1);
       for (int i = threadIdx.x; i < n_b; i += blockDim.x) tabbnd[i] = srcb[i];
     }
-    stage_case(&G, pal, rcs[c].cd);
+    const uint32_t cells = (uint32_t)rcs[c].cd->ne - 1u;
+    if (TAB) stage_case(&G, pal, rcs[c].cd, (uint32_t)(uintptr_t)tabbnd, 4u * cells);
+    else stage_case(&G, pal, rcs[c].cd, 0u, cells);
+    if constexpr (kPark) {
+      // (without a grid, or room for it: one cell that rejects nothing)
+      const CaseDev *cd = rcs[c].cd;
+      const uint32_t *src = cd->ncoarse <= coarse_cap ? (const uint32_t *)cd->coarse : nullptr;
+      const int nw4 = src ? (cd->ncoarse + 3) / 4 : 1;
+      for (int i = threadIdx.x; i < nw4; i += blockDim.x)
+        ((LOCAL uint32_t *)coarse)[i] = src ? src[i] : 255u;
+    }
     if constexpr (OUT == kOutRecords) {
       const int nb = (int)rcs[c].buckets;
       for (int i = threadIdx.x; i < nb; i += blockDim.x) cur[i] = (unsigned long long)kLogSeg;
@@ -1112,9 +1186,18 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
     for (;;) {
       const unsigned long long dead = __ballot(!alive);
       const int ndead = __popcll(dead);
-      if (ndead == 64 || ndead >= refill_min) {
-        // counters of the histories that ended since the last refill step
+      // deferred kind: a pass comes first where enough collisions wait (it
+      // takes the idle lanes), otherwise every idle lane gets a photon
+      bool due = false, hand_out = ndead == 64 || ndead >= refill_min;
+      if constexpr (kDefer) {
+        due = n_wait + (uint32_t)__popcll(__ballot(alive && wait)) >= pass_min;
         if (!alive && (p.k & kEndBit)) count_ended<OUT>(p, G, cnt);
+        hand_out = dead != 0ull && !due;
+      }
+      if (hand_out) {
+        // counters of the histories that ended since the last refill step
+        if constexpr (!kDefer)
+          if (!alive && (p.k & kEndBit)) count_ended<OUT>(p, G, cnt);
         // idle lanes take the stash's records in order, lowest lanes first;
         // an empty stash is refilled from the pool (a chunk of case c is
         // claimed when the pool is empty) with the sources of the pool's
@@ -1122,7 +1205,26 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         const bool want = !alive;
         const uint32_t rank = (uint32_t)__popcll(dead & lt_mask);
         uint32_t filled = 0;
+        if constexpr (kPark) {
+          if (n_on) {
+            filled = min((uint32_t)ndead, n_on);
+            if (want && rank < filled) {
+              const uint32_t i = (uint32_t)park_cap - n_on + rank;
+              const float4 a = pl[i], b = pl[park_cap + i], d = pl[2 * park_cap + i];
+              p.px = a.x; p.py = a.y; p.pz = a.z;
+              p.ux = b.x; p.uy = b.y; p.uz = b.z;
+              p.hlo = __float_as_uint(d.x);
+              p.hhi = __float_as_uint(d.y);
+              p.k = __float_as_uint(d.z);
+              set_energy<TAB>(p, S, a.w);
+              alive = true;
+            }
+            n_on -= filled;
+          }
+        }
         for (;;) {
+          if constexpr (kPark)
+            if (filled == (uint32_t)ndead) break;
           if (st_pos < st_n) {
             const uint32_t take = min((uint32_t)ndead - filled, st_n - st_pos);
             if (want && rank >= filled && rank < filled + take) {
@@ -1163,7 +1265,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
             // the wave's step constants at its first chunk; a wave's claims
             // of one case increase, so later bin searches start from the last
             if (first) {
-              S = make_step_case(G, rcs[c].tally, tally_mode, bound_shift, cache);
+              S = make_step_case(G, rcs[c].tally, tally_mode, bound_shift, coarse_cap, cache);
               if constexpr (OUT == kOutRecords) {
                 S.cur = cur;
                 S.seg_next = seg_next;
@@ -1214,7 +1316,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         }
         if (filled > 0) refills += 1;
       }
-      if (__ballot(alive) == 0ull) {
+      if (__ballot(alive) == 0ull && (!kPark || n_wait == 0)) {
         // case c done for this wave
         if (claims_done && pool_next >= pool_end && st_pos >= st_n) break;
         continue;
@@ -1224,49 +1326,117 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
         // spills more than it saves
         if (alive) alive = step_macro<OUT, TAB>(p, S, G, pal_lds, cnt);
       } else if constexpr (KIND == kStepDeferred) {
-        // collision pass: the pending tentative collisions of the wave, once
-        // defer_min of them have gathered (or every live lane waits on one)
-        const unsigned long long pm = __ballot(alive && pvox >= 0);
-        if (pm && (__popcll(pm) >= defer_min || pm == __ballot(alive))) {
-          if (alive && pvox >= 0) {
-            // the step's selection word waited in the lane's LDS word
+        const unsigned long long on = __ballot(alive && !wait);
+        if (due || on == 0ull) {
+          // collision pass: the waiting collisions of the wave, once pass_min
+          // have gathered or nothing else is left to do
+          // the waiting photons' voxel records, asked for as early as possible
+          uint2 rec = make_uint2(0u, 0u);
+          if (alive && wait) rec = S.vox[voxel_at(p, S)];
+          if constexpr (kPark) {
+            if (n_wait) {
+              // lanes without a waiting collision take the parked ones, idle
+              // lanes first; the others park the photon they held
+              const unsigned long long idle = __ballot(!alive);
+              const uint32_t n_idle = (uint32_t)__popcll(idle);
+              const uint32_t n_take = min(n_wait, n_idle + (uint32_t)__popcll(on));
+              const uint32_t r = alive ? n_idle + (uint32_t)__popcll(on & lt_mask)
+                                       : (uint32_t)__popcll(idle & lt_mask);
+              const bool take = !(alive && wait) && r < n_take;
+              const bool keep = take && alive;
+              const uint32_t in = n_wait - 1u - r;
+              const uint32_t out = (uint32_t)park_cap - n_on - 1u - (r - n_idle);
+              float4 a;
+              __builtin_amdgcn_wave_barrier();
+              if (take) a = pl[in];
+              __builtin_amdgcn_wave_barrier();
+              if (keep) pl[out] = make_float4(p.px, p.py, p.pz, p.E);
+              if (take) {
+                p.px = a.x; p.py = a.y; p.pz = a.z;
+                rec = S.vox[voxel_at(p, S)];
+                set_energy<TAB>(p, S, a.w);
+                a = pl[park_cap + in];
+              }
+              __builtin_amdgcn_wave_barrier();
+              if (keep) pl[park_cap + out] = make_float4(p.ux, p.uy, p.uz, 0.0f);
+              if (take) {
+                p.ux = a.x; p.uy = a.y; p.uz = a.z;
+                u1 = __float_as_uint(a.w);
+                a = pl[2 * park_cap + in];
+              }
+              __builtin_amdgcn_wave_barrier();
+              if (keep)
+                pl[2 * park_cap + out] = make_float4(__uint_as_float(p.hlo), __uint_as_float(p.hhi),
+                                                     __uint_as_float(p.k), 0.0f);
+              if (take) {
+                p.hlo = __float_as_uint(a.x);
+                p.hhi = __float_as_uint(a.y);
+                p.k = __float_as_uint(a.z);
+                alive = true;
+                wait = true;
+              }
+              __builtin_amdgcn_wave_barrier();
+              n_wait -= n_take;
+              n_on += n_take > n_idle ? n_take - n_idle : 0u;
+            }
+          }
+          if (alive && wait) {
             const uint32_t P = p.k & kStepMask;
             uint32_t m;
-            // (a bound grid comes with the 8-byte records only)
-            const int sel = select_at<OUT, TAB, kVoxRecord>(p, S, G, pal_lds, cnt, pvox,
-                                                            lane_word->y, p.mumax, m);
+            const int32_t vox = voxel_at(p, S);
+            const int sel = select_in<OUT, TAB && !kPark>(p, S, G, cnt, vox, rec.x, rec.y, u1,
+                                                          p.mumax);
+            m = rec.y;
             if (sel == kSelPhoto) {
               alive = false;
             } else if (sel != kSelFict) {   // the scatter takes the next pair
               const uint4 q = pair_block<OUT>(p, S, P);
               const bool odd = (P & 1u) != 0u;
               p.k += 1;
-              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, pvox, m, odd ? q.z : q.x,
+              alive = scatter<OUT, TAB>(p, S, G, cnt, sel, vox, m, odd ? q.z : q.x,
                                               odd ? q.w : q.y);
             }
-            pvox = -1;
           }
+          wait = false;
+          continue;
         }
-        // fast steps until a refill or a collision pass is due: a tight
-        // loop in which a photon's direction, energy and tables stay put;
+        // fast steps until refill_min more lanes have stopped (or every lane): a
+        // tight loop in which a photon's direction, energy and tables stay put;
         // one block serves two steps (a photon at an odd pair takes one)
+        const int quit = max(__popcll(on) - refill_min, 0);
+        // the bound grid's address in scalar registers
+        const GLOBAL uint8_t *bg = uniform_ptr(S.bgrid);
+        uint32_t halt = alive && !wait ? kGoing : ~0u;
         for (;;) {
-          if (alive && pvox < 0 && (alive = guard_ok(p, cnt))) {
-            const uint32_t P = p.k & kStepMask;
-            const uint4 r = pair_block<OUT>(p, S, P);
-            LOCAL uint32_t *u1 = &lane_word->y;
-            // the bound grid's address into scalar registers once per block
-            // (held in vector registers, it was re-read before every step)
-            const GLOBAL uint8_t *bg = uniform_ptr(S.bgrid);
-            int st = kStepOn;
-            if ((P & 1u) == 0u) st = step_fast<OUT, TAB>(p, S, pal_lds, bg, pvox, u1, r.x, r.y);
-            if (st == kStepOn) st = step_fast<OUT, TAB>(p, S, pal_lds, bg, pvox, u1, r.z, r.w);
-            alive = st <= kStepPending;
+          if (halt == kGoing) {
+            if (!guard_ok(p, cnt)) {
+              halt = kStopped;
+            } else {
+              const uint32_t P = p.k & kStepMask;
+              const uint4 r = pair_block<OUT>(p, S, P);
+              if ((P & 1u) == 0u)
+                step_fast<OUT, TAB>(p, S, pal_lds, coarse, bg, u1, halt, r.x, r.y);
+              if (halt == kGoing)
+                step_fast<OUT, TAB>(p, S, pal_lds, coarse, bg, u1, halt, r.z, r.w);
+            }
           }
-          const unsigned long long al = __ballot(alive);
-          if (64 - __popcll(al) >= refill_min) break;
-          const unsigned long long pw = __ballot(alive && pvox >= 0);
-          if (pw && (__popcll(pw) >= defer_min || pw == al)) break;
+          if (__popcll(__ballot(halt == kGoing)) <= quit) break;
+        }
+        if (halt == kWaiting) wait = true;
+        if (halt == kGone || halt == kStopped) alive = false;
+        if (halt == kGone) p.k |= kGoneBit | kEndBit;
+        if constexpr (kPark) {   // park what waits, as far as there is room
+          const unsigned long long pm = __ballot(alive && wait);
+          const uint32_t room = (uint32_t)park_cap - n_wait - n_on;
+          const uint32_t r = (uint32_t)__popcll(pm & lt_mask);
+          __builtin_amdgcn_wave_barrier();
+          if (alive && wait && r < room) {
+            park(p, pl, (uint32_t)park_cap, n_wait + r, u1);
+            alive = false;
+            wait = false;
+          }
+          __builtin_amdgcn_wave_barrier();
+          n_wait += min((uint32_t)__popcll(pm), room);
         }
       } else {
         // steps until a refill is due, one block per pass of the loop: its
@@ -1442,6 +1612,34 @@ __global__ void __launch_bounds__(256) k_cell_max_block(const uint2 *__restrict_
   if (hi && (int)cur < M) atomicMax(&top[cur], hi);
   __syncthreads();
   if ((int)threadIdx.x < M) out[(int64_t)blockIdx.x * M + threadIdx.x] = top[threadIdx.x];
+}
+
+// Coarse bound grid: one block per cell of 2^shift voxels per edge, the byte of
+// the cell's largest share rho f[m] (ctd_bound.h).  Reads every voxel once, rows
+// of the cell coalesced.
+__global__ void __launch_bounds__(256) k_coarse(const uint2 *__restrict__ vox, int nx, int ny,
+                                                int nz, int shift, int ncx, int ncy,
+                                                const float *__restrict__ f,
+                                                uint8_t *__restrict__ out) {
+  __shared__ float top[4];
+  const int cx = (int)(blockIdx.x % (unsigned)ncx);
+  const int row = (int)(blockIdx.x / (unsigned)ncx);
+  const int cs = 1 << shift;
+  const int x0 = cx * cs, y0 = (row % ncy) * cs, z0 = (row / ncy) * cs;
+  const int wx = min(cs, nx - x0), wy = min(cs, ny - y0), wz = min(cs, nz - z0);
+  float share = 0.0f;
+  for (int i = threadIdx.x; i < wx * wy * wz; i += blockDim.x) {
+    const int x = i % wx, t = i / wx;
+    const uint2 r = vox[((int64_t)(z0 + t / wy) * ny + (y0 + t % wy)) * nx + (x0 + x)];
+    if (r.x) share = fmaxf(share, __uint_as_float(r.x) * f[r.y]);
+  }
+  for (int d = 32; d > 0; d >>= 1) share = fmaxf(share, __shfl_xor(share, d));
+  if ((threadIdx.x & 63) == 0) top[threadIdx.x >> 6] = share;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int i = 1; i < 4; ++i) share = fmaxf(share, top[i]);
+    out[blockIdx.x] = coarse_byte(share);
+  }
 }
 
 // Bound grid: one lane per block of 2^shift voxels per edge.  A block whose
@@ -2068,26 +2266,40 @@ int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,
   // workgroup's LDS then still allows the resident workgroups the grid is
   // sized for, with the largest source stash (64, 32 or 16 records per wave)
   // that fits beside them; without the tables, the largest stash that fits
-  // (16 at least)
+  // (16 at least).  Deferred launches take with them the coarse bound grid and
+  // the largest store of parked photons that fits (72: a pass finds a photon
+  // for each of 64 lanes; head 1e9 histories 90.9 ms with 64, 88.4 with 72),
+  // or the coarse grid alone, or neither.
   const int cursors = out == kOutRecords ? dl.cursors : 0;
-  int tab_n = cfg.tab_n, cap = 0;
+  const bool parks = step_kind == kStepDeferred && out == kOutTally;
+  int tab_n = cfg.tab_n, cap = 0, park_cap = 0, coarse_cap = parks ? kCoarseCells : 0;
+  const auto bytes = [&](int n, int stash) {
+    return transport_lds_bytes(cfg.block, cfg.tally_mode, n, cfg.tab_ne, stash, cursors,
+                               parks ? park_cap : -1, coarse_cap);
+  };
+  if (parks && tab_n > 0 && cfg.defer_min > 0) {
+    for (int pc : {72, 64, 48, 32}) {
+      park_cap = pc;
+      if (bytes(tab_n, 64) <= cfg.lds_budget) cap = 64;
+      else if (bytes(tab_n, 32) <= cfg.lds_budget) cap = 32;
+      if (cap) break;
+    }
+    if (!cap) park_cap = 0;
+  }
   if (tab_n > 0) {
     for (int c = 64; c >= 16 && !cap; c >>= 1)
-      if (transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, c, cursors) <=
-          cfg.lds_budget)
-        cap = c;
+      if (bytes(tab_n, c) <= cfg.lds_budget) cap = c;
     if (!cap) tab_n = 0;
   }
   if (!cap) {
     cap = 16;
+    if (bytes(0, cap) > cfg.lds_budget) coarse_cap = parks ? 16 : 0;
     for (int c = 64; c > 16 && cap == 16; c >>= 1)
-      if (transport_lds_bytes(cfg.block, cfg.tally_mode, 0, 0, c, cursors) <= cfg.lds_budget)
-        cap = c;
+      if (bytes(0, c) <= cfg.lds_budget) cap = c;
   }
-  const size_t lds =
-      transport_lds_bytes(cfg.block, cfg.tally_mode, tab_n, cfg.tab_ne, cap, cursors);
+  const size_t lds = bytes(tab_n, cap);
   using Kern = void (*)(const RoundCase *, int, uint64_t, unsigned long long *, int, int, int,
-                        int, int, int, int, int, DepositLog);
+                        int, int, int, int, int, int, int, DepositLog);
 #define CTD_KIND(OUT, KIND) {k_transport<OUT, KIND, false>, k_transport<OUT, KIND, true>}
   static const Kern kerns[3][kStepKinds][2] = {
       {CTD_KIND(kOutTally, kStepPlain), CTD_KIND(kOutTally, kStepDeferred),
@@ -2103,7 +2315,8 @@ int launch_transport(const RoundCase *rc_dev, int nrc, uint64_t total_chunks,
   if (!kern) return -1;
   hipLaunchKernelGGL(kern, dim3(cfg.grid), dim3(cfg.block), lds, s, rc_dev, nrc, total_chunks,
                      chunk_ctr, cfg.refill_min, cfg.chunk, cfg.tally_mode, cfg.bound_shift,
-                     cfg.defer_min, tab_n, tab_n > 0 ? cfg.tab_ne : 0, cap, dl);
+                     cfg.defer_min, tab_n, tab_n > 0 ? cfg.tab_ne : 0, cap, park_cap,
+                     coarse_cap, dl);
   return check_launch();
 }
 
@@ -2115,12 +2328,14 @@ int launch_collect(const RoundCase *rc_dev, int nrc, const DepositLog &dl, int w
 }
 
 size_t transport_lds_bytes(int block, int tally_mode, int tab_n, int tab_ne, int stash_cap,
-                           int cursors) {
+                           int cursors, int park_cap, int coarse_cap) {
   const size_t nw = (size_t)(block / 64);
   size_t b = kWgSlotsOff + nw * kWaveSlotBytes + (tally_mode == 2 ? nw * kCacheBytesPerWave : 0);
   b += nw * (size_t)stash_cap * kStashRecBytes + (size_t)cursors * 8;
   // majorant nodes, mu/rho rows and (room for) the bound-test sums
-  if (tab_n > 0) b += (size_t)((tab_ne + 3) & ~3) * 4 + (size_t)tab_n * 20;
+  if (tab_n > 0) b += (size_t)((tab_ne + 3) & ~3) * 4 + (size_t)tab_n * (park_cap < 0 ? 20 : 4);
+  if (park_cap >= 0) b += coarse_cap - nw * (kWaveSlotBytes - kWaveAccBytes);
+  if (park_cap > 0) b += nw * (size_t)park_cap * kParkRecBytes;
   return b;
 }
 
@@ -2131,7 +2346,7 @@ bool transport_lds_fits(int block, int tally_mode, int device) {
     (void)hipGetLastError();  // not a launch error: leave nothing for check_launch
     return false;
   }
-  return transport_lds_bytes(block, tally_mode, 0, 0, 16, 0) <= (size_t)lim;
+  return transport_lds_bytes(block, tally_mode, 0, 0, 16, 0, -1, 0) <= (size_t)lim;
 }
 
 static int grid_for(int64_t n, int block, int cap) {
@@ -2184,6 +2399,16 @@ int launch_cell_max(const uint2 *vox, int nx, int ny, int nz, int cs, int ncx, i
   }
   hipLaunchKernelGGL(k_cell_max, dim3(grid_for(V, 256, 8192)), dim3(256), 0, (hipStream_t)stream,
                      vox, nx, ny, V, cs, ncx, ncy, M, out);
+  return check_launch();
+}
+
+int launch_coarse(const uint2 *vox, int nx, int ny, int nz, int shift, const float *f,
+                  uint8_t *out, void *stream) {
+  const int e = (1 << shift) - 1;
+  const int cx = (nx + e) >> shift, cy = (ny + e) >> shift, cz = (nz + e) >> shift;
+  if ((int64_t)cx * cy * cz > kCoarseCells || nx < 1 || ny < 1 || nz < 1) return -1;
+  hipLaunchKernelGGL(k_coarse, dim3((unsigned)(cx * cy * cz)), dim3(256), 0, (hipStream_t)stream,
+                     vox, nx, ny, nz, shift, cx, cy, f, out);
   return check_launch();
 }
 
