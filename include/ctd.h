@@ -213,9 +213,11 @@ typedef struct {
                             Tallies are integer sums: every mode gives the
                             same bits. */
   int32_t bound_block;   /* Early rejection of fictitious collisions (GLOBAL
-                            tracking of phantoms stored as 8-byte records):
-                            0 off; 1, 2 or 4 = edge in voxels of the blocks
-                            of a 1-byte bound grid built at phantom load.  A
+                            tracking of phantoms stored as 8-byte records,
+                            and of piecewise-constant ones where few
+                            collisions deposit, there by voxel whatever the
+                            edge): 0 off; 1, 2 or 4 = edge in voxels of the
+                            blocks of a 1-byte bound grid.  A
                             block of one material carries a density level at
                             or above all of its voxels'; a tentative
                             collision whose xi reaches the level times the

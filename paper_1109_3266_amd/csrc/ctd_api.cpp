@@ -191,6 +191,7 @@ static int build_palette(ctd_ctx *ctx, ctd_phantom *ph, const unsigned int *stat
     return hip_err(ctx, hipGetLastError(), "palette kernel");
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   ph->npal = n;
+  ph->bclass_host.assign(pal.begin(), pal.begin() + n);
   return CTD_OK;
 }
 
@@ -645,6 +646,13 @@ static bool bound_test_in_range(const ctd_phantom *ph, const std::vector<float> 
   return true;
 }
 
+// Palette phantoms take the deferred steps (collision passes on full waves, the
+// coarse bound grid, no deposit records) below this share of collisions that
+// deposit: bodies with bone (shares 0.05-0.07, 35-45 steps per history) 15.8
+// and 10.6 ms per 1e8 histories on 6.7e5 voxels, 21.4 and 13.0 on 4.8e6; bodies
+// without (0.24-0.33, 5-7 steps) 5.3 and 5.7-6.2 ms, water 56 and 113 per 1e9.
+constexpr double kDeferShare = 0.15;
+
 extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms,
                                    ctd_spectrum *sp, ctd_geometry *geo, const ctd_params *p,
                                    ctd_case **out) {
@@ -728,7 +736,12 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
     return cleanup(hip_err(ctx, e, "case alloc"));
   {
     const std::vector<float> bnd = bound_sums(ms, p->rayleigh != 0);
-    cs->use_bound_grid = ph->nclass > 0 && bound_test_in_range(ph, bnd, eg.ne);
+    // a palette phantom's voxel indices are its bound grid, used where few
+    // tentative collisions are real
+    cs->use_bound_grid = (ph->npal > 0 ? cs->deposit_share < kDeferShare &&
+                                             cs->p.tracking != CTD_TRACK_MACRO
+                                       : ph->nclass > 0) &&
+                         bound_test_in_range(ph, bnd, eg.ne);
     // bnd, then the materials' shares and the coarse grid made from them
     std::vector<float> up(bnd);
     up.resize(bnd.size() + (size_t)ms->M);
@@ -817,8 +830,9 @@ void ctd::fill_desc(ctd_case *cs) {
   d.vox8 = cs->ph->vox8;
   d.palette = cs->ph->palette;
   d.npal = cs->ph->npal;
-  for (int s = 0; s < 3; ++s) d.bgrid[s] = cs->ph->bgrid[s];
-  d.bclass = cs->use_bound_grid ? cs->ph->bclass : nullptr;
+  const bool pal = cs->ph->npal > 0;
+  for (int s = 0; s < 3; ++s) d.bgrid[s] = pal ? cs->ph->vox8 : cs->ph->bgrid[s];
+  d.bclass = !cs->use_bound_grid ? nullptr : pal ? cs->ph->palette : cs->ph->bclass;
   d.bnd = cs->d_bnd;
   d.coarse = cs->d_coarse;
   d.cshift = cs->coarse_shift;
@@ -2093,7 +2107,7 @@ extern "C" int32_t ctd_autotune(ctd_ctx *ctx, ctd_case *cs, uint64_t trial_histo
   }
   // stage 1: launch shape and tally mode with the default bound grid; stage
   // 2 (below): the bound grid's block size for the best of stage 1
-  const bool bounded = cs->ph->nclass > 0 && cs->mc_cs == 0;
+  const bool bounded = cs->use_bound_grid && cs->mc_cs == 0;
   const int bb0 = bounded ? default_tuning(ctx).bound_block : 0;
   const int dm0 = default_tuning(ctx).defer_min;
   std::vector<ctd_tuning> cand;

@@ -105,7 +105,7 @@ struct CaseDev {
   float mc_fcs, mc_inv_cs;
   int32_t mc_shift, mc_ncell;
   const float *mc_f;
-  // Bound grid (8-byte record layout only): the class of every block of
+  // Bound grid: the class of every block of
   // 2^s x 2^s x 2^s voxels, s = 0, 1, 2 (blocks per axis ceil(n / 2^s), x
   // fastest; kMixedClass where the block holds more than one material), and
   // the class table bclass[256] = (float bits of a density level, material):

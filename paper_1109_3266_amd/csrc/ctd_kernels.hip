@@ -218,7 +218,7 @@ __device__ __forceinline__ StepCase make_step_case(const CaseDev &c, unsigned lo
   s.cshift = c.coarse && uniform_i(c.ncoarse) <= coarse_cap ? uniform_i(c.cshift) : 31;
   if (bound_shift >= 0 && c.bclass) {
     s.bgrid = uniform_ptr(c.bgrid[bound_shift]);
-    s.bshift = bound_shift;
+    s.bshift = uniform_i(c.npal) > 0 ? 0 : bound_shift;
   }
   s.vox = uniform_ptr(c.vox);
   s.vox8 = uniform_ptr(c.vox8);
@@ -1022,19 +1022,21 @@ __device__ __forceinline__ int home_case(const RoundCase *__restrict__ rcs, int 
 
 static_assert(sizeof(CaseDev) % 4 == 0 && sizeof(CaseDev) <= 512, "CaseDev copy size");
 
-// Copy a case descriptor (and its voxel palette, or else its bound-grid class
-// table, if any) into the workgroup's LDS (threads copy words; the caller's
-// barrier publishes them).
+// Copy a case descriptor and its voxel palette or, for deferred steps, its
+// bound-grid class table into the workgroup's LDS (threads copy words; the
+// caller's barrier publishes them).  A class holds its density level and the
+// row of its material's bound-test sums, at bnd0 + bnd_step * material; the
+// mixed class an infinite level, which rejects nothing.
 __device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseDev *src,
-                                           uint32_t bnd0, uint32_t bnd_step) {
+                                           uint32_t bnd0, uint32_t bnd_step, bool defer) {
   const uint32_t *s = reinterpret_cast<const uint32_t *>(src);
   uint32_t *d = reinterpret_cast<uint32_t *>(dst);
   for (int i = threadIdx.x; i < (int)(sizeof(CaseDev) / 4); i += blockDim.x) d[i] = s[i];
   const uint2 *sp = src->palette;
   const uint2 *sc = src->bclass;
-  if (__builtin_amdgcn_readfirstlane(src->npal) > 0)
+  if (!defer && __builtin_amdgcn_readfirstlane(src->npal) > 0)
     for (int i = threadIdx.x; i < 256; i += blockDim.x) pal[i] = sp[i];
-  else if (sc)
+  else if (defer && sc)
     for (int i = threadIdx.x; i < 256; i += blockDim.x)
       pal[i] = i == (int)kMixedClass ? make_uint2(__float_as_uint(INFINITY), bnd0)
                                      : make_uint2(sc[i].x, bnd0 + __umul24(sc[i].y, bnd_step));
@@ -1161,8 +1163,8 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
       for (int i = threadIdx.x; i < n_b; i += blockDim.x) tabbnd[i] = srcb[i];
     }
     const uint32_t cells = (uint32_t)rcs[c].cd->ne - 1u;
-    if (TAB) stage_case(&G, pal, rcs[c].cd, (uint32_t)(uintptr_t)tabbnd, 4u * cells);
-    else stage_case(&G, pal, rcs[c].cd, 0u, cells);
+    if (TAB) stage_case(&G, pal, rcs[c].cd, (uint32_t)(uintptr_t)tabbnd, 4u * cells, kDefer);
+    else stage_case(&G, pal, rcs[c].cd, 0u, cells, kDefer);
     if constexpr (kPark) {
       // (without a grid, or room for it: one cell that rejects nothing)
       const CaseDev *cd = rcs[c].cd;
