@@ -1367,11 +1367,11 @@ static void harvest_timing(ctd_case *cs) {
 // tally of its own, folded together after it.  A launch ends with its last
 // histories on few lanes (about 0.2 ms) and starts with set-up, so batches are
 // gathered until the launch has kGroupHistories (3e7 / 1e8 / 3e8: the head with
-// macro cells 36.3 / 34.3 / 33.4 ms per 3e8, six uneven cases 63.2 / 63.4 /
-// 60.4 ms per 6e8; no more than the room for deposit records where they are
-// kept), within kGroupMaxBytes of tallies (and an eighth of the
-// free memory), and while the headroom bounds hold without a read-back.  Per-XCD tallies and the event log run a batch at
-// a time, as does a context without workspaces (a server's).
+// macro cells 36.3 / 34.3 / 33.4 ms per 3e8; no more than the room for deposit
+// records where they are kept), within kGroupMaxBytes of tallies (and an eighth
+// of the free memory), and while the headroom bounds hold without a read-back.
+// Per-XCD tallies and the event log run a batch at a time, as does a context
+// without workspaces (a server's).
 constexpr uint64_t kGroupHistories = 300000000, kGroupRounds = 64;
 constexpr size_t kGroupMaxBytes = (size_t)1 << 30;
 
@@ -1440,7 +1440,8 @@ static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases,
 // Enqueue `count` rounds over several cases (batch sizes n[round][case]) as
 // one launch per step kind, then fold every participating case.
 static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
-                     const std::vector<std::vector<uint64_t>> &n, const ctd_tuning &t) {
+                     const std::vector<std::vector<uint64_t>> &n, const ctd_tuning &t,
+                     bool timed) {
   std::vector<RoundItem> items;
   const size_t rounds = n.size();
   bool with_log = false;
@@ -1519,7 +1520,6 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
         if (total[i]) cases[i]->failed = true;
     }
   } mark{ctx, cases, total};
-  const bool timed = cases.size() == 1;
   if (timed) {
     HIPCHK(ctx, hipEventCreate(&tm.a));
     HIPCHK(ctx, hipEventCreate(&tm.b));
@@ -1542,7 +1542,7 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
   for (auto &it : items) group[it.step_kind].push_back(std::move(it));
   for (int gi = 0; gi < kStepKinds && rc == CTD_OK; ++gi) {
     if (group[gi].empty()) continue;
-    rc = submit_round(ctx, group[gi], t, with_log, timed);
+    rc = submit_round(ctx, group[gi], t, with_log, cases.size() == 1);
     if (rc == CTD_OK && ctx->fail_next_round) {
       ctx->fail_next_round = false;
       rc = set_err(ctx, CTD_EDEVICE, "failure injected after a transport launch");
@@ -1577,17 +1577,18 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
 
 int ctd::run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vector<uint64_t> &n,
                    const ctd_tuning &t) {
-  return run_group(ctx, cases, {n}, t);
+  return run_group(ctx, cases, {n}, t, cases.size() == 1);
 }
 
 int ctd::run_rounds(ctd_ctx *ctx, std::vector<ctd_case *> &cases, uint64_t count,
-                    const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t) {
+                    const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t,
+                    bool timed) {
   for (uint64_t r = 0; r < count;) {
     const uint64_t g = group_rounds(ctx, cases, r, count, size, t);
     std::vector<std::vector<uint64_t>> n((size_t)g, std::vector<uint64_t>(cases.size()));
     for (uint64_t k = 0; k < g; ++k)
       for (size_t i = 0; i < cases.size(); ++i) n[k][i] = size(r + k, i);
-    const int rc = run_group(ctx, cases, n, t);
+    const int rc = run_group(ctx, cases, n, t, timed);
     if (rc != CTD_OK) return rc;
     r += g;
   }
@@ -1608,7 +1609,7 @@ extern "C" int32_t ctd_run(ctd_ctx *ctx, ctd_case *cs, uint64_t n_histories) {
   sizes.erase(std::remove(sizes.begin(), sizes.end(), (uint64_t)0), sizes.end());
   std::vector<ctd_case *> one{cs};
   return run_rounds(ctx, one, sizes.size(), [&](uint64_t r, size_t) { return sizes[r]; },
-                    cs->tune);
+                    cs->tune, true);
 }
 
 extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_t *n,
@@ -1625,9 +1626,41 @@ extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_
   }
   const ctd_tuning t = cs[0]->tune;
   std::vector<ctd_case *> cases(cs, cs + count);
-  return run_rounds(
-      ctx, cases, rounds,
-      [&](uint64_t r, size_t i) { return r < sizes[i].size() ? sizes[i][r] : (uint64_t)0; }, t);
+  // One case after another where a case's batches can share launches
+  // (group_rounds): a launch then stages one case, changes none and is sized for
+  // its kind of step.  Rounds over all cases, a batch of each, took 48.7 ms
+  // against 45.2 (six uneven cases, 6e8 histories), 8.1 against 7.3 (6e7), 4.2
+  // against 1.7 (1.8e6), and 16.5 against 10.3 (24 cases, 2.4e7); they remain
+  // for per-XCD tallies, the event log and contexts without workspaces, whose
+  // launches hold one batch of a case, and where the headroom bounds of a case
+  // do not admit all its batches (it may be refused part-way).
+  bool alone = count > 1 && t.tally_mode == 0 && ctx->keep_records;
+  for (int i = 0; i < count && alone; ++i) {
+    double s1 = cases[i]->s1_bound, s2 = cases[i]->s2_bound;
+    alone = cases[i]->log_cap == 0;
+    for (size_t r = 0; r < sizes[i].size() && alone; ++r)
+      alone = headroom_bounds((double)sizes[i][r], cases[i]->e_max, s1, s2, &s1, &s2) ==
+              kHeadroomOk;
+  }
+  if (!alone)
+    return run_rounds(
+        ctx, cases, rounds,
+        [&](uint64_t r, size_t i) { return r < sizes[i].size() ? sizes[i][r] : (uint64_t)0; }, t,
+        count == 1);
+  for (int i = 0; i < count; ++i)
+    if (n[i]) NEED_INTACT(ctx, cases[i]);
+  for (int i = 0; i < count; ++i) {
+    std::vector<ctd_case *> one{cases[i]};
+    const int rc = run_rounds(ctx, one, sizes[i].size(),
+                              [&](uint64_t r, size_t) { return sizes[i][r]; }, t, false);
+    if (rc == CTD_OK) continue;
+    // a case left part-way through its batches spoils the whole call
+    if (cases[i]->failed)
+      for (int k = 0; k < count; ++k)
+        if (n[k]) cases[k]->failed = true;
+    return rc;
+  }
+  return CTD_OK;
 }
 
 extern "C" int32_t ctd_sync(ctd_ctx *ctx, ctd_case *cs) {
@@ -1698,7 +1731,7 @@ uint64_t ctd::sigma_plan(uint64_t have, double sig, double target, uint64_t max_
 
 int ctd::run_batches(ctd_ctx *ctx, ctd_case *cs, uint64_t batch, uint64_t count) {
   std::vector<ctd_case *> one{cs};
-  return run_rounds(ctx, one, count, [&](uint64_t, size_t) { return batch; }, cs->tune);
+  return run_rounds(ctx, one, count, [&](uint64_t, size_t) { return batch; }, cs->tune, true);
 }
 
 extern "C" int32_t ctd_run_batches(ctd_ctx *ctx, ctd_case *cs, uint64_t batch_histories,

@@ -202,9 +202,11 @@ int batch_prefix(ctd_ctx *ctx, const ctd_case *cs, uint64_t n,
 // One round: n[i] histories of case i, one batch each.
 int run_round(ctd_ctx *ctx, std::vector<ctd_case *> &cases, const std::vector<uint64_t> &n,
               const ctd_tuning &t);
-// `count` rounds in order, round r taking size(r, i) histories of case i.
+// `count` rounds in order, round r taking size(r, i) histories of case i; timed
+// (one case): the launches' times go into the case's stats.
 int run_rounds(ctd_ctx *ctx, std::vector<ctd_case *> &cases, uint64_t count,
-               const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t);
+               const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t,
+               bool timed);
 std::vector<uint64_t> split_batches(uint64_t n, int nb);
 int sigma_now(ctd_ctx *ctx, ctd_case *cs, int kind, double frac, double *out);
 // Enqueue the sigma-bar reduction of a case on ctx->stream and the copy of
