@@ -976,8 +976,8 @@ __device__ __forceinline__ bool step_macro(Photon &p, const StepCase &S, const C
 // out are handed to the lanes that next fall idle.  Bound by instruction issue:
 // before, 45 of 64 lanes stepped (the others waited or were idle) and a pass
 // had 17; now 56 and 63.  With fewer wave-level steps the L2 became the limit
-// (96 % of its cycles on random bytes of the bound grid), which the coarse grid
-// below relieves.  Head, 1e9 histories: 124.8 ms without both, 122.8 parked
+// (28 requests per history, 0.73 per channel and clock, nearly all random bytes
+// of the bound grid), which the coarse grid below relieves (6.3 requests).  Head, 1e9 histories: 124.8 ms without both, 122.8 parked
 // only, 102.5 with the coarse grid, 88.4 with the states of a lane in one
 // register (halt), staged row addresses and passes of 64.
 // Three planes of cap 16-byte words per wave; what set_energy derives from the
