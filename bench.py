@@ -19,7 +19,7 @@ variants and the gamma tool) are included unless --quick.
     python bench.py --summarize-counters [--workload W]
 
 turns the rocprofv3 counter runs listed in the counter summary's "commands"
-(written under gpurun_out/) into profiles/k_transport_<W>_pmc.json.
+(in the directories those commands name) into profiles/k_transport_<W>_pmc.json.
 """
 from __future__ import annotations
 
@@ -106,7 +106,7 @@ def counter_file(workload: str, records: bool = False) -> str:
 
 def counter_commands(workload: str, records: bool = False) -> list:
     """rocprofv3 runs behind counter_file (one counter group per run,
-    repository root, output under gpurun_out/).  The static entry point adds
+    repository root).  The static entry point adds
     every deposit to the tally."""
     b = (f"python -u bench.py --quick --no-cpu --workload {workload} --steps 2 --warmup 0"
          + ("" if records else " --static"))

@@ -54,9 +54,11 @@ def _same(a, b):
     return all(np.array_equal(x, y) for x, y in zip(a, b))
 
 
-def _solo(ctx, wl, n, bound):
+def _solo(ctx, wl, n, bound, log=False):
     with Case(ctx, wl) as c:
         L.ctd_set_tuning(ctx, c.cs, L.ctd_tuning(256, 5, 16, 1024, 0, bound, 16))
+        if log:
+            L.ctd_debug_deposit_log(ctx, c.cs, 0, 1, 64)
         L.ctd_run_batches(ctx, c.cs, n, 2)
         return _read(c)
 
@@ -74,19 +76,23 @@ def test_palette_runs_match_plain_runs(ctx, shape, levels, bone, n):
     ref = _solo(ctx, wl, n, 0)
     for bound in (1, 2, 4):
         assert _same(_solo(ctx, wl, n, bound), ref), bound
+    assert _same(_solo(ctx, wl, n, 2, log=True), ref)
 
 
-def test_round_of_all_three_phantom_kinds(ctx):
-    print("[gpu-test] batched round of deferred palette, plain palette and records", flush=True)
+# one case after another (mode 0) and rounds over all cases (mode 1), in which
+# the two deferred cases share launches and workgroups change between them
+@pytest.mark.parametrize("mode", [0, 1])
+def test_run_of_all_three_phantom_kinds(ctx, mode):
+    print(f"[gpu-test] deferred palette, plain palette and records, mode {mode}", flush=True)
     sys.stdout.flush()
     wls = [_body(33, 29, 17, 2, True, 1), _body(24, 24, 20, 2, False, 2), W.head(scale=8)]
     n = [30_000, 40_001, 20_000]
 
-    def run(members, bound):
+    def run(members, bound, mode):
         cases = [Case(ctx, wls[i]) for i in members]
         try:
             for c in cases:
-                L.ctd_set_tuning(ctx, c.cs, L.ctd_tuning(256, 5, 16, 1024, 0, bound, 16))
+                L.ctd_set_tuning(ctx, c.cs, L.ctd_tuning(256, 5, 16, 1024, mode, bound, 16))
             for _ in range(2):
                 L.ctd_run_many(ctx, [c.cs for c in cases], [n[i] for i in members])
             return [_read(c) for c in cases]
@@ -94,5 +100,5 @@ def test_round_of_all_three_phantom_kinds(ctx):
             for c in cases:
                 c.close()
 
-    for i, got in enumerate(run([0, 1, 2], 2)):
-        assert _same(run([i], 0)[0], got), i
+    for i, got in enumerate(run([0, 1, 2], 2, mode)):
+        assert _same(run([i], 0, 0)[0], got), i
