@@ -67,18 +67,14 @@ __device__ __forceinline__ double cell_min(const GammaTables &t, const GammaCell
   return best;
 }
 
-// best over the cell of lattice points around voxel (ix, iy, iz), or `best`
-// where the eight doses rule the cell out.
+// The eight doses of the cell with lower corner j: at its border the outermost
+// cell's, with lo / hi the axes whose weight is clamped to 0 / 1.
 template <bool BORDER>
-__device__ __forceinline__ double visit(const GammaTables &t, const GammaCell &c,
-                                        const float *__restrict__ ev, int nx, int ny, int nz,
-                                        int ix, int iy, int iz, double dr, double best,
-                                        double scale) {
+__device__ __forceinline__ void load_cell(const float *__restrict__ ev, int nx, int ny, int nz,
+                                          const int j[3], float f[8], bool lo[3], bool hi[3]) {
   const int64_t sy = nx, sz = (int64_t)nx * ny;
-  const int j[3] = {ix + c.cx, iy + c.cy, iz + c.cz}, nn[3] = {nx, ny, nz};
-  float f[8];
-  bool lo[3], hi[3];
   if constexpr (BORDER) {
+    const int nn[3] = {nx, ny, nz};
     int a0[3], a1[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
@@ -96,6 +92,34 @@ __device__ __forceinline__ double visit(const GammaTables &t, const GammaCell &c
     f[0] = p[0]; f[1] = p[1]; f[2] = p[sy]; f[3] = p[sy + 1];
     f[4] = p[sz]; f[5] = p[sz + 1]; f[6] = p[sz + sy]; f[7] = p[sz + sy + 1];
   }
+}
+
+// Whether the dose at the centre of voxel (ix, iy, iz) counts: the interpolant
+// there is formed from the eight doses of the voxel's cell, and is not a number
+// where one of them is not finite.
+__device__ __forceinline__ bool centre_finite(const float *__restrict__ ev, int nx, int ny, int nz,
+                                              int ix, int iy, int iz) {
+  const int j[3] = {ix, iy, iz};
+  float f[8];
+  bool lo[3], hi[3];
+  load_cell<true>(ev, nx, ny, nz, j, f, lo, hi);
+  uint32_t top = 0u;
+#pragma unroll
+  for (int a = 0; a < 8; ++a) top = max(top, __float_as_uint(f[a]) & 0x7FFFFFFFu);
+  return top < 0x7F800000u;
+}
+
+// best over the cell of lattice points around voxel (ix, iy, iz), or `best`
+// where the eight doses rule the cell out.
+template <bool BORDER>
+__device__ __forceinline__ double visit(const GammaTables &t, const GammaCell &c,
+                                        const float *__restrict__ ev, int nx, int ny, int nz,
+                                        int ix, int iy, int iz, double dr, double best,
+                                        double scale) {
+  const int j[3] = {ix + c.cx, iy + c.cy, iz + c.cz};
+  float f[8];
+  bool lo[3], hi[3];
+  load_cell<BORDER>(ev, nx, ny, nz, j, f, lo, hi);
   const float fl = fminf(fminf(fminf(f[0], f[1]), fminf(f[2], f[3])),
                          fminf(fminf(f[4], f[5]), fminf(f[6], f[7])));
   const float fh = fmaxf(fmaxf(fmaxf(f[0], f[1]), fmaxf(f[2], f[3])),
@@ -151,7 +175,7 @@ __global__ void __launch_bounds__(256) k_gamma(const float *__restrict__ ref,
     iy = (int)(row % ny);
     iz = (int)(row / ny);
   }
-  if (active) {   // the voxel's own centre first: it bounds the search
+  if (active && centre_finite(ev, nx, ny, nz, ix, iy, iz)) {   // it bounds the search
     const double d = dr - (double)ev[v] * scale;
     best = fmin(best, d * d);
   }
