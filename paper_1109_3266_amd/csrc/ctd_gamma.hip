@@ -67,6 +67,13 @@ __device__ __forceinline__ double cell_min(const GammaTables &t, const GammaCell
   return best;
 }
 
+// Cell index of a voxel index and a cell's offset, which for voxels far smaller
+// than a lattice step lies at the end of the int range: saturating (one
+// instruction), so that such a cell stays beyond the grid's edge.
+__device__ __forceinline__ int cell_at(int i, int offset) {
+  return __builtin_elementwise_add_sat(i, offset);
+}
+
 // The eight doses of the cell with lower corner j: at its border the outermost
 // cell's, with lo / hi the axes whose weight is clamped to 0 / 1.
 template <bool BORDER>
@@ -116,7 +123,7 @@ __device__ __forceinline__ double visit(const GammaTables &t, const GammaCell &c
                                         const float *__restrict__ ev, int nx, int ny, int nz,
                                         int ix, int iy, int iz, double dr, double best,
                                         double scale) {
-  const int j[3] = {ix + c.cx, iy + c.cy, iz + c.cz};
+  const int j[3] = {cell_at(ix, c.cx), cell_at(iy, c.cy), cell_at(iz, c.cz)};
   float f[8];
   bool lo[3], hi[3];
   load_cell<BORDER>(ev, nx, ny, nz, j, f, lo, hi);
@@ -185,7 +192,7 @@ __global__ void __launch_bounds__(256) k_gamma(const float *__restrict__ ref,
     const bool want = active && (double)c.r2min < best;
     const int left = __popcll(__ballot(want));
     if (left <= kFewLanes) break;   // none included
-    const int jx = ix + c.cx, jy = iy + c.cy, jz = iz + c.cz;
+    const int jx = cell_at(ix, c.cx), jy = cell_at(iy, c.cy), jz = cell_at(iz, c.cz);
     const bool in = (unsigned)jx < (unsigned)(nx - 1) && (unsigned)jy < (unsigned)(ny - 1) &&
                     (unsigned)jz < (unsigned)(nz - 1);
     if (__all(in || !want)) {
