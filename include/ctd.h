@@ -470,6 +470,17 @@ int32_t ctd_read_event_log(ctd_ctx *ctx, ctd_case *cs, ctd_event *out, uint64_t 
  * completes normally), leaving its cases in the failed state described under
  * Conventions.  One-shot. */
 int32_t ctd_debug_fail_next_round(ctd_ctx *ctx);
+/* For callers that test what happens at limits, until called again (zeros: no
+ * limits).  memory_bytes: a device allocation fails as out of memory where it
+ * and the context's workspaces would together take more.  record_segments:
+ * most segments of deposit records per workgroup of a launch.  rounds: 1 =
+ * ctd_run_many runs rounds over all cases also where it would run them one
+ * after another.  Results do not depend on the last two. */
+int32_t ctd_debug_limits(ctd_ctx *ctx, uint64_t memory_bytes, uint32_t record_segments,
+                         int32_t rounds);
+/* Transport launches of ctd_run* calls on ctx so far (without those of
+ * ctd_run_batches_static), and how many of them kept deposit records. */
+int32_t ctd_debug_launches(ctd_ctx *ctx, uint64_t *launches, uint64_t *with_records);
 
 /* ---------------- serving (continuous batching) ----------------
  * A server owns two private contexts on `device` and two host threads: one

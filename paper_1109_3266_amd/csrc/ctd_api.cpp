@@ -68,6 +68,25 @@ static void dfree(void *p) {
   if (p) (void)hipFree(p);
 }
 
+// Bytes of a segment of deposit records with its link.
+constexpr size_t kSegBytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
+
+size_t ctd::workspace_bytes(const ctd_ctx *ctx) {
+  return ctx->rec_segs * kSegBytes + 8 * ctx->rec_heads + 8 * ctx->group_words + ctx->tool_cap;
+}
+
+hipError_t ctd::dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes) {
+  *p = nullptr;
+  hipError_t e = hipErrorOutOfMemory;
+  if (!ctx->debug_memory || bytes + workspace_bytes(ctx) <= ctx->debug_memory)
+    e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    *p = nullptr;
+  }
+  return e;
+}
+
 // --------------------------------------------------------------- context
 
 extern "C" int32_t ctd_create(ctd_ctx **out, int32_t device) {
@@ -182,8 +201,8 @@ static int build_palette(ctd_ctx *ctx, ctd_phantom *ph, const unsigned int *stat
   std::vector<uint2> pal(512, make_uint2(0u, 0u));
   for (int j = 0; j < n; ++j) pal[j] = make_uint2((uint32_t)keys[j], (uint32_t)(keys[j] >> 32));
   std::memcpy(pal.data() + 256, keys.data(), 8 * (size_t)n);
-  HIPCHK(ctx, hipMalloc(&ph->vox8, (size_t)ph->V));
-  HIPCHK(ctx, hipMalloc(&ph->palette, sizeof(uint2) * 512));
+  HIPCHK(ctx, dev_alloc(ctx, &ph->vox8, (size_t)ph->V));
+  HIPCHK(ctx, dev_alloc(ctx, &ph->palette, sizeof(uint2) * 512));
   HIPCHK(ctx, hipMemcpyAsync(ph->palette, pal.data(), sizeof(uint2) * 512, hipMemcpyHostToDevice,
                              ctx->stream));
   if (launch_palette_index(ph->vox, ph->V, (const unsigned long long *)(ph->palette + 256), n,
@@ -221,8 +240,8 @@ static int build_bound_grids(ctd_ctx *ctx, ctd_phantom *ph) {
     }
   }
   const ctd_grid &g = ph->g;
-  HIPCHK(ctx, hipMalloc(&ph->bclass, sizeof(uint2) * 256));
-  HIPCHK(ctx, hipMalloc(&ph->bclass_range, sizeof(int2) * 256));
+  HIPCHK(ctx, dev_alloc(ctx, &ph->bclass, sizeof(uint2) * 256));
+  HIPCHK(ctx, dev_alloc(ctx, &ph->bclass_range, sizeof(int2) * 256));
   HIPCHK(ctx, hipMemcpy(ph->bclass, cls.data(), sizeof(uint2) * 256, hipMemcpyHostToDevice));
   HIPCHK(ctx, hipMemcpy(ph->bclass_range, range.data(), sizeof(int2) * 256,
                         hipMemcpyHostToDevice));
@@ -230,7 +249,7 @@ static int build_bound_grids(ctd_ctx *ctx, ctd_phantom *ph) {
     const int e = (1 << s) - 1;
     const size_t nb = (size_t)((g.nx + e) >> s) * (size_t)((g.ny + e) >> s) *
                       (size_t)((g.nz + e) >> s);
-    HIPCHK(ctx, hipMalloc(&ph->bgrid[s], nb));
+    HIPCHK(ctx, dev_alloc(ctx, &ph->bgrid[s], nb));
     if (launch_block_class(ph->vox, g.nx, g.ny, g.nz, s, ph->bclass, ph->bclass_range,
                            ph->bgrid[s], ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "bound grid kernel");
@@ -282,12 +301,12 @@ extern "C" int32_t ctd_phantom_load(ctd_ctx *ctx, const ctd_grid *g, const uint8
     delete ph;
     return code;
   };
-  hipError_t e = hipMalloc(&ph->vox, sizeof(uint2) * V);
+  hipError_t e = dev_alloc(ctx, &ph->vox, sizeof(uint2) * V);
   if (e != hipSuccess) return fail(hip_err(ctx, e, "phantom alloc"));
   const uint8_t *pm = mat;
   const float *pr = rho;
   if (mem == CTD_MEM_HOST) {
-    if ((e = hipMalloc(&dmat, V)) != hipSuccess || (e = hipMalloc(&drho, 4 * V)) != hipSuccess)
+    if ((e = dev_alloc(ctx, &dmat, V)) != hipSuccess || (e = dev_alloc(ctx, &drho, 4 * V)) != hipSuccess)
       return fail(hip_err(ctx, e, "phantom staging alloc"));
     if ((e = hipMemcpyAsync(dmat, mat, V, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess ||
         (e = hipMemcpyAsync(drho, rho, 4 * V, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess)
@@ -341,7 +360,7 @@ extern "C" int32_t ctd_phantom_release(ctd_ctx *ctx, ctd_phantom *ph) {
 // ------------------------------------------------------------- materials
 
 static int upload(ctd_ctx *ctx, void **dst, const void *src, size_t bytes) {
-  HIPCHK(ctx, hipMalloc(dst, bytes));
+  HIPCHK(ctx, dev_alloc(ctx, dst, bytes));
   HIPCHK(ctx, hipMemcpy(*dst, src, bytes, hipMemcpyHostToDevice));
   return CTD_OK;
 }
@@ -726,13 +745,13 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
   };
   hipError_t e;
   std::vector<float> blo(sp->lo.begin(), sp->lo.end());
-  if ((e = hipMalloc(&cs->d_tally, 8 * V)) != hipSuccess ||
-      (e = hipMalloc(&cs->d_s1, 8 * V)) != hipSuccess ||
-      (e = hipMalloc(&cs->d_s2, 16 * V)) != hipSuccess ||
-      (e = hipMalloc(&cs->d_acc, 8 * kAccWords)) != hipSuccess ||
-      (e = hipMalloc(&cs->d_desc, sizeof(CaseDev))) != hipSuccess ||
-      (e = hipMalloc(&cs->d_mu_max, 4 * eg.ne)) != hipSuccess ||
-      (e = hipMalloc(&cs->d_bin_lo, 4 * blo.size())) != hipSuccess)
+  if ((e = dev_alloc(ctx, &cs->d_tally, 8 * V)) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_s1, 8 * V)) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_s2, 16 * V)) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_acc, 8 * kAccWords)) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_desc, sizeof(CaseDev))) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_mu_max, 4 * eg.ne)) != hipSuccess ||
+      (e = dev_alloc(ctx, &cs->d_bin_lo, 4 * blo.size())) != hipSuccess)
     return cleanup(hip_err(ctx, e, "case alloc"));
   {
     const std::vector<float> bnd = bound_sums(ms, p->rayleigh != 0);
@@ -746,7 +765,7 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
     std::vector<float> up(bnd);
     up.resize(bnd.size() + (size_t)ms->M);
     bound_shares(bnd.data(), cs->mu_max.data(), ms->M, eg.ne, up.data() + bnd.size());
-    if ((e = hipMalloc(&cs->d_bnd, 4 * up.size() + kCoarseCells)) != hipSuccess ||
+    if ((e = dev_alloc(ctx, &cs->d_bnd, 4 * up.size() + kCoarseCells)) != hipSuccess ||
         (e = hipMemcpy(cs->d_bnd, up.data(), 4 * up.size(), hipMemcpyHostToDevice)) != hipSuccess)
       return cleanup(hip_err(ctx, e, "bound-test sums"));
     if (cs->use_bound_grid && cs->p.tracking != CTD_TRACK_MACRO) {
@@ -766,11 +785,11 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
     }
   }
   if (!geo->proj_sc.empty() &&
-      (e = hipMalloc(&cs->d_proj, sizeof(float4) * geo->proj_sc.size())) != hipSuccess)
+      (e = dev_alloc(ctx, &cs->d_proj, sizeof(float4) * geo->proj_sc.size())) != hipSuccess)
     return cleanup(hip_err(ctx, e, "case alloc"));
   if (!geo->fl_cdf.empty() &&
-      ((e = hipMalloc(&cs->d_fl_cdf, sizeof(double) * geo->fl_cdf.size())) != hipSuccess ||
-       (e = hipMalloc(&cs->d_fl_guide, sizeof(int32_t) * geo->fl_guide.size())) != hipSuccess ||
+      ((e = dev_alloc(ctx, &cs->d_fl_cdf, sizeof(double) * geo->fl_cdf.size())) != hipSuccess ||
+       (e = dev_alloc(ctx, &cs->d_fl_guide, sizeof(int32_t) * geo->fl_guide.size())) != hipSuccess ||
        (e = hipMemcpy(cs->d_fl_cdf, geo->fl_cdf.data(), sizeof(double) * geo->fl_cdf.size(),
                       hipMemcpyHostToDevice)) != hipSuccess ||
        (e = hipMemcpy(cs->d_fl_guide, geo->fl_guide.data(),
@@ -778,8 +797,8 @@ extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms
            hipSuccess))
     return cleanup(hip_err(ctx, e, "fluence map upload"));
   if (!geo->fl_f.empty() &&
-      ((e = hipMalloc(&cs->d_fl_f, sizeof(float) * geo->fl_f.size())) != hipSuccess ||
-       (e = hipMalloc(&cs->d_mh_state, sizeof(int32_t) * (size_t)geo->g.fluence_chains)) !=
+      ((e = dev_alloc(ctx, &cs->d_fl_f, sizeof(float) * geo->fl_f.size())) != hipSuccess ||
+       (e = dev_alloc(ctx, &cs->d_mh_state, sizeof(int32_t) * (size_t)geo->g.fluence_chains)) !=
            hipSuccess ||
        (e = hipMemcpy(cs->d_fl_f, geo->fl_f.data(), sizeof(float) * geo->fl_f.size(),
                       hipMemcpyHostToDevice)) != hipSuccess))
@@ -1006,7 +1025,7 @@ int ctd::ensure_tally_copies(ctd_ctx *ctx, ctd_case *cs, int copies) {
   const int64_t V = cs->ph->V;
   HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   unsigned long long *t = nullptr;
-  HIPCHK(ctx, hipMalloc(&t, 8 * V * copies));
+  HIPCHK(ctx, dev_alloc(ctx, &t, 8 * V * copies));
   // batch tallies are zero between rounds: a fresh zeroed array replaces them
   if (launch_zero(t, 8 * V * copies, ctx->stream) != 0) {
     dfree(t);
@@ -1027,7 +1046,7 @@ int ctd::ensure_mh_buffer(ctd_ctx *ctx, ctd_case *cs, uint64_t n) {
   dfree(cs->d_mh_beam);
   cs->d_mh_beam = nullptr;
   cs->mh_cap = 0;
-  HIPCHK(ctx, hipMalloc(&cs->d_mh_beam, sizeof(int32_t) * n));
+  HIPCHK(ctx, dev_alloc(ctx, &cs->d_mh_beam, sizeof(int32_t) * n));
   cs->mh_cap = n;
   return CTD_OK;
 }
@@ -1184,7 +1203,6 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
   dl.buckets = total;
   dl.cursors = (int32_t)((most + 1) & ~1u);
   if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors, -1, 0) > cfg.lds_budget) return false;
-  const size_t seg_bytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
   double want = room / ((double)cfg.grid * kLogSeg);
   want += (double)std::min(total, 2 * most);   // a part-filled segment per bucket
   size_t per_wg = (size_t)std::ceil(std::min(want, 1e9));
@@ -1198,11 +1216,11 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
       (void)hipGetLastError();
       return false;
     }
-    const size_t have = segs_of * seg_bytes + ctx->rec_heads * 8;
+    const size_t have = segs_of * kSegBytes + ctx->rec_heads * 8;
     const size_t lim = std::min(kRecordMaxBytes, (free_b + have) / 8);
     const size_t hb = std::max(ctx->rec_heads, heads) * 8;
     if (hb >= lim) return false;
-    const size_t segs = std::min((lim - hb) / seg_bytes, std::max(segs_of, per_wg * cfg.grid + 1));
+    const size_t segs = std::min((lim - hb) / kSegBytes, std::max(segs_of, per_wg * cfg.grid + 1));
     if (segs > segs_of || ctx->rec_heads < heads) {
       if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
       dfree(ctx->rec);
@@ -1210,8 +1228,8 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
       ctx->rec = nullptr;
       ctx->rec_head = nullptr;
       ctx->rec_segs = ctx->rec_heads = 0;
-      if (hipMalloc(&ctx->rec, segs * seg_bytes) != hipSuccess ||
-          hipMalloc(&ctx->rec_head, hb) != hipSuccess) {
+      if (dev_alloc(ctx, &ctx->rec, segs * kSegBytes) != hipSuccess ||
+          dev_alloc(ctx, &ctx->rec_head, hb) != hipSuccess) {
         (void)hipGetLastError();
         dfree(ctx->rec);
         ctx->rec = nullptr;
@@ -1222,6 +1240,7 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
     }
   }
   per_wg = std::min(per_wg, (ctx->rec_segs - 1) / (size_t)cfg.grid);
+  if (ctx->debug_segments) per_wg = std::min(per_wg, (size_t)ctx->debug_segments);
   if (per_wg == 0) return false;
   dl.rec = (uint2 *)ctx->rec;
   dl.prev = (uint32_t *)((char *)ctx->rec + ctx->rec_segs * kLogSeg * sizeof(uint2));
@@ -1302,6 +1321,8 @@ int ctd::submit_round(ctd_ctx *ctx, const std::vector<RoundItem> &items, const c
       launch_transport((const RoundCase *)d, nrc, chunks, (unsigned long long *)(d + ctr_off),
                        cfg, out, dl, kind, ctx->stream) != 0)
     return hip_err(ctx, hipGetLastError(), "transport launch");
+  ctx->n_launches += chunks > 0 ? 1 : 0;
+  ctx->n_record_launches += records ? 1 : 0;
   if (records) {
     // two workgroups per CU walk the chains; more slices add more atomics
     const int slices = std::max(1, (int)(2u * (uint32_t)ctx->n_cu / dl.buckets));
@@ -1424,7 +1445,7 @@ static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases,
     dfree(ctx->group_tally);
     ctx->group_tally = nullptr;
     ctx->group_words = 0;
-    if (hipMalloc(&ctx->group_tally, 8 * words) != hipSuccess) {
+    if (dev_alloc(ctx, &ctx->group_tally, 8 * words) != hipSuccess) {
       (void)hipGetLastError();
       ctx->group_tally = nullptr;
       return 1;
@@ -1634,7 +1655,7 @@ extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_
   // for per-XCD tallies, the event log and contexts without workspaces, whose
   // launches hold one batch of a case, and where the headroom bounds of a case
   // do not admit all its batches (it may be refused part-way).
-  bool alone = count > 1 && t.tally_mode == 0 && ctx->keep_records;
+  bool alone = count > 1 && t.tally_mode == 0 && ctx->keep_records && !ctx->debug_rounds;
   for (int i = 0; i < count && alone; ++i) {
     double s1 = cases[i]->s1_bound, s2 = cases[i]->s2_bound;
     alone = cases[i]->log_cap == 0;
@@ -2039,8 +2060,8 @@ extern "C" int32_t ctd_debug_deposit_log(ctd_ctx *ctx, ctd_case *cs, uint64_t h0
   cs->log_cap = 0;
   cs->log_h0 = cs->log_h1 = 0;
   if (capacity > 0 && nh > 0) {
-    HIPCHK(ctx, hipMalloc(&cs->d_log, sizeof(ctd_event) * capacity));
-    HIPCHK(ctx, hipMalloc(&cs->d_log_n, 256));
+    HIPCHK(ctx, dev_alloc(ctx, &cs->d_log, sizeof(ctd_event) * capacity));
+    HIPCHK(ctx, dev_alloc(ctx, &cs->d_log_n, 256));
     HIPCHK(ctx, hipMemset(cs->d_log_n, 0, 256));
     cs->log_cap = capacity;
     cs->log_h0 = h0;
@@ -2053,6 +2074,22 @@ extern "C" int32_t ctd_debug_deposit_log(ctd_ctx *ctx, ctd_case *cs, uint64_t h0
 extern "C" int32_t ctd_debug_fail_next_round(ctd_ctx *ctx) {
   if (!ctx) return CTD_EINVAL;
   ctx->fail_next_round = true;
+  return CTD_OK;
+}
+
+extern "C" int32_t ctd_debug_limits(ctd_ctx *ctx, uint64_t memory_bytes,
+                                    uint32_t record_segments, int32_t rounds) {
+  if (!ctx) return CTD_EINVAL;
+  ctx->debug_memory = memory_bytes;
+  ctx->debug_segments = record_segments;
+  ctx->debug_rounds = rounds != 0;
+  return CTD_OK;
+}
+
+extern "C" int32_t ctd_debug_launches(ctd_ctx *ctx, uint64_t *launches, uint64_t *with_records) {
+  if (!ctx) return CTD_EINVAL;
+  if (launches) *launches = ctx->n_launches;
+  if (with_records) *with_records = ctx->n_record_launches;
   return CTD_OK;
 }
 
@@ -2114,16 +2151,16 @@ extern "C" int32_t ctd_autotune(ctd_ctx *ctx, ctd_case *cs, uint64_t trial_histo
   hipError_t e;
   tw.tally_copies = kTallyCopies;
   if (cs->d_mh_state &&
-      (e = hipMalloc(&tw.d_mh_state, sizeof(int32_t) * (size_t)cs->geo->g.fluence_chains)) !=
+      (e = dev_alloc(ctx, &tw.d_mh_state, sizeof(int32_t) * (size_t)cs->geo->g.fluence_chains)) !=
           hipSuccess) {
     release();
     return hip_err(ctx, e, "autotune alloc");
   }
-  if ((e = hipMalloc(&tw.d_tally, 8 * V * kTallyCopies)) != hipSuccess ||
-      (e = hipMalloc(&tw.d_s1, 8 * V)) != hipSuccess ||
-      (e = hipMalloc(&tw.d_s2, 16 * V)) != hipSuccess ||
-      (e = hipMalloc(&tw.d_acc, 8 * kAccWords)) != hipSuccess ||
-      (e = hipMalloc(&tw.d_desc, sizeof(CaseDev))) != hipSuccess) {
+  if ((e = dev_alloc(ctx, &tw.d_tally, 8 * V * kTallyCopies)) != hipSuccess ||
+      (e = dev_alloc(ctx, &tw.d_s1, 8 * V)) != hipSuccess ||
+      (e = dev_alloc(ctx, &tw.d_s2, 16 * V)) != hipSuccess ||
+      (e = dev_alloc(ctx, &tw.d_acc, 8 * kAccWords)) != hipSuccess ||
+      (e = dev_alloc(ctx, &tw.d_desc, sizeof(CaseDev))) != hipSuccess) {
     release();
     return hip_err(ctx, e, "autotune alloc");
   }
@@ -2228,8 +2265,8 @@ extern "C" int32_t ctd_microbench(ctd_ctx *ctx, int32_t kind, uint64_t bytes, ui
   NEED(ctx, kind == 0 || (ops > 0 && bytes / 8 <= 0xFFFFFFFFull), "bad ops or size");
   HIPCHK(ctx, hipSetDevice(ctx->device));
   void *a = nullptr, *b = nullptr;
-  HIPCHK(ctx, hipMalloc(&a, bytes));
-  hipError_t e = hipMalloc(&b, kind == 0 ? bytes : 256);
+  HIPCHK(ctx, dev_alloc(ctx, &a, bytes));
+  hipError_t e = dev_alloc(ctx, &b, kind == 0 ? bytes : 256);
   if (e != hipSuccess) {
     dfree(a);
     return hip_err(ctx, e, "microbench alloc");

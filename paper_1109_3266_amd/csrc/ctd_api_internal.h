@@ -68,6 +68,13 @@ struct ctd_ctx {
   unsigned long long *group_tally = nullptr;
   size_t group_words = 0;
   bool group_dirty = false;
+  // ctd_debug_limits: device memory of the workspaces and one allocation
+  // together (0: no limit), segments per workgroup of a record-keeping launch
+  // (0: as planned), ctd_run_many in rounds; ctd_debug_launches
+  uint64_t debug_memory = 0;
+  uint32_t debug_segments = 0;
+  bool debug_rounds = false;
+  uint64_t n_launches = 0, n_record_launches = 0;
   bool xcd_tally_ok = false;  // every XCC id < kTallyCopies
   unsigned int max_xcc = 0;
   int lds_per_cu = 160 * 1024, lds_per_block = 64 * 1024;  // device LDS limits
@@ -227,6 +234,15 @@ int ensure_tally_copies(ctd_ctx *ctx, ctd_case *cs, int copies);
 // of up to round_histories).
 uint64_t case_footprint(const ctd_grid &g, const ctd_geometry *geo, const ctd_params &p,
                         int ne, int tally_copies, uint64_t round_histories);
+// Device memory of the context's workspaces (records, group tallies, tools).
+size_t workspace_bytes(const ctd_ctx *ctx);
+// hipMalloc within ctd_debug_limits; a failure leaves no error behind for the
+// check of a later launch.
+hipError_t dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes);
+template <typename T>
+hipError_t dev_alloc(ctd_ctx *ctx, T **p, size_t bytes) {
+  return dev_alloc_bytes(ctx, (void **)p, bytes);
+}
 // Alg. A1 beamlet buffer of at least n entries.
 int ensure_mh_buffer(ctd_ctx *ctx, ctd_case *cs, uint64_t n);
 // Read V voxels as `planes` arrays of elem-byte words into dst (null: plane

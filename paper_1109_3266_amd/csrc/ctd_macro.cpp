@@ -70,7 +70,7 @@ int ctd::build_macro(ctd_ctx *ctx, ctd_case *cs) {
   unsigned int *d_max = nullptr;
   // whole 8-byte words, so the clearing kernel covers every entry
   const size_t bytes = (sizeof(unsigned int) * (size_t)(cells * M) + 7) & ~(size_t)7;
-  hipError_t e = hipMalloc(&d_max, bytes);
+  hipError_t e = dev_alloc(ctx, &d_max, bytes);
   if (e != hipSuccess) return hip_err(ctx, e, "macro-cell scratch");
   std::vector<unsigned int> hmax((size_t)(cells * M));
   int rc = CTD_OK;
@@ -141,7 +141,7 @@ int ctd::build_macro(ctd_ctx *ctx, ctd_case *cs) {
   for (int b = 0; b < nb; ++b)
     for (int64_t c = 0; c < cells; ++c)
       fac[(size_t)b * cells + c] = fcls[(size_t)cls[(size_t)c] * nb + b];
-  if ((e = hipMalloc(&cs->d_mc_f, sizeof(float) * fac.size())) != hipSuccess ||
+  if ((e = dev_alloc(ctx, &cs->d_mc_f, sizeof(float) * fac.size())) != hipSuccess ||
       (e = hipMemcpy(cs->d_mc_f, fac.data(), sizeof(float) * fac.size(),
                      hipMemcpyHostToDevice)) != hipSuccess)
     return hip_err(ctx, e, "macro-cell upload");

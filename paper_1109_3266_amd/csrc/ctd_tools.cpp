@@ -130,12 +130,12 @@ extern "C" int32_t ctd_gamma(ctd_ctx *ctx, const ctd_grid *g, const float *ref, 
   Dev d;   // a block too large to keep
   hipError_t e;
   if (bytes > kToolMaxBytes) {
-    if ((e = hipMalloc(&d.p, bytes)) != hipSuccess) return hip_err(ctx, e, "gamma alloc");
+    if ((e = dev_alloc(ctx, &d.p, bytes)) != hipSuccess) return hip_err(ctx, e, "gamma alloc");
   } else if (ctx->tool_cap < bytes) {   // nothing uses it: every call ends with a wait
     if (ctx->tool_ws) (void)hipFree(ctx->tool_ws);
     ctx->tool_ws = nullptr;
     ctx->tool_cap = 0;
-    if ((e = hipMalloc(&ctx->tool_ws, bytes)) != hipSuccess)
+    if ((e = dev_alloc(ctx, &ctx->tool_ws, bytes)) != hipSuccess)
       return hip_err(ctx, e, "gamma alloc");
     ctx->tool_cap = bytes;
   }

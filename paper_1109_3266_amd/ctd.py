@@ -177,6 +177,8 @@ _SIGS = {
                         C.POINTER(U64), C.POINTER(U64)]),
     "ctd_debug_deposit_log": (I32, [P, P, U64, U64, U64]),
     "ctd_debug_fail_next_round": (I32, [P]),
+    "ctd_debug_limits": (I32, [P, U64, U32, I32]),
+    "ctd_debug_launches": (I32, [P, C.POINTER(U64), C.POINTER(U64)]),
     "ctd_server_start": (I32, [I32, C.POINTER(ctd_server_config), PP]),
     "ctd_server_last_error": (C.c_char_p, [P]),
     "ctd_server_now": (F64, [P]),
@@ -443,6 +445,17 @@ def ctd_gamma(ctx, grid: ctd_grid, ref, ev, dose_tol: float, dta_cm: float, regi
 
 def ctd_debug_fail_next_round(ctx):
     check(lib().ctd_debug_fail_next_round(ctx), ctx)
+
+
+def ctd_debug_limits(ctx, memory_bytes: int = 0, record_segments: int = 0, rounds: bool = False):
+    check(lib().ctd_debug_limits(ctx, int(memory_bytes), int(record_segments), int(rounds)), ctx)
+
+
+def ctd_debug_launches(ctx) -> tuple:
+    """(transport launches, those with deposit records) of the context so far"""
+    n, r = C.c_uint64(), C.c_uint64()
+    check(lib().ctd_debug_launches(ctx, C.byref(n), C.byref(r)), ctx)
+    return n.value, r.value
 
 
 def ctd_debug_deposit_log(ctx, cs, h0: int, nh: int, capacity: int):
