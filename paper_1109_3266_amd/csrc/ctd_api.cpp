@@ -1198,8 +1198,6 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
       dense ? std::max<uint64_t>(100000, std::min(3 * voxels, std::max<uint64_t>(3000000, voxels / 4)))
             : std::max<uint64_t>(100000000, 4 * voxels);
   if (n < least) return false;
-  // a cursor's 32-bit count holds every deposit its workgroup may add to it
-  if (n / (uint64_t)cfg.grid >= ((uint64_t)1 << 28)) return false;
   dl.buckets = total;
   dl.cursors = (int32_t)((most + 1) & ~1u);
   if (transport_lds_bytes(cfg.block, 0, 0, 0, 16, dl.cursors, -1, 0) > cfg.lds_budget) return false;

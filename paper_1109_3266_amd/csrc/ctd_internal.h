@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "ctd.h"
+#include "ctd_records.h"
 #include "ctd_schedule.h"
 
 namespace ctd {
@@ -166,7 +167,6 @@ constexpr int kOutTally = 0, kOutEvents = 1, kOutRecords = 2;
 // segment its LDS cursor of the voxel's bucket points to; prev links a
 // bucket's segments of one workgroup, head[workgroup][bucket] = (last
 // segment, records in it) once the workgroup has left the bucket's case.
-constexpr uint32_t kLogSeg = 256;
 struct DepositLog {
   uint2 *rec;                // [segments][kLogSeg] (voxel within the bucket, q)
   uint32_t *prev;            // [segments]

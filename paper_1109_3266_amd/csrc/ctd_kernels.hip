@@ -312,6 +312,11 @@ __device__ __forceinline__ void record_deposit(const StepCase &S, int32_t vox, u
       const uint32_t next = __hip_atomic_fetch_add(S.seg_next, mine ? 1u : 0u, __ATOMIC_RELAXED,
                                                    __HIP_MEMORY_SCOPE_WORKGROUP);
       if (next >= S.seg_next[1] || (!mine && t >= 16)) {
+        if ((uint32_t)w >= kCursorHigh) {   // (ctd_records.h)
+          unsigned long long seen = w + 1ull;
+          __hip_atomic_compare_exchange_strong(cur, &seen, cursor_full(w), __ATOMIC_RELAXED,
+                                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        }
         tally_add(S, vox, q);
         w = kLogSeg;
         todo = false;
