@@ -72,7 +72,8 @@ static void dfree(void *p) {
 constexpr size_t kSegBytes = kLogSeg * sizeof(uint2) + sizeof(uint32_t);
 
 size_t ctd::workspace_bytes(const ctd_ctx *ctx) {
-  return ctx->rec_segs * kSegBytes + 8 * ctx->rec_heads + 8 * ctx->group_words + ctx->tool_cap;
+  return ctx->rec_segs * kSegBytes + 8 * ctx->rec_heads + 8 * ctx->group_words +
+         4 * ctx->group_beams + ctx->tool_cap;
 }
 
 hipError_t ctd::dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes) {
@@ -161,6 +162,7 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   dfree(ctx->rec);
   dfree(ctx->rec_head);
   dfree(ctx->group_tally);
+  dfree(ctx->group_beam);
   if (ctx->sigma_host) (void)hipHostFree(ctx->sigma_host);
   if (ctx->read_host) (void)hipHostFree(ctx->read_host);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
@@ -1387,12 +1389,46 @@ static void harvest_timing(ctd_case *cs) {
 // histories on few lanes (about 0.2 ms) and starts with set-up, so batches are
 // gathered until the launch has kGroupHistories (3e7 / 1e8 / 3e8: the head with
 // macro cells 36.3 / 34.3 / 33.4 ms per 3e8; no more than the room for deposit
-// records where they are kept), within kGroupMaxBytes of tallies (and an eighth
-// of the free memory), and while the headroom bounds hold without a read-back.
-// Per-XCD tallies and the event log run a batch at a time, as does a context
-// without workspaces (a server's).
+// records where they are kept), within kGroupMaxBytes of tallies and Alg. A1
+// beamlets (and an eighth of the free memory), and while the headroom bounds
+// hold without a read-back.  Per-XCD tallies and the event log run a batch at a
+// time, as does a context without workspaces (a server's).
 constexpr uint64_t kGroupHistories = 300000000, kGroupRounds = 64;
 constexpr size_t kGroupMaxBytes = (size_t)1 << 30;
+
+// Room for `words` tally words, all zero, and `beams` beamlets; false where the
+// memory does not allow it.
+static bool reserve_group(ctd_ctx *ctx, size_t words, size_t beams) {
+  const bool more_words = ctx->group_words < words, more_beams = ctx->group_beams < beams;
+  if (more_words || more_beams) {
+    size_t free_b = 0, total_b = 0;
+    const size_t bytes = (more_words ? 8 * words : 0) + (more_beams ? 4 * beams : 0);
+    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 8 ||
+        hipStreamSynchronize(ctx->stream) != hipSuccess) {
+      (void)hipGetLastError();
+      return false;
+    }
+  }
+  if (more_beams) {
+    dfree(ctx->group_beam);
+    ctx->group_beam = nullptr;
+    ctx->group_beams = 0;
+    if (dev_alloc(ctx, &ctx->group_beam, 4 * beams) != hipSuccess) return false;
+    ctx->group_beams = beams;
+  }
+  if (more_words) {
+    dfree(ctx->group_tally);
+    ctx->group_tally = nullptr;
+    ctx->group_words = 0;
+    if (dev_alloc(ctx, &ctx->group_tally, 8 * words) != hipSuccess) return false;
+    ctx->group_words = words;
+    ctx->group_dirty = true;
+  }
+  if (ctx->group_dirty && launch_zero(ctx->group_tally, 8 * ctx->group_words, ctx->stream) != 0)
+    return false;
+  ctx->group_dirty = false;
+  return true;
+}
 
 static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases, uint64_t r,
                              uint64_t count,
@@ -1412,13 +1448,14 @@ static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases,
     s1[i] = cases[i]->s1_bound;
     s2[i] = cases[i]->s2_bound;
   }
-  uint64_t g = 0, n = 0;
+  uint64_t g = 0, n = 0, beams = 0;
   for (; r + g < count && g < kGroupRounds; ++g) {
-    uint64_t more = 0;
-    bool fits = 8 * voxels * g <= kGroupMaxBytes;
+    uint64_t more = 0, more_beams = 0;
+    bool fits = true;
     for (size_t i = 0; i < cases.size() && fits; ++i) {
       const uint64_t k = size(r + g, i);
       more += k;
+      if (cases[i]->d_mh_state) more_beams += k;
       double a = 0.0, b = 0.0;
       if (k && headroom_bounds((double)k, cases[i]->e_max, s1[i], s2[i], &a, &b) != kHeadroomOk)
         fits = false;
@@ -1427,33 +1464,14 @@ static uint64_t group_rounds(ctd_ctx *ctx, const std::vector<ctd_case *> &cases,
         s2[i] = b;
       }
     }
-    if (!fits || (g > 0 && n + more > most)) break;
+    if (!fits || 8 * voxels * g + 4 * (beams + more_beams) > kGroupMaxBytes ||
+        (g > 0 && n + more > most))
+      break;
     n += more;
+    beams += more_beams;
   }
   if (g <= 1) return 1;
-  const size_t words = (size_t)(voxels * (g - 1));
-  if (ctx->group_words >= words && !ctx->group_dirty) return g;
-  if (ctx->group_words < words) {
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || 8 * words > free_b / 8 ||
-        hipStreamSynchronize(ctx->stream) != hipSuccess) {
-      (void)hipGetLastError();
-      return 1;
-    }
-    dfree(ctx->group_tally);
-    ctx->group_tally = nullptr;
-    ctx->group_words = 0;
-    if (dev_alloc(ctx, &ctx->group_tally, 8 * words) != hipSuccess) {
-      (void)hipGetLastError();
-      ctx->group_tally = nullptr;
-      return 1;
-    }
-    ctx->group_words = words;
-  }
-  ctx->group_dirty = true;
-  if (launch_zero(ctx->group_tally, 8 * ctx->group_words, ctx->stream) != 0) return 1;
-  ctx->group_dirty = false;
-  return g;
+  return reserve_group(ctx, (size_t)(voxels * (g - 1)), (size_t)beams) ? g : 1;
 }
 
 // Enqueue `count` rounds over several cases (batch sizes n[round][case]) as
@@ -1469,8 +1487,9 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
     for (size_t r = 0; r < rounds; ++r) total[i] += n[r][i];
     if (total[i]) NEED_INTACT(ctx, cases[i]);
   }
-  size_t off = 0;   // words of the group's tallies taken
+  size_t off = 0, beam_off = 0;   // of the group's tallies and beamlets taken
   std::vector<unsigned long long *> more(cases.size(), nullptr);
+  std::vector<int32_t *> beam(cases.size(), nullptr);
   for (size_t i = 0; i < cases.size(); ++i) {
     ctd_case *cs = cases[i];
     if (total[i] == 0) continue;
@@ -1479,9 +1498,15 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
       rc0 = ensure_tally_copies(ctx, cs, kTallyCopies);
       if (rc0 != CTD_OK) return rc0;
     }
-    if (cs->d_mh_state) {
+    // the case's own buffer holds one batch, and does not move for a group
+    // (ctd_run_batches_static may have enqueued its address)
+    if (cs->d_mh_state && rounds == 1) {
       rc0 = ensure_mh_buffer(ctx, cs, total[i]);
       if (rc0 != CTD_OK) return rc0;
+      beam[i] = cs->d_mh_beam;
+    } else if (cs->d_mh_state) {
+      beam[i] = ctx->group_beam + beam_off;
+      beam_off += (size_t)total[i];
     }
     more[i] = ctx->group_tally + off;
     off += (size_t)cs->ph->V * (rounds - 1);
@@ -1500,7 +1525,7 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
       it.step_kind = step_kind(cs, t);
       it.tab_n = cs->ms->M * cs->ms->eg.ne;
       it.tab_ne = cs->ms->eg.ne;
-      if (cs->d_mh_state) it.beamlets = cs->d_mh_beam + done;
+      if (beam[i]) it.beamlets = beam[i] + done;
       if (r > 0 && n[r][i] == n[r - 1][i] && !items.empty()) {
         it.prefix = items.back().prefix;
       } else {
@@ -1553,7 +1578,7 @@ static int run_group(ctd_ctx *ctx, std::vector<ctd_case *> &cases,
     if (total[i] == 0 || !cs->d_mh_state) continue;
     if (launch_mh_fill(cs->d_fl_f, (int)cs->geo->fl_f.size(), cs->geo->g.fluence_chains,
                        cs->h_next, total[i], cs->desc.key0, cs->desc.key1, cs->d_mh_state,
-                       cs->d_mh_beam, ctx->stream) != 0)
+                       beam[i], ctx->stream) != 0)
       return hip_err(ctx, hipGetLastError(), "Metropolis-Hastings fill launch");
   }
   int rc = CTD_OK;
@@ -1603,6 +1628,13 @@ int ctd::run_rounds(ctd_ctx *ctx, std::vector<ctd_case *> &cases, uint64_t count
                     const std::function<uint64_t(uint64_t, size_t)> &size, const ctd_tuning &t,
                     bool timed) {
   for (uint64_t r = 0; r < count;) {
+    // beamlets of one batch, grouped or not: callers of ctd_run_batches_static
+    // size the buffer with a run of the same batch size
+    for (size_t i = 0; i < cases.size(); ++i)
+      if (cases[i]->d_mh_state) {
+        const int rc = ensure_mh_buffer(ctx, cases[i], size(r, i));
+        if (rc != CTD_OK) return rc;
+      }
     const uint64_t g = group_rounds(ctx, cases, r, count, size, t);
     std::vector<std::vector<uint64_t>> n((size_t)g, std::vector<uint64_t>(cases.size()));
     for (uint64_t k = 0; k < g; ++k)

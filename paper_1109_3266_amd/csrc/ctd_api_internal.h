@@ -63,10 +63,12 @@ struct ctd_ctx {
   void *rec = nullptr, *rec_head = nullptr;
   size_t rec_segs = 0, rec_heads = 0;
   // batch tallies of the launches that run several batches at once
-  // (run_group), zero between launches unless group_dirty; grown on demand,
-  // at most kGroupMaxBytes, freed with the context; kept where the records are
+  // (run_group), zero between launches unless group_dirty, and their Alg. A1
+  // beamlets; grown on demand, together at most kGroupMaxBytes, freed with the
+  // context; kept where the records are
   unsigned long long *group_tally = nullptr;
-  size_t group_words = 0;
+  int32_t *group_beam = nullptr;
+  size_t group_words = 0, group_beams = 0;
   bool group_dirty = false;
   // ctd_debug_limits: device memory of the workspaces and one allocation
   // together (0: no limit), segments per workgroup of a record-keeping launch
