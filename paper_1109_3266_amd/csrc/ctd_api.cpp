@@ -1698,15 +1698,27 @@ extern "C" int32_t ctd_run_many(ctd_ctx *ctx, ctd_case *const *cs, const uint64_
         ctx, cases, rounds,
         [&](uint64_t r, size_t i) { return r < sizes[i].size() ? sizes[i][r] : (uint64_t)0; }, t,
         count == 1);
-  for (int i = 0; i < count; ++i)
-    if (n[i]) NEED_INTACT(ctx, cases[i]);
+  // what a later case may be refused for, before the first case's work is
+  // enqueued
+  std::vector<uint64_t> h0;
+  for (int i = 0; i < count; ++i) {
+    h0.push_back(cases[i]->h_next);
+    if (n[i] == 0) continue;
+    NEED_INTACT(ctx, cases[i]);
+    if (cases[i]->d_mh_state) {
+      const int rc = ensure_mh_buffer(ctx, cases[i], sizes[i][0]);
+      if (rc != CTD_OK) return rc;
+    }
+  }
   for (int i = 0; i < count; ++i) {
     std::vector<ctd_case *> one{cases[i]};
     const int rc = run_rounds(ctx, one, sizes[i].size(),
                               [&](uint64_t r, size_t) { return sizes[i][r]; }, t, false);
     if (rc == CTD_OK) continue;
-    // a case left part-way through its batches spoils the whole call
-    if (cases[i]->failed)
+    // a failure with part of the work enqueued spoils the whole call
+    bool begun = false;
+    for (int k = 0; k <= i; ++k) begun |= cases[k]->failed || cases[k]->h_next != h0[(size_t)k];
+    if (begun)
       for (int k = 0; k < count; ++k)
         if (n[k]) cases[k]->failed = true;
     return rc;

@@ -92,3 +92,28 @@ def test_static_entry_after_a_grouped_run(ctx):
         with pytest.raises(L.CtdError) as e:
             L.ctd_run_batches_static(ctx, c.cs, 5_001, 1)
         assert e.value.code == L.CTD_EINVAL
+
+
+def test_run_many_refused_for_a_later_case(ctx):
+    """A batched run whose last case cannot have its beamlets leaves every case
+    as it was; with the memory it equals the cases alone."""
+    print("[gpu-test] run_many without memory for its last case", flush=True)
+    wls = [W.tiny(), W.head(scale=8), _chains(100)]
+    ns = [20_000, 10_001, 30_000_000]
+    objs = [Case(ctx, wl) for wl in wls]
+    try:
+        for rounds in (False, True):
+            L.ctd_debug_limits(ctx, memory_bytes=4_000_000, rounds=rounds)
+            with pytest.raises(L.CtdError) as e:
+                L.ctd_run_many(ctx, [o.cs for o in objs], ns)
+            assert e.value.code == L.CTD_ENOMEM
+            assert all(o.stats().n_histories == 0 and o.stats().n_batches == 0 for o in objs)
+        L.ctd_debug_limits(ctx)
+        L.ctd_run_many(ctx, [o.cs for o in objs], ns)
+        for o, wl, n in zip(objs, wls, ns):
+            with Case(ctx, wl) as c:
+                c.run(n)
+                _same(_state(o), _state(c))
+    finally:
+        for o in objs:
+            o.close()
