@@ -43,6 +43,14 @@
  *     fails after enqueueing part of a round (a launch or copy error) leaves
  *     their sums, counters and history ids undefined: the calls that run or
  *     read such a case return CTD_EINVAL until ctd_case_reset.
+ *   - A context keeps workspaces for the calls that use them: on the device,
+ *     deposit records (at most 6 GiB, and an eighth of what is free), tallies
+ *     and Alg. A1 beamlets of batches that share a launch (1 GiB each, and an
+ *     eighth) and a block of ctd_gamma (256 MiB), and 48 MiB of pinned host
+ *     memory.  Launches that find no room for them do without.  They are
+ *     given back where another device allocation of the context finds no
+ *     memory, and by ctd_destroy.  A server's contexts keep none of the first
+ *     three.
  */
 #ifndef CTD_H
 #define CTD_H

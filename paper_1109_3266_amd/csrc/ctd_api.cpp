@@ -76,7 +76,19 @@ size_t ctd::workspace_bytes(const ctd_ctx *ctx) {
          4 * ctx->group_beams + ctx->tool_cap;
 }
 
-hipError_t ctd::dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes) {
+// Give the workspaces back; the next launches that want them make them anew.
+static void release_workspaces(ctd_ctx *ctx) {
+  (void)hipStreamSynchronize(ctx->stream);
+  for (void **p : {&ctx->rec, &ctx->rec_head, (void **)&ctx->group_tally,
+                   (void **)&ctx->group_beam, &ctx->tool_ws}) {
+    dfree(*p);
+    *p = nullptr;
+  }
+  ctx->rec_segs = ctx->rec_heads = ctx->group_words = ctx->group_beams = ctx->tool_cap = 0;
+  ctx->group_dirty = false;
+}
+
+hipError_t ctd::workspace_alloc(ctd_ctx *ctx, void **p, size_t bytes) {
   *p = nullptr;
   hipError_t e = hipErrorOutOfMemory;
   if (!ctx->debug_memory || bytes + workspace_bytes(ctx) <= ctx->debug_memory)
@@ -84,6 +96,15 @@ hipError_t ctd::dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes) {
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
+  }
+  return e;
+}
+
+hipError_t ctd::dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes) {
+  hipError_t e = workspace_alloc(ctx, p, bytes);
+  if (e == hipErrorOutOfMemory && workspace_bytes(ctx) > 0) {
+    release_workspaces(ctx);
+    e = workspace_alloc(ctx, p, bytes);
   }
   return e;
 }
@@ -158,11 +179,7 @@ extern "C" int32_t ctd_destroy(ctd_ctx *ctx) {
   }
   dfree(ctx->sigma_scratch);
   dfree(ctx->pack_stats);
-  dfree(ctx->tool_ws);
-  dfree(ctx->rec);
-  dfree(ctx->rec_head);
-  dfree(ctx->group_tally);
-  dfree(ctx->group_beam);
+  release_workspaces(ctx);
   if (ctx->sigma_host) (void)hipHostFree(ctx->sigma_host);
   if (ctx->read_host) (void)hipHostFree(ctx->read_host);
   if (ctx->own) (void)hipStreamDestroy(ctx->own);
@@ -1228,9 +1245,8 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
       ctx->rec = nullptr;
       ctx->rec_head = nullptr;
       ctx->rec_segs = ctx->rec_heads = 0;
-      if (dev_alloc(ctx, &ctx->rec, segs * kSegBytes) != hipSuccess ||
-          dev_alloc(ctx, &ctx->rec_head, hb) != hipSuccess) {
-        (void)hipGetLastError();
+      if (workspace_alloc(ctx, &ctx->rec, segs * kSegBytes) != hipSuccess ||
+          workspace_alloc(ctx, &ctx->rec_head, hb) != hipSuccess) {
         dfree(ctx->rec);
         ctx->rec = nullptr;
         return false;
@@ -1413,14 +1429,14 @@ static bool reserve_group(ctd_ctx *ctx, size_t words, size_t beams) {
     dfree(ctx->group_beam);
     ctx->group_beam = nullptr;
     ctx->group_beams = 0;
-    if (dev_alloc(ctx, &ctx->group_beam, 4 * beams) != hipSuccess) return false;
+    if (workspace_alloc(ctx, (void **)&ctx->group_beam, 4 * beams) != hipSuccess) return false;
     ctx->group_beams = beams;
   }
   if (more_words) {
     dfree(ctx->group_tally);
     ctx->group_tally = nullptr;
     ctx->group_words = 0;
-    if (dev_alloc(ctx, &ctx->group_tally, 8 * words) != hipSuccess) return false;
+    if (workspace_alloc(ctx, (void **)&ctx->group_tally, 8 * words) != hipSuccess) return false;
     ctx->group_words = words;
     ctx->group_dirty = true;
   }

@@ -64,8 +64,8 @@ struct ctd_ctx {
   size_t rec_segs = 0, rec_heads = 0;
   // batch tallies of the launches that run several batches at once
   // (run_group), zero between launches unless group_dirty, and their Alg. A1
-  // beamlets; grown on demand, together at most kGroupMaxBytes, freed with the
-  // context; kept where the records are
+  // beamlets; grown on demand, a launch's at most kGroupMaxBytes, freed with
+  // the context; kept where the records are
   unsigned long long *group_tally = nullptr;
   int32_t *group_beam = nullptr;
   size_t group_words = 0, group_beams = 0;
@@ -239,7 +239,10 @@ uint64_t case_footprint(const ctd_grid &g, const ctd_geometry *geo, const ctd_pa
 // Device memory of the context's workspaces (records, group tallies, tools).
 size_t workspace_bytes(const ctd_ctx *ctx);
 // hipMalloc within ctd_debug_limits; a failure leaves no error behind for the
-// check of a later launch.
+// check of a later launch.  workspace_alloc is for the workspaces themselves;
+// dev_alloc, for everything else, gives them back where the memory does not
+// suffice and tries again (so not between planning a launch and enqueueing it).
+hipError_t workspace_alloc(ctd_ctx *ctx, void **p, size_t bytes);
 hipError_t dev_alloc_bytes(ctd_ctx *ctx, void **p, size_t bytes);
 template <typename T>
 hipError_t dev_alloc(ctd_ctx *ctx, T **p, size_t bytes) {
