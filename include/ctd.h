@@ -219,7 +219,8 @@ typedef struct {
                             to the XCD tally); 6 KB of LDS per wave, rejected
                             where the workgroup would exceed the LDS limit.
                             Tallies are integer sums: every mode gives the
-                            same bits. */
+                            same bits.  Batches share launches and keep
+                            deposit records under mode 0 only. */
   int32_t bound_block;   /* Early rejection of fictitious collisions (GLOBAL
                             tracking of phantoms stored as 8-byte records,
                             and of piecewise-constant ones where few
@@ -337,9 +338,10 @@ int32_t ctd_case_reset(ctd_ctx *ctx, ctd_case *cs);
 /* Launch configuration for this case (defaults are chosen at creation). */
 int32_t ctd_set_tuning(ctd_ctx *ctx, ctd_case *cs, const ctd_tuning *t);
 int32_t ctd_get_tuning(ctd_ctx *ctx, const ctd_case *cs, ctd_tuning *t);
-/* Time a few launch configurations on `trial_histories` histories of this
- * case (run on a scratch copy of the tallies; the case is left unchanged)
- * and keep the fastest.  Synchronous. */
+/* Time a few launch configurations on a batch of `trial_histories` histories of
+ * this case, the fastest of them and the default again on n_batches (at most
+ * 10) such batches, run as ctd_run_batches runs them, and keep the fastest.
+ * On a scratch copy of the tallies: the case is left unchanged.  Synchronous. */
 int32_t ctd_autotune(ctd_ctx *ctx, ctd_case *cs, uint64_t trial_histories, ctd_tuning *best);
 
 /* Run n_histories as n_batches equal batches (the first n mod n_batches

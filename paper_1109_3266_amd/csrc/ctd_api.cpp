@@ -2233,11 +2233,11 @@ extern "C" int32_t ctd_autotune(ctd_ctx *ctx, ctd_case *cs, uint64_t trial_histo
     release();
     return rc;
   }
-  // stage 1: launch shape and tally mode with the default bound grid; stage
-  // 2 (below): the bound grid's block size for the best of stage 1
+  // launch shape and tally mode with the default bound grid first, then the
+  // bound grid's block size and the collision deferral, each varied around the
+  // best so far; one batch each
   const bool bounded = cs->use_bound_grid && cs->mc_cs == 0;
-  const int bb0 = bounded ? default_tuning(ctx).bound_block : 0;
-  const int dm0 = default_tuning(ctx).defer_min;
+  const ctd_tuning def = default_tuning(ctx);
   std::vector<ctd_tuning> cand;
   for (int tm = ctx->xcd_tally_ok ? 2 : 0; tm >= 0; --tm) {
     if (!transport_lds_fits(256, tm, ctx->device)) continue;
@@ -2250,51 +2250,91 @@ extern "C" int32_t ctd_autotune(ctd_ctx *ctx, ctd_case *cs, uint64_t trial_histo
           t.refill_min = rm;
           t.chunk = ch;
           t.tally_mode = tm;
-          t.bound_block = bb0;
-          t.defer_min = dm0;
+          t.bound_block = bounded ? def.bound_block : 0;
+          t.defer_min = def.defer_min;
           cand.push_back(t);
         }
   }
-  const size_t stage1 = cand.size();
   hipEvent_t a, b;
   (void)hipEventCreate(&a);
   (void)hipEventCreate(&b);
-  double best_ms = INFINITY;
-  ctd_tuning best_t = cs->tune;
   std::vector<ctd_case *> one{&tw};
-  for (size_t i = 0;; ++i) {
-    // stage 2: the bound grid's block size, then the collision deferral, each
-    // varied around the best so far
-    if (i == stage1 + 1 && bounded) {
-      for (int bb : {0, 1, 2, 4}) {
-        if (bb == best_t.bound_block) continue;
-        ctd_tuning t = best_t;
-        t.bound_block = bb;
-        cand.push_back(t);
-      }
-    }
-    if (i == stage1 + 4 && bounded && best_t.bound_block > 0) {
-      for (int dm : {0, 8, 16, 32}) {
-        if (dm == best_t.defer_min) continue;
-        ctd_tuning t = best_t;
-        t.defer_min = dm;
-        cand.push_back(t);
-      }
-    }
-    if (i > cand.size()) break;
-    const ctd_tuning t = i == 0 ? cand[0] : cand[i - 1];  // first run warms up
+  struct Timed {
+    double ms;
+    ctd_tuning t;
+  };
+  std::vector<Timed> timed;   // ascending
+  // `count` batches under t, into `timed` unless they warm up; false on an error
+  const auto trial = [&](const ctd_tuning &t, uint64_t count, bool warm_up) {
     (void)hipEventRecord(a, ctx->stream);
-    rc = run_round(ctx, one, std::vector<uint64_t>{trial_histories}, t);
-    if (rc != CTD_OK) break;
+    rc = run_rounds(ctx, one, count, [&](uint64_t, size_t) { return trial_histories; }, t, false);
+    if (rc != CTD_OK) return false;
     (void)hipEventRecord(b, ctx->stream);
     (void)hipEventSynchronize(b);
     float ms = 0.f;
     (void)hipEventElapsedTime(&ms, a, b);
-    if (i > 0 && ms < best_ms) {
-      best_ms = ms;
-      best_t = t;
+    if (!warm_up)
+      timed.insert(std::upper_bound(timed.begin(), timed.end(), (double)ms,
+                                    [](double x, const Timed &y) { return x < y.ms; }),
+                   Timed{(double)ms, t});
+    return true;
+  };
+  const auto same = [](const ctd_tuning &x, const ctd_tuning &y) {
+    return std::memcmp(&x, &y, sizeof x) == 0;
+  };
+  bool ok = trial(cand[0], 1, true);
+  for (size_t i = 0; ok && i < cand.size(); ++i) ok = trial(cand[i], 1, false);
+  if (ok && bounded) {
+    const ctd_tuning best = timed[0].t;
+    for (int bb : {0, 1, 2, 4}) {
+      // (a palette phantom's grid has single voxels whatever the edge)
+      if (!ok || bb == best.bound_block || (cs->ph->npal > 0 && bb != 0)) continue;
+      ctd_tuning t = best;
+      t.bound_block = bb;
+      ok = trial(t, 1, false);
     }
   }
+  if (ok && bounded && timed[0].t.bound_block > 0) {
+    const ctd_tuning best = timed[0].t;
+    for (int dm : {0, 8, 16, 32}) {
+      ctd_tuning t = best;
+      t.defer_min = dm;
+      if (ok && dm != best.defer_min) ok = trial(t, 1, false);
+    }
+  }
+  // A run's batches share launches and keep deposit records under tally mode 0
+  // where they are many or large enough, which one batch does not show: the
+  // fastest few, the fastest of each tally mode and the default are timed
+  // again over several batches, the same histories each.
+  if (ok) {
+    std::vector<ctd_tuning> last{def};
+    const auto add = [&](const ctd_tuning &t) {
+      for (const ctd_tuning &u : last)
+        if (same(t, u)) return;
+      last.push_back(t);
+    };
+    for (size_t i = 0; i < timed.size() && i < 3; ++i) add(timed[i].t);
+    for (int tm = 0; tm < 3; ++tm)
+      for (const Timed &x : timed)
+        if (x.t.tally_mode == tm) {
+          add(x.t);
+          break;
+        }
+    timed.clear();
+    const uint64_t count = (uint64_t)std::min(cs->p.n_batches, 10);
+    for (size_t i = 0; ok && i < 2 * last.size() + 1; ++i) {
+      if (launch_zero(tw.d_s1, 8 * V, ctx->stream) || launch_zero(tw.d_s2, 16 * V, ctx->stream) ||
+          launch_zero(tw.d_acc, 8 * kAccWords, ctx->stream)) {
+        rc = hip_err(ctx, hipGetLastError(), "autotune clear");
+        ok = false;
+        break;
+      }
+      tw.s1_bound = tw.s2_bound = 0.0;
+      tw.h_next = 0;
+      ok = trial(last[i == 0 ? 0 : (i - 1) % last.size()], count, i == 0);
+    }
+  }
+  const ctd_tuning best_t = ok ? timed[0].t : cs->tune;
   for (auto &t : tw.timing) {
     (void)hipEventDestroy(t.a);
     (void)hipEventDestroy(t.b);
