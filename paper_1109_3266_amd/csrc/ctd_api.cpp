@@ -1183,7 +1183,30 @@ constexpr size_t kRecordMaxBytes = (size_t)6 << 30;
 // Records to make room for per history, by the case's deposit share: water
 // 2.6, the pencil beam 4, bodies in air 0.7-1.3.  Deposits beyond it go to the
 // tally.
+// Records of a launch that finds less memory than 1 / kDenseRoom or 1 /
+// kOtherRoom of that cost more than they save: a deposit without a place pays
+// for looking before it goes to the tally.  With 1/50, 1/24, 1/12, 1/6, 1/3 of
+// the room and all of it, ms per 1e8 histories: water 11.6, 11.3, 10.7, 9.8,
+// 7.9, 6.1, tally alone 11.4; a body in air on 8e6 voxels 9.5, 9.4, 9.3, 9.1,
+// 8.9, 8.0, tally 8.7, and on 2e6 voxels 9.3, 9.2, 9.1, 8.9, 8.1, 6.4, tally 8.7 (one
+// batch of 2.2e9 with 1/7 of the room: 187.5 and 179.1 ms, tally 186.0 and
+// 186.7).
+constexpr double kDenseRoom = 32.0, kOtherRoom = 8.0;
 static double record_room(double share) { return share >= kDenseShare ? 5.0 : 2.5; }
+
+// Device memory that is free (within ctd_debug_limits); false: unknown.
+static bool free_memory(ctd_ctx *ctx, size_t *free_b) {
+  size_t total_b = 0;
+  if (hipMemGetInfo(free_b, &total_b) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  if (ctx->debug_memory) {
+    const size_t held = workspace_bytes(ctx);
+    *free_b = std::min(*free_b, ctx->debug_memory > held ? (size_t)ctx->debug_memory - held : 0);
+  }
+  return true;
+}
 
 static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, RoundCase *rc,
                          const LaunchCfg &cfg, int kind, bool with_log, DepositLog &dl,
@@ -1224,21 +1247,22 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
   want += (double)std::min(total, 2 * most);   // a part-filled segment per bucket
   size_t per_wg = (size_t)std::ceil(std::min(want, 1e9));
   const size_t heads = (size_t)cfg.grid * total;
+  const auto enough = [&](size_t segs) {
+    return (double)segs >= want / (dense ? kDenseRoom : kOtherRoom) * (double)cfg.grid + 1.0;
+  };
   const size_t segs_of = ctx->rec_segs;
   if (ctx->rec_heads < heads || segs_of < per_wg * cfg.grid + 1) {
     // grown to what the launch wants, within kRecordMaxBytes and an eighth of
     // the memory that is free (with what is given back first)
-    size_t free_b = 0, total_b = 0;
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
-      (void)hipGetLastError();
-      return false;
-    }
+    size_t free_b = 0;
+    if (!free_memory(ctx, &free_b)) return false;
     const size_t have = segs_of * kSegBytes + ctx->rec_heads * 8;
     const size_t lim = std::min(kRecordMaxBytes, (free_b + have) / 8);
     const size_t hb = std::max(ctx->rec_heads, heads) * 8;
     if (hb >= lim) return false;
     const size_t segs = std::min((lim - hb) / kSegBytes, std::max(segs_of, per_wg * cfg.grid + 1));
     if (segs > segs_of || ctx->rec_heads < heads) {
+      if (!enough(segs)) return false;
       if (hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
       dfree(ctx->rec);
       dfree(ctx->rec_head);
@@ -1256,6 +1280,7 @@ static bool plan_records(ctd_ctx *ctx, const std::vector<RoundItem> &items, Roun
     }
   }
   per_wg = std::min(per_wg, (ctx->rec_segs - 1) / (size_t)cfg.grid);
+  if (!enough(per_wg * (size_t)cfg.grid + 1)) return false;
   if (ctx->debug_segments) per_wg = std::min(per_wg, (size_t)ctx->debug_segments);
   if (per_wg == 0) return false;
   dl.rec = (uint2 *)ctx->rec;
@@ -1417,9 +1442,9 @@ constexpr size_t kGroupMaxBytes = (size_t)1 << 30;
 static bool reserve_group(ctd_ctx *ctx, size_t words, size_t beams) {
   const bool more_words = ctx->group_words < words, more_beams = ctx->group_beams < beams;
   if (more_words || more_beams) {
-    size_t free_b = 0, total_b = 0;
+    size_t free_b = 0;
     const size_t bytes = (more_words ? 8 * words : 0) + (more_beams ? 4 * beams : 0);
-    if (hipMemGetInfo(&free_b, &total_b) != hipSuccess || bytes > free_b / 8 ||
+    if (!free_memory(ctx, &free_b) || bytes > free_b / 8 ||
         hipStreamSynchronize(ctx->stream) != hipSuccess) {
       (void)hipGetLastError();
       return false;

@@ -75,6 +75,26 @@ def test_records_run_out(ctx, shape, pencil, batch, segments):
         _same(_state(a), _state(b))
 
 
+def test_too_little_memory_for_records(ctx):
+    """A launch whose records would find less than 1/32 of the room it wants
+    (1.2 GB here) adds its deposits to the tally; with more it keeps what it
+    can, also in a block made for another launch."""
+    print("[gpu-test] records by memory", flush=True)
+    wl = _box(32, 32, 32, False)
+    with Case(ctx, wl) as a, Case(ctx, wl) as b:
+        L.ctd_debug_deposit_log(ctx, b.cs, 0, 1, 64)
+        for free, batch, recorded in [(200, 30, 0), (600, 30, 1), (0, 1, 1), (1, 30, 1)]:
+            n0, r0 = L.ctd_debug_launches(ctx)
+            # MB; an eighth of what is free counts
+            L.ctd_debug_limits(ctx, memory_bytes=free * 1_000_000)
+            L.ctd_run_batches(ctx, a.cs, batch * 1_000_000, 1)
+            n1, r1 = L.ctd_debug_launches(ctx)
+            assert (n1 - n0, r1 - r0) == (1, recorded)
+            L.ctd_debug_limits(ctx)
+            L.ctd_run_batches(ctx, b.cs, batch * 1_000_000, 1)
+            _same(_state(a), _state(b))
+
+
 @pytest.mark.parametrize("segments", [0, 20])
 def test_records_of_several_cases_in_a_launch(ctx, segments):
     print(f"[gpu-test] records in rounds, {segments} segments", flush=True)
