@@ -1978,6 +1978,9 @@ int ctd::read_planes(ctd_ctx *ctx, int64_t V, int planes, size_t elem, void *con
                               hipHostMallocDefault));
     ctx->read_cap = slot_bytes * (size_t)threads;
   }
+  // (the per-thread default stream is another one in each helper: what the
+  // caller has enqueued on its own comes first)
+  if (ctx->stream == hipStreamPerThread) HIPCHK(ctx, hipStreamSynchronize(ctx->stream));
   std::vector<hipError_t> status((size_t)threads, hipSuccess);
   std::atomic<int64_t> next{0};
   std::mutex enqueue;   // an event is recorded right behind its own kernel
