@@ -7,7 +7,8 @@ cortical bone, brain, air sinuses and a lung-like insert in air; half-fan
 cone beam at SAD 100 cm, 200 projections over 360 deg, 100 kVp Kramers
 spectrum with 2 mm Al in 1 keV bins, Rayleigh on; Woodcock tracking against
 the paper's global majorant; batches of 1e8 histories.  One step = one batch:
-transport launch plus the batch fold.  Inputs are resident in device memory
+its histories in a transport launch (which several batches may share) and the
+batch's fold.  Inputs are resident in device memory
 before timing.
 
     python bench.py [--gpus 1] [--steps 10] [--warmup 2] [--no-cpu] [--quick]
@@ -91,8 +92,11 @@ PINNED_TUNING = {
     "head": (256, 5, 16, 1024, 0, 2, 16),
     "head_helical": (256, 5, 16, 1024, 0, 2, 16),
     "water_cbct": (256, 5, 16, 1024, 0, 2, 16),
-    "water_box_bowtie": (256, 5, 32, 1024, 1, 2, 16),
-    "tiny": (256, 4, 16, 1024, 2, 2, 16),
+    # per-XCD tallies (mode 1, and mode 2 on tiny) share no launches and keep no
+    # deposit records: 105.6 against 41.1 ms per ten batches of 1e8 histories,
+    # and 78.0 against 50.6
+    "water_box_bowtie": (256, 5, 16, 1024, 0, 2, 16),
+    "tiny": (256, 5, 16, 1024, 0, 2, 16),
 }
 
 
@@ -106,15 +110,15 @@ def counter_file(workload: str, records: bool = False) -> str:
 
 def counter_commands(workload: str, records: bool = False) -> list:
     """rocprofv3 runs behind counter_file (one counter group per run,
-    repository root).  The static entry point adds
-    every deposit to the tally."""
+    repository root).  The static entry point adds every deposit to the tally."""
+    d = f"gpurun_out/pmc_{workload}" + ("_records" if records else "")
     b = (f"python -u bench.py --quick --no-cpu --workload {workload} --steps 2 --warmup 0"
          + ("" if records else " --static"))
     return [
-        f"rocprofv3 --pmc FETCH_SIZE -f csv -d gpurun_out/pmc_{workload}_fetch -o f -- {b}",
-        f"rocprofv3 --pmc WRITE_SIZE -f csv -d gpurun_out/pmc_{workload}_write -o w -- {b}",
+        f"rocprofv3 --pmc FETCH_SIZE -f csv -d {d}_fetch -o f -- {b}",
+        f"rocprofv3 --pmc WRITE_SIZE -f csv -d {d}_write -o w -- {b}",
         f"rocprofv3 --pmc VALUBusy VALUUtilization SQ_INSTS_VALU SQ_INSTS_SALU -f csv "
-        f"-d gpurun_out/pmc_{workload}_valu -o v -- {b}",
+        f"-d {d}_valu -o v -- {b}",
         "rocprofv3 --pmc FETCH_SIZE -f csv -d gpurun_out/pmc_copy_fetch -o cf -- "
         "python -u bench.py --calibrate-copy",
         "rocprofv3 --pmc WRITE_SIZE -f csv -d gpurun_out/pmc_copy_write -o cw -- "
@@ -144,12 +148,14 @@ def summarize_counters(workload: str, records: bool = False):
     # (2, 0), or plain steps (0, 0) and steps with collision passes (0, 1)
     kerns = ("k_transport<2, 0,",) if records else ("k_transport<0, 0,", "k_transport<0, 1,")
 
+    runs = f"gpurun_out/pmc_{workload}" + ("_records" if records else "")
+
     def per_launch(d, name):
         v = [x for k, n, x, _ in _pmc_rows(d) if any(p in k for p in kerns) and n == name]
         return statistics.mean(v), len(v)
 
     names = sorted({k.split("(")[0].replace("void ctd::", "")
-                    for k, n, x, _ in _pmc_rows(f"gpurun_out/pmc_{workload}_fetch")
+                    for k, n, x, _ in _pmc_rows(f"{runs}_fetch")
                     if any(p in k for p in kerns)})
 
     def copy_scale(d, name):
@@ -157,11 +163,11 @@ def summarize_counters(workload: str, records: bool = False):
                    reverse=True)[:3]
         return float(1 << 20) / statistics.median(v)   # KiB counted per KiB moved
 
-    fetch, n1 = per_launch(f"gpurun_out/pmc_{workload}_fetch", "FETCH_SIZE")
-    write, n2 = per_launch(f"gpurun_out/pmc_{workload}_write", "WRITE_SIZE")
+    fetch, n1 = per_launch(f"{runs}_fetch", "FETCH_SIZE")
+    write, n2 = per_launch(f"{runs}_write", "WRITE_SIZE")
     fs = copy_scale("gpurun_out/pmc_copy_fetch", "FETCH_SIZE")
     ws = copy_scale("gpurun_out/pmc_copy_write", "WRITE_SIZE")
-    valu = {name: per_launch(f"gpurun_out/pmc_{workload}_valu", name)[0]
+    valu = {name: per_launch(f"{runs}_valu", name)[0]
             for name in ("VALUBusy", "VALUUtilization", "SQ_INSTS_VALU", "SQ_INSTS_SALU")}
     t = PINNED_TUNING[workload]
     out = dict(kernel=", ".join(names), workload=workload,
@@ -267,8 +273,9 @@ def other_oracle_rates(threads: int):
 
 
 def batched_leg(ctx, L, W, Case, tuning, torch, hist_scale, tracking=None):
-    """48 uneven cases: each run alone back to back (plain per-case launches)
-    vs one batched launch per round over all cases; results must match.
+    """48 uneven cases: each run alone back to back vs all in one batched call
+    (which runs them one after another, or in rounds over all cases where their
+    batches cannot share launches); results must match.
     tracking: None (each case's own, the global majorant) or a CTD_TRACK_*
     mode for every case on both sides."""
     import numpy as np
@@ -643,6 +650,7 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     run_batches(ctx, case.cs, BATCH, warmup)
     torch.cuda.synchronize()
     st0 = L.ctd_read_stats(ctx, case.cs)
+    launches0, recorded0 = L.ctd_debug_launches(ctx)
     torch.cuda.synchronize()
     ev0 = torch.cuda.Event(enable_timing=True)
     ev1 = torch.cuda.Event(enable_timing=True)
@@ -655,15 +663,17 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     gpu_ms = ev0.elapsed_time(ev1)
     assert gpu_ms > 0.5 * wall * 1e3, "timing events do not bracket the library's work"
     st1 = L.ctd_read_stats(ctx, case.cs)
+    launches1, recorded1 = L.ctd_debug_launches(ctx)
     bal = L.ctd_read_balance(ctx, case.cs)
     assert bal.q_incident == bal.q_deposited + bal.q_escaped, "energy balance broken"
     n_timed = steps * BATCH
     value = n_timed / wall
     log(f"{name}: {value:.4g} histories/s ({wall:.3f} s wall, {gpu_ms:.1f} ms events)")
 
-    # roofline of the dominant kernel (k_transport): one launch = one batch;
-    # launch time from the HIP events the library records around each
-    # transport launch on its stream
+    # roofline of the dominant kernel (k_transport), per batch: its share of the
+    # launches' time, from the HIP events the library records around each
+    # transport launch on its stream (batches may share a launch; one that keeps
+    # deposit records is followed by their collection, which the events include)
     d_steps = st1.n_steps - st0.n_steps
     d_scat = (st1.n_compton - st0.n_compton) + (st1.n_rayleigh - st0.n_rayleigh)
     d_comp = st1.n_compton - st0.n_compton
@@ -682,9 +692,9 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     hbm = alg_bytes / steps / launch_s
     atom_rate = d_dep / steps / launch_s
     atom_peak, _ = L.ctd_microbench(ctx, 1, wl.n_voxels * 8, 1 << 28)
-    # deposits faster than the memory side's atomics went through deposit
-    # records (summed in LDS by k_collect): the atomics bound nothing then
-    recorded = atom_rate > atom_peak
+    # launches that kept deposit records sum them in LDS (k_collect): the
+    # memory side's atomics bound nothing then
+    recorded = recorded1 > recorded0
     counters = (load_counters(name, tuning, recorded) if tracking == L.CTD_TRACK_GLOBAL
                 else None)
     traffic = (counters["hbm_bytes_per_launch"] / counters["histories_per_launch"] * BATCH
@@ -703,7 +713,10 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
     peak = dict(alu=PEAK_LANE_OPS / 1e12, hbm=8000.0, atomic=atom_peak)[bound]
     roof = dict(bound=bound, achieved=ach, peak=peak, unit=unit, frac=fracs[bound],
                 traffic=traffic, kernel="k_transport", launch_ms=launch_ms,
-                note="bound = the largest of the ALU, HBM and atomic fractions below",
+                launches=steps if static else launches1 - launches0,
+                launches_with_records=recorded1 - recorded0,
+                note="bound = the largest of the ALU, HBM and atomic fractions below; "
+                     "launch_ms: a batch's share of its launch",
                 ops_per_history=ops / n_timed, steps_per_history=d_steps / n_timed,
                 deposits_per_history=d_dep / n_timed,
                 alu=dict(achieved=alu / 1e12, peak=PEAK_LANE_OPS / 1e12, unit="T lane-ops/s",
@@ -717,8 +730,8 @@ def transport_leg(ctx, L, W, Case, torch, stream, name: str, steps: int, warmup:
                             frac=fracs["atomic"],
                             peak_source="ctd_microbench random 64-bit atomics into a "
                                         "tally-sized array, measured in this run",
-                            note="deposits per second; above the peak: kept as records and "
-                                 "summed in LDS, not tally atomics" if recorded else
+                            note="deposits per second, kept as records and summed in LDS, "
+                                 "not tally atomics" if recorded else
                                  "tally updates per second; with tally_mode 2 part of them "
                                  "are LDS atomics" if tuning.tally_mode == 2 else ""))
     out = dict(workload=WORKLOADS[name] + ("" if tracking == L.CTD_TRACK_GLOBAL
