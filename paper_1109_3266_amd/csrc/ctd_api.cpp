@@ -614,9 +614,11 @@ static int mean_energy_node(const ctd_egrid &eg, const ctd_spectrum *sp) {
   return std::min(std::max((int)std::lround((emean - eg.e0) / eg.de), 0), eg.ne - 1);
 }
 
-// CTD_TRACK_AUTO: macro-cell majorants pay where one material's attenuation
-// sets the global majorant well above that of the material filling most of
-// the phantom (bone in tissue): at the spectrum's mean energy, the largest
+// CTD_TRACK_AUTO: macro-cell majorants save most steps where one material's
+// attenuation sets the global majorant well above that of the material filling
+// most of the phantom (bone in tissue; since the global steps park their
+// collisions they are the faster ones on the head all the same, and the rule
+// stays for the random streams it picks): at the spectrum's mean energy, the largest
 // rho_max * mu/rho over the present materials against that of the most
 // frequent material denser than 0.05 g/cm^3; MACRO above 1.5.  Depends on
 // the inputs only, so a case's histories do not depend on the machine.
@@ -685,10 +687,17 @@ static bool bound_test_in_range(const ctd_phantom *ph, const std::vector<float> 
 }
 
 // Palette phantoms take the deferred steps (collision passes on full waves, the
-// coarse bound grid, no deposit records) below this share of collisions that
-// deposit: bodies with bone (shares 0.05-0.07, 35-45 steps per history) 15.8
-// and 10.6 ms per 1e8 histories on 6.7e5 voxels, 21.4 and 13.0 on 4.8e6; bodies
-// without (0.24-0.33, 5-7 steps) 5.3 and 5.7-6.2 ms, water 56 and 113 per 1e9.
+// coarse bound grid) below this share of collisions that deposit: bodies with
+// bone (shares 0.05-0.07, 35-45 steps per history) 15.8 and 10.6 ms per 1e8
+// histories on 6.7e5 voxels, 21.4 and 13.0 on 4.8e6.  Above it they keep the
+// plain steps, because only those have deposit records: a deferred launch adds
+// every deposit to the tally and is held to the atomics' rate where collisions
+// deposit often (bodies without bone, 0.24-0.33: 5.3 ms plain with records and
+// 5.7-6.2 deferred; water 56 and 113 ms per 1e9, of which its 2.55 deposits per
+// history at 2.4e10 atomics/s take 107).  The share is a mean over the voxels and
+// does not know the beam: a beam on a small object in much air counts as few
+// (water of 3.2 cm radius in 32 cm of air, 64^3: 15.4 ms per 2e8, 12.5 plain with
+// records).
 constexpr double kDeferShare = 0.15;
 
 extern "C" int32_t ctd_case_create(ctd_ctx *ctx, ctd_phantom *ph, ctd_matset *ms,
@@ -1174,9 +1183,8 @@ static int launch_chunk(const LaunchCfg &cfg, uint64_t n) {
 //  - at most kRecordBuckets buckets per case, so its cursors fit beside the
 //    tables.
 // A bucket holds as few voxels as give at most 64 buckets (32-64 measured
-// best, 128 and more cost the cube 8 % and more: a bucket's open line stays in
-// L2 while a workgroup fills it), at most the 2^14 whose sums fill 128 KB of
-// LDS.
+// best, 128 and more cost the cube 8 % and more), at most the 2^14 whose sums
+// fill 128 KB of LDS.
 constexpr double kDenseShare = 0.45;
 constexpr int kRecordBuckets = 1024, kRecordMaxBits = 14;
 constexpr size_t kRecordMaxBytes = (size_t)6 << 30;

@@ -252,8 +252,9 @@ hipError_t dev_alloc(ctd_ctx *ctx, T **p, size_t bytes) {
 int ensure_mh_buffer(ctd_ctx *ctx, ctd_case *cs, uint64_t n);
 // Read V voxels as `planes` arrays of elem-byte words into dst (null: plane
 // not wanted).  launch(v0, n, out) enqueues on ctx->stream what writes the
-// planes of n voxels from v0 one behind the other into pinned memory; a few host threads, one staging slot each, copy the pieces to
-// the caller's arrays: filling fresh pages of those is the slow part (4 GB/s on
+// planes of n voxels from v0 one behind the other into pinned memory; a few
+// host threads, one staging slot each, copy the pieces to the caller's arrays:
+// filling fresh pages of those is the slow part (4 GB/s on
 // one thread, against 57 GB/s over the link), so it is spread and overlapped.
 int read_planes(ctd_ctx *ctx, int64_t V, int planes, size_t elem, void *const *dst,
                 const std::function<int(int64_t, int, void *)> &launch);

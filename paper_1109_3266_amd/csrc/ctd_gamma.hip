@@ -157,8 +157,8 @@ __device__ __forceinline__ double lane_f64(double v, int lane) {
 // lanes the head grid takes 6.1 / 5.4 / 5.7 / 6.3 ms a call at 5 % noise).
 constexpr int kFewLanes = 8;
 
-// gamma may be null; counts (kGammaSlots pairs, one 128-byte line each) the voxels with D_ref > region
-// and those with gamma < 1.
+// gamma may be null; counts (kGammaSlots pairs, one 128-byte line each) the
+// voxels with D_ref > region and those with gamma < 1.
 __global__ void __launch_bounds__(256) k_gamma(const float *__restrict__ ref,
                                                const float *__restrict__ ev, int nx, int ny,
                                                int nz, GammaTables t,

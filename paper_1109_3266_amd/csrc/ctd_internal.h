@@ -334,7 +334,8 @@ struct GammaTables {
 };
 constexpr int kGammaSlots = 64;      // counter pairs, 128 bytes apart
 // Gamma index of ev against ref on an nx*ny*nz grid: scale = substeps /
-// dose_tol, cap2 = (gamma_cap substeps)^2; gamma [V] may be null; counts[kGammaSlots][16] (region voxels, passing voxels) accumulate.
+// dose_tol, cap2 = (gamma_cap substeps)^2; gamma [V] may be null;
+// counts[kGammaSlots][16] (region voxels, passing voxels) accumulate.
 int launch_gamma(const float *ref, const float *ev, int nx, int ny, int nz, const GammaTables &t,
                  double scale, double region, double cap2, float *gamma,
                  unsigned long long *counts, void *stream);

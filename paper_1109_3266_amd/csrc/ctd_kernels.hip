@@ -295,9 +295,11 @@ __device__ __forceinline__ void tally_add(const StepCase &S, int32_t vox, unsign
 // installs it, while later lanes add again a bounded number of times.  A lane
 // without a slot after that, or in a workgroup without segments left, adds
 // straight to the tally.  Against the tally's atomics a deposit costs the wave
-// an LDS round trip and 8 bytes into a line that mostly stays in L2 until it is
-// full (water 128x128x100, 1e8 histories: 11.4 ms at 94 % of the memory-side
-// atomic rate, 5.1 ms with records, bound by instruction issue).  The slow
+// an LDS round trip and an 8-byte store instead of an atomic that the memory
+// side performs one by one; no fewer bytes leave the L2, since most lines go
+// out before they are full (37 bytes written per record, 32 per atomic; water
+// 128x128x100, 1e8 histories: 11.4 ms at 94 % of the memory-side atomic rate,
+// 5.2 ms with records, VALU 87 % busy with 60 % of lanes).  The slow
 // path's loop condition is the wave's (a ballot), so the installing lane
 // always runs inside it.
 __device__ __forceinline__ void record_deposit(const StepCase &S, int32_t vox, uint32_t q) {
@@ -1048,8 +1050,8 @@ __device__ __forceinline__ void stage_case(CaseDev *dst, uint2 *pal, const CaseD
 }
 
 // KIND selects the step for every case of the launch (kStepPlain,
-// kStepDeferred, kStepMacro, kStepRecord; a round whose cases need different steps is
-// split into one launch per step), so each instance carries only its own
+// kStepDeferred, kStepMacro, kStepRecord; a round whose cases need different
+// steps is split into one launch per step), so each instance carries only its own
 // step's registers and a tight loop of its steps between refills.  Every
 // instance is held to 96 VGPRs (5 waves per SIMD): the global steps fit
 // without spilling, the macro-cell step spills a few words outside its cell
@@ -1083,7 +1085,7 @@ __global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(5))) k
   LOCAL uint2 *lane_word = (LOCAL uint2 *)(slot + kWaveAccBytes) + lane;
   // staged tables: the majorant nodes and mu/rho rows of the workgroup's
   // current case and its bound-test sums, shared by its waves (room for the
-// round's largest case)
+  // round's largest case)
   LOCAL float *tabmax = nullptr;
   LOCAL float4 *tab = nullptr;
   LOCAL float *tabbnd = nullptr;
